@@ -446,11 +446,12 @@ lbi_status lbi_scan_backward_ragged(const void *A, const void *b, const void *la
  *   M     [n][r][r]  dt storage, row-major.
  *   spec  [n]        OUTPUT float32, or NULL (not computed): ||M_i||_2, to
  *                    within 2e-5 relative.  Method: repeated normalised
- *                    squaring of M^T M on the fp32 matrix cores (24 steps),
- *                    then a Rayleigh quotient; with no spectral-gap assumption
- *                    the iteration's own error is at most r / (2 e 2^24)
- *                    relative (1.4e-6 at r = 128); the rest is float32
- *                    rounding.
+ *                    squaring of M M^T on the matrix cores (fp32 products from
+ *                    exact three-part bf16 splits; at most 24 steps, fewer once
+ *                    the leading singular vector stands out), then a Rayleigh
+ *                    quotient; with no spectral-gap assumption the iteration's
+ *                    own error is at most r / (2 e 2^24) relative (1.4e-6 at
+ *                    r = 128); the rest is float32 rounding.
  *   fro   [n]        OUTPUT float32, or NULL: ||M_i||_F / sqrt(r).
  *   n >= 0; r in {16, 32, 64, 128}.  At least one output; outputs must not
  *   overlap M or each other.  A zero matrix gives 0 in both; a matrix with a

@@ -102,6 +102,27 @@ def test_norms_subnormal_matrix():
     _check(M, "subnormal")
 
 
+@pytest.mark.parametrize("r", [16, 32, 64, 128])
+def test_norms_close_leading_pair(r):
+    """The squarings end when the leading vector stands out; a second singular
+    value from half of the first up to equal to it makes them end after any
+    number of steps, or not at all.  Tolerance: the iteration's 1.4e-6 plus
+    the float32 rounding of a quotient of r-term sums, under 16 ulps."""
+    g = torch.Generator().manual_seed(61)
+    mats = []
+    for k in list(range(1, 26)) + [99]:
+        q1, _ = torch.linalg.qr(torch.randn(r, r, generator=g, dtype=torch.float64))
+        q2, _ = torch.linalg.qr(torch.randn(r, r, generator=g, dtype=torch.float64))
+        s = torch.full((r,), 0.25, dtype=torch.float64)
+        s[0], s[1] = 1.0, 1.0 - 2.0 ** -k
+        mats.append((q1 * s) @ q2)
+    M = torch.stack(mats).to(torch.float32)
+    _say(f"[norms] close pair r={r}")
+    spec, _ = binding.lbi_matrix_norms(M.to(DEV))
+    es = _rel(spec.cpu().numpy(), oracle.matrix_norms(M)[0])
+    assert es.max() <= 1.4e-6 + 16 * 2.0 ** -24, f"r={r}: {es.max():.3g}"
+
+
 def test_norms_non_finite_entries_give_nan():
     r = 32
     M = torch.eye(r).repeat(3, 1, 1)

@@ -76,8 +76,7 @@ typedef enum {
  * lbi_scan_backward_ragged).  bf16 inputs always use the bf16 matrix cores. */
 typedef enum {
     LBI_MATH_DEFAULT = 0,   /* the library's choice: LBI_MATH_F32_SPLIT for
-                             * fp32 at r <= 64, LBI_MATH_F32_MFMA for fp32 at
-                             * r = 128; for bf16 the running fp32 composite is
+                             * fp32; for bf16 the running fp32 composite is
                              * fed back to the matrix cores as bf16 hi + lo
                              * (two products), so the only bf16 rounding is
                              * the inputs'                                      */
@@ -85,8 +84,7 @@ typedef enum {
     LBI_MATH_F32_SPLIT = 2, /* fp32 products from exact three-part bf16 splits
                              * of both operands on the bf16 matrix cores (the
                              * six partial products down to 2^-16 of the leading
-                             * one), fp32 accumulation; r = 128 falls back to
-                             * LBI_MATH_F32_MFMA                                 */
+                             * one), fp32 accumulation                           */
     LBI_MATH_BF16_SINGLE = 3 /* bf16 inputs only (else LBI_ERR_DTYPE) and
                              * K <= LBI_BF16_SINGLE_MAX_K (else
                              * LBI_ERR_SHAPE): the running composite is fed

@@ -18,7 +18,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 SOURCES = ["lbi_chain_f32.hip", "lbi_chain_f32x.hip", "lbi_chain_bf16.hip", "lbi_chain_bf16r1.hip",
-           "lbi_chain_wave.hip",
+           "lbi_chain_wave.hip", "lbi_chain_wide.hip",
            "lbi_chain_ksplit.hip", "lbi_tree.hip", "lbi_chain_ring.hip", "lbi_aux.hip", "lbi_norms.hip", "lbi_region.hip",
            "lbi_api.hip"]
 INCLUDE = os.path.join(ROOT, "include")

@@ -399,9 +399,9 @@ hipError_t launch_chain_mode(const ChainLaunch &c, lbi_dtype dt, lbi_math math)
 {
     if (dt == LBI_BF16)
         return math == LBI_MATH_BF16_SINGLE ? launch_chain_bf16r1(c) : launch_chain_bf16(c);
-    if (math == LBI_MATH_F32_MFMA || c.r == 128)
+    if (math == LBI_MATH_F32_MFMA)
         return launch_chain_f32(c);
-    return launch_chain_f32x(c);
+    return c.r == 128 ? launch_chain_wide_f32x(c) : launch_chain_f32x(c);
 }
 
 // With scratch = true, ws / ws_bytes are the library's static scratch array:

@@ -976,8 +976,8 @@ hipError_t launch_r(const ChainLaunch &c)
     case 64: return launch_kernel<64, M, AFF, HINT, 4, OUT>(c);
     default:
         if constexpr (M == kF32X) {
-            // three bf16 planes of a 128-wide tile do not fit LDS twice over;
-            // the host sends r = 128 fp32 work to the fp32 matrix cores
+            // three bf16 planes of a 128-wide tile do not fit LDS twice over:
+            // scan_wide_kernel takes this width
             return hipErrorInvalidValue;
         } else {
             // With a hint whose r_K <= 64 only the first four column blocks

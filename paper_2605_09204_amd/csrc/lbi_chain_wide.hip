@@ -1,0 +1,546 @@
+// The chain scan for fp32 storage at r = 128 in the split arithmetic: four
+// matrix waves and four staging waves per chain segment, A_j in column panels.
+//
+// It computes what the workgroup chain kernel computes: the suffix composites
+// P_j = A_j P_{j+1}, c_j = A_j c_{j+1} + b_j of a segment (Proposition "Scan
+// Formulation of Backpropagation"), written out, or applied as they form,
+// lambda_j = P_j lambda_K + c_j (Algorithm "Bounded-Interface Backpropagation",
+// Phase 2).  The workgroup kernel has no split form at this width, because two
+// tiles of three bf16 planes (192 KB) do not fit LDS; its fp32 matrix cores
+// need 6.8 us for a slot's product, the six bf16 products 2.6.
+//
+//   * Panels.  A_j goes through LDS 32 columns at a time (the k range of one
+//     MFMA): 128 x 32 values as three bf16 planes, 24 KB, two buffers, one
+//     barrier per panel, four panels per slot.  A row's 32 values sit in
+//     operand order in four 16-byte chunks, swizzled over 16 slots of a
+//     256-byte line of four rows, so that operand reads and staging writes
+//     touch all banks.
+//   * Matrix waves (w < 4) hold column blocks w and w + 4 of P in the
+//     accumulator layout, which is the B operand layout of the next product,
+//     as in the workgroup kernel.  Per panel and wave: 24 operand reads, 96
+//     MFMAs, and the split of the next panel's 16 P values per lane between
+//     them; the apply of slot j+1 runs beside the second panel's products.
+//     Eight waves of one column block each would read A twice as often, as
+//     many LDS cycles as the MFMAs take; that is why only four form products.
+//   * Staging waves, one beside each matrix wave on its SIMD, load A a slot
+//     ahead (two slots with a widths hint; 16-byte buffer loads), split it, form c_j from the same registers
+//     and store lambda.  Neither role's registers are live in the other's loop.
+//
+// What bounds it: a slot is 384 MFMAs of 16 cycles per SIMD (2.6 us at the top
+// clock), with about 500 VALU instructions of the matrix wave beside them; with
+// every CU busy the MFMAs run at 1.0-1.2 PFLOP/s of bf16 products, where a
+// large library matrix product reaches 1.4 on the same card.  192 chains of 24
+// slots: 142 us against 233 with the workgroup kernel on the fp32 matrix cores;
+// 256 x 128: 835 against 1170; widths cycling 32/64/128, 1024 x 64: 713 against
+// 808 (compact storage 709 against 791).
+//
+// All HIP code here is built with packed fp32 math disabled.
+
+#include <type_traits>
+
+#include "lbi_device.hpp"
+#include "lbi_internal.h"
+
+namespace lbi {
+namespace {
+
+constexpr int kR = 128;
+constexpr int kNP = 4;                       // panels per tile
+constexpr int kPC = kR / kNP;                // panel columns
+constexpr int kPlane = kR * kPC;             // elements of one plane of a panel
+constexpr int kTileBytes = kR * kR * 4;
+
+// Element offset of 16-byte chunk q (0..3) of panel row r.
+__device__ __forceinline__ int panel_pos(int r, int q)
+{
+    const int line = r >> 2;
+    return line * 128 + ((r & 3) * 4 + (q ^ (line & 3))) * 8;
+}
+
+// The three parts of a lane's B operand: 4 rows of two row blocks of P.
+struct Parts {
+    bf16x8 h, m, l;
+};
+__device__ __forceinline__ Parts split_rows(const f4 &a, const f4 &b)
+{
+    const Split2 s0 = split_pair_keep(a[0], a[1]), s1 = split_pair_keep(a[2], a[3]);
+    const Split2 s2 = split_pair_keep(b[0], b[1]), s3 = split_pair_keep(b[2], b[3]);
+    return {__builtin_bit_cast(bf16x8, u4{s0.h, s1.h, s2.h, s3.h}),
+            __builtin_bit_cast(bf16x8, u4{s0.m, s1.m, s2.m, s3.m}),
+            __builtin_bit_cast(bf16x8, u4{s0.l, s1.l, s2.l, s3.l})};
+}
+
+// acc += A panel x b for the first NR row blocks and NT column blocks of a wave;
+// pan: this lane's operand of row block 0 (row block I adds 512 I elements).
+// Row blocks go in groups that give four independent accumulators.
+template <int NR, int NT>
+__device__ __forceinline__ void panel_product(f4 (&acc)[8][2], const __bf16 *pan,
+                                              const Parts (&b)[2])
+{
+    constexpr int GI = NT == 1 && NR >= 4 ? 4 : 2;
+#pragma unroll
+    for (int I0 = 0; I0 < NR; I0 += GI) {
+        bf16x8 ah[GI], am[GI], al[GI];
+#pragma unroll
+        for (int i = 0; i < GI; ++i) {
+            ah[i] = *(const bf16x8 *)(pan + 512 * (I0 + i));
+            am[i] = *(const bf16x8 *)(pan + kPlane + 512 * (I0 + i));
+            al[i] = *(const bf16x8 *)(pan + 2 * kPlane + 512 * (I0 + i));
+        }
+#define LBI_WIDE_TERM(X, Y)                                                                   \
+    _Pragma("unroll") for (int i = 0; i < GI; ++i)                                            \
+        _Pragma("unroll") for (int t = 0; t < NT; ++t) acc[I0 + i][t] =                       \
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(X[i], b[t].Y, acc[I0 + i][t], 0, 0, 0);
+        LBI_WIDE_TERM(ah, h)
+        LBI_WIDE_TERM(ah, m)
+        LBI_WIDE_TERM(am, h)
+        LBI_WIDE_TERM(ah, l)
+        LBI_WIDE_TERM(al, h)
+        LBI_WIDE_TERM(am, m)
+#undef LBI_WIDE_TERM
+    }
+}
+
+template <bool AFF, int HINT, int OUT>
+__global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 sA[2][3 * kPlane];
+    // c_s in entry s & 3; the apply's partial sums of slot s per matrix wave, in
+    // entry s & 1
+    __shared__ __attribute__((aligned(16))) float sC[4][kR];
+    __shared__ __attribute__((aligned(16))) float sPart[OUT == kOutLambda ? 2 : 1][4][kR];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, li = lane & 15;
+    // this workgroup's segment: slots s0 .. s0 + K - 1 of chain beta; below,
+    // slot indices are local to the segment
+    const int64_t beta = blockIdx.x / args.S;
+    const int64_t s0 = (int64_t)(blockIdx.x % args.S) * args.L;
+    const int64_t K = args.K - s0 < args.L ? args.K - s0 : args.L;
+    const int64_t first = beta * args.K + s0;
+    // (compact storage, whole chains: slot s's tile, b_s and lambda_s follow
+    // those of slot s - 1 at their true sizes)
+    constexpr bool compact = HINT == kHintCompact;
+    const float *A = (const float *)args.A +
+                     (compact ? beta * (int64_t)args.totalA : first * (int64_t)(kR * kR));
+    const float *bv = AFF ? (const float *)args.b +
+                                (compact ? beta * (int64_t)args.totalR : first * (int64_t)kR)
+                          : nullptr;
+    // composites at [B][K], or only the segment aggregates at [B][S]
+    const int64_t cslot = args.agg_only ? (int64_t)blockIdx.x : first;
+    // With a widths hint: 16-row blocks of slot s that can be nonzero (s = K:
+    // the segment's end; 0 before the segment).  What the kernel leaves out
+    // would add exact zeros.  A lookup is a scalar load, whose wait also drains
+    // the LDS queue: the loops carry the codes they need and fetch one per slot,
+    // a slot early.
+    auto blocks = [&](int64_t s) {
+        return !HINT ? 8 : s < 0 ? 0 : (int)((args.wcode[(s0 + s) >> 3] >> (((s0 + s) & 7) * 4)) & 15u);
+    };
+    // (writing composites, every row block is formed: the shapes of the product
+    // do not fit the registers beside the stores)
+    constexpr bool kShapes = HINT && OUT == kOutLambda;
+    // panels of a tile with wc column blocks; its row pitch in storage
+    auto panels = [](int wc) { return HINT ? (wc + 1) >> 1 : kNP; };
+    auto pitch = [](int wc) { return compact ? 16 * wc : kR; };
+
+    if (w < 4) {
+        // ---- matrix waves ---------------------------------------------------
+        float lk[2] = {0.0f, 0.0f};
+        if constexpr (OUT == kOutLambda) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int idx = 16 * (w + 4 * t) + li;
+                const int rK = compact ? 16 * blocks(K) : kR;
+                lk[t] = idx >= rK     ? 0.0f
+                        : args.lamSeg ? args.lamSeg[(int64_t)blockIdx.x * kR + idx]
+                                      : ((const float *)args.lamK)[beta * rK + idx];
+            }
+        }
+        float *Pout = OUT == kOutComposite ? args.Pout + cslot * (int64_t)(kR * kR) : nullptr;
+        // P_s, row blocks i0 .. i1 - 1, to global memory
+        auto store_rows = [&](const f4(&P)[8][2], int64_t s, int i0, int i1) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(Pout + s * (int64_t)(kR * kR)), 0, kTileBytes, kBufferWord3);
+#pragma unroll
+            for (int I = i0; I < i1; ++I)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        __builtin_amdgcn_raw_buffer_store_b32(
+                            fbits(P[I][t][v]), rs,
+                            ((16 * I + 4 * g + v) * kR + 16 * (w + 4 * t) + li) * 4, 0, 0);
+        };
+        // P_s lambda over this wave's columns, rows 64 h .. 64 h + 63
+        auto apply = [&](const f4(&P)[8][2], int64_t s, int h) {
+            float q[16];
+#pragma unroll
+            for (int I = 0; I < 4; ++I)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    q[4 * I + v] = P[4 * h + I][0][v] * lk[0] + P[4 * h + I][1][v] * lk[1];
+            group_reduce<16, 16>(q, li);
+            // lane li holds value li (= 4 I + v)
+            sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0];
+        };
+        f4 P[8][2];
+        {
+            const int nrow = 16 * blocks(K - 1), ld = pitch(blocks(K));
+            const float *T = A + (compact ? (int64_t)args.totalA - nrow * ld
+                                          : (K - 1) * (int64_t)(kR * kR));
+#pragma unroll
+            for (int I = 0; I < 8; ++I)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = 16 * I + 4 * g + v, col = 16 * (w + 4 * t) + li;
+                        P[I][t][v] = row < nrow && col < ld ? T[row * ld + col] : 0.0f;
+                    }
+        }
+        const int apos = panel_pos(li, g);  // row block I adds 512 I elements
+        Parts b[2] = {split_rows(P[0][0], P[1][0]), split_rows(P[0][1], P[1][1])};
+        // (columns past the segment end's width are zero)
+        const int nt = HINT && 4 + w >= blocks(K) ? 1 : 2;
+        int buf = 0;  // the panel's LDS buffer
+        __syncthreads();
+        // P_j (Pn) from P_{j+1} (P); b holds the split of P's first two row
+        // blocks on entry, of Pn's on return
+        int wr = blocks(K - 1), wnext = blocks(K - 2);
+        auto slot = [&](const f4(&P)[8][2], f4(&Pn)[8][2], int64_t j) {
+            [[maybe_unused]] const int np = panels(wr), nr = wnext;
+            wr = wnext;
+            wnext = blocks(j - 1);
+#pragma unroll
+            for (int I = 0; I < 8; ++I)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    Pn[I][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int p = 0; p < kNP; ++p) {
+                if (HINT && p >= np)
+                    break;
+                __syncthreads();
+                const __bf16 *pan = sA[HINT ? buf : p & 1] + apos;
+                buf ^= 1;
+                Parts bn[2] = {b[0], b[1]};
+                if constexpr (kShapes) {
+                    // (blocks past nr hold zeros)
+                    auto rows_for = [&](auto ntag) {
+                        constexpr int NT = decltype(ntag)::value;
+                        if (nr <= 2)
+                            panel_product<2, NT>(Pn, pan, b);
+                        else if (nr <= 4)
+                            panel_product<4, NT>(Pn, pan, b);
+                        else
+                            panel_product<8, NT>(Pn, pan, b);
+                    };
+                    if (nt == 1)
+                        rows_for(std::integral_constant<int, 1>{});
+                    else
+                        rows_for(std::integral_constant<int, 2>{});
+                } else {
+                    panel_product<8, 2>(Pn, pan, b);
+                }
+                if (p < kNP - 1) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        bn[t] = split_rows(P[2 * p + 2][t], P[2 * p + 3][t]);
+                }
+                if constexpr (OUT == kOutLambda) {
+                    // (a hinted slot may have one panel only)
+                    if (HINT ? p == 0 : p == 1)
+                        apply(P, j + 1, 0);
+                    if (HINT ? p == 0 : p == 2)
+                        apply(P, j + 1, 1);
+                } else if (!args.agg_only) {
+                    if (!HINT)
+                        store_rows(P, j + 1, 2 * p, 2 * p + 2);
+                    else if (p == 0)
+                        store_rows(P, j + 1, 0, 8);
+                }
+                b[0] = bn[0];
+                b[1] = bn[1];
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                b[t] = split_rows(Pn[0][t], Pn[1][t]);
+        };
+        auto last = [&](const f4(&X)[8][2]) {
+            __syncthreads();
+            if constexpr (OUT == kOutLambda) {
+                apply(X, 0, 0);
+                apply(X, 0, 1);
+            } else {
+                store_rows(X, 0, 0, 8);
+            }
+        };
+        // (the barrier: lambda_2's sums, in slot 0's entry, may still be read in
+        // the last phase)
+        f4 Q[8][2];
+        int64_t j = K - 2;
+        if constexpr (HINT) {
+            for (; j >= 0; --j) {
+                slot(P, Q, j);
+#pragma unroll
+                for (int I = 0; I < 8; ++I)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        P[I][t] = Q[I][t];
+            }
+            last(P);
+        } else {
+            // (two slots per iteration, so that P and Q swap without copies)
+            for (; j >= 1; j -= 2) {
+                slot(P, Q, j);
+                slot(Q, P, j - 1);
+            }
+            if (j == 0) {
+                slot(P, Q, 0);
+                last(Q);
+            } else {
+                last(P);
+            }
+        }
+        __syncthreads();
+        if (args.progress)
+            __syncthreads();
+    } else {
+        // ---- staging waves --------------------------------------------------
+        // chunk i of this thread: row i * 32 + srow, columns 4 sgi .. + 3 of the
+        // panel; after the row reduce, lanes 2 i, 2 i + 1 of the eight lanes of
+        // a row hold the sum of row i * 32 + srow (the even one owns it)
+        const int st = tid - 256, sgi = st & 7, srow = st >> 3;
+        const int orow = (sgi >> 1) * 32 + srow;
+        const bool oown = (sgi & 1) == 0;
+        const int wpos = panel_pos(srow, sgi & 3) + ((sgi >> 2) << 2);  // chunk i adds 1024 i
+        // slots loaded ahead: a hinted slot may have one panel and no time in it
+        // for the loads of the next one's four
+        constexpr int NPF = HINT ? 2 : 1;
+        u4 pf[NPF][kNP][4];
+        uint32_t pfb = 0;
+        // compact storage: offsets of the slot being loaded (A, b) and stored
+        // (lambda), each walked down from the chain's end
+        int32_t curA = args.totalA, curB = args.totalR, curL = args.totalR;
+        // panel q of slot s, of wr row and wc column blocks (rows past the slot's,
+        // and slots before the segment, lie outside the resource and read as
+        // zero)
+        auto load = [&](u4(&dst)[kNP][4], int q, int64_t s, int wr, int wc) {
+            const int ld = pitch(wc);
+            const int nrow = s >= 0 && q < panels(wc) ? 16 * wr : 0;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(A + (compact ? (int64_t)__builtin_amdgcn_readfirstlane(curA)
+                              : (s >= 0 ? s : 0) * (int64_t)(kR * kR))),
+                0, __builtin_amdgcn_readfirstlane(nrow * ld * 4), kBufferWord3);
+            int off = srow * (ld * 4) + sgi * 16;
+            if (compact)
+                off |= q * kPC + 4 * sgi < ld ? 0 : kOutOfRange;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                dst[q][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + i * 32 * (ld * 4),
+                                                                  q * kPC * 4, 0);
+        };
+        auto load_b = [&](int64_t s, int wr) {
+            if constexpr (AFF) {
+                const int nrow = s < 0 ? 0 : compact ? 16 * wr : kR;
+                if (compact)
+                    curB -= nrow;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)(bv + (compact ? (int64_t)__builtin_amdgcn_readfirstlane(curB)
+                                   : (s >= 0 ? s : 0) * (int64_t)kR)),
+                    0, __builtin_amdgcn_readfirstlane(nrow * 4), kBufferWord3);
+                pfb = __builtin_amdgcn_raw_buffer_load_b32(rs, orow * 4, 0, 0);
+            }
+        };
+        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        // panel q of slot s from registers into LDS, and its share of c_s
+        int buf = 0;
+        // (wq[d]: blocks of slot s + 1 - d, d = 0 .. NPF + 1)
+        auto stage = [&](u4(&src)[kNP][4], int q, int64_t s, const int *wq) {
+            f4 cv = {};
+            if constexpr (AFF)
+                cv = *(const f4 *)&sC[(s + 1) & 3][q * kPC + 4 * sgi];
+            // (the products read no row blocks past these)
+            const int nst = kShapes && s >= 0 ? (wq[1] <= 2 ? 1 : wq[1] <= 4 ? 2 : 4) : 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (kShapes && i >= nst) {
+                    part[i] = 0.0f;
+                    continue;
+                }
+                const float x0 = bitsf(src[q][i][0]), x1 = bitsf(src[q][i][1]);
+                const float x2 = bitsf(src[q][i][2]), x3 = bitsf(src[q][i][3]);
+                if constexpr (AFF) {
+                    const float d = x0 * cv[0] + x1 * cv[1] + x2 * cv[2] + x3 * cv[3];
+                    part[i] = q == 0 ? d : part[i] + d;
+                }
+                const Split2 s01 = split_pair(x0, x1), s23 = split_pair(x2, x3);
+                __bf16 *dst = sA[HINT ? buf : q & 1] + wpos + 1024 * i;
+                *(u2 *)dst = u2{s01.h, s23.h};
+                *(u2 *)(dst + kPlane) = u2{s01.m, s23.m};
+                *(u2 *)(dst + 2 * kPlane) = u2{s01.l, s23.l};
+            }
+            buf ^= 1;
+            // the registers take panel q of slot s - NPF, and after the last panel
+            // of slot s those that slot s did not use
+            const bool end = s >= 0 && q == panels(wq[0]) - 1;
+            if (compact && q == 0 && s >= NPF)
+                curA -= 16 * wq[NPF + 1] * pitch(wq[NPF]);
+            load(src, q, s - NPF, wq[NPF + 1], wq[NPF]);
+            if (HINT && end) {
+#pragma unroll
+                for (int u = 1; u < kNP; ++u)
+                    if (u > q)
+                        load(src, u, s - NPF, wq[NPF + 1], wq[NPF]);
+            }
+            if constexpr (AFF) {
+                if (end) {
+                    group_reduce<8, 4>(part, sgi);
+                    if (oown)
+                        sC[s & 3][orow] = part[0] + bitsf(pfb);
+                    load_b(s - 1, wq[2]);
+                }
+            }
+        };
+        // lambda_s (or, with composites, c_s), by the first two staging waves
+        int32_t pub_left = args.pchunk;
+        int64_t pub = -1;  // slots final once the next barrier is passed, or -1
+        int64_t npub = 0;  // publications so far
+        auto finish = [&](int64_t s, int wr) {
+            const int nrow = compact ? 16 * wr : kR;
+            if (compact)
+                curL -= nrow;
+            if (st < kR) {
+                const float c = AFF ? sC[s & 3][st] : 0.0f;
+                if constexpr (OUT == kOutLambda) {
+                    float *lam = args.lam + (compact ? beta * (int64_t)args.totalR + curL
+                                                     : (first + s) * (int64_t)kR);
+                    if (st < nrow)
+                        lam[st] = ((sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
+                                   (sPart[s & 1][2][st] + sPart[s & 1][3][st])) +
+                                  c;
+                } else if (args.cout && (!args.agg_only || s == 0)) {
+                    args.cout[(cslot + s) * kR + st] = c;
+                }
+            }
+            // streaming: at a publish point both storing waves make their
+            // stores visible device-wide; publish() follows the next barrier
+            if constexpr (OUT == kOutLambda) {
+                if (args.progress) {
+                    if (--pub_left == 0 || s == 0) {
+                        pub = K - s;
+                        if (st < kR)
+                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    }
+                    if (pub_left == 0)
+                        pub_left = args.pchunk;
+                }
+            }
+        };
+        // raises the chain's count (system scope: it lands in memory, past this
+        // XCD's L2) and records the clock
+        auto publish = [&]() {
+            if constexpr (OUT == kOutLambda) {
+                if (pub >= 0 && st == 0) {
+                    __hip_atomic_fetch_max(&args.progress[beta], (uint32_t)pub, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_SYSTEM);
+                    if (args.pub_clock)
+                        args.pub_clock[beta * args.npub + npub] = __builtin_amdgcn_s_memrealtime();
+                }
+                npub += pub >= 0 ? 1 : 0;
+                pub = -1;
+            }
+        };
+        if (compact)
+            curA -= 16 * blocks(K - 1) * pitch(blocks(K));
+#pragma unroll
+        for (int u = 0; u < NPF; ++u) {
+            if (compact && K - 2 - u >= 0)
+                curA -= 16 * blocks(K - 2 - u) * pitch(blocks(K - 1 - u));
+#pragma unroll
+            for (int q = 0; q < kNP; ++q)
+                load(pf[u], q, K - 2 - u, blocks(K - 2 - u), blocks(K - 1 - u));
+        }
+        if (AFF && st < kR) {
+            const int nrow = compact ? 16 * blocks(K - 1) : kR;
+            const float *bl = bv + (compact ? (int64_t)args.totalR - nrow : (K - 1) * (int64_t)kR);
+            sC[(K - 1) & 3][st] = st < nrow ? bl[st] : 0.0f;
+        }
+        if (compact)
+            curB -= 16 * blocks(K - 1);
+        load_b(K - 2, blocks(K - 2));
+        __syncthreads();
+        // wq[d]: blocks of slot j + 2 - d in the slot loop below
+        int wq[NPF + 4];
+#pragma unroll
+        for (int d = 0; d < NPF + 4; ++d)
+            wq[d] = blocks(K - d);
+        stage(pf[0], 0, K - 2, wq + 1);
+        // In the phase of panel p of slot j the next panel is staged: the rest of
+        // slot j from its registers, the first of slot j - 1 from the others.
+        // The slot's first phase also stores lambda_{j+2}: the apply of slot
+        // j + 2 ran in slot j + 1, before this phase's barrier.
+        auto slot = [&](u4(&cur)[kNP][4], u4(&next)[kNP][4], int64_t j) {
+            const int np = panels(wq[1]);
+            const int wnext = blocks(j - 2 - NPF);
+#pragma unroll
+            for (int p = 0; p < kNP; ++p) {
+                if (HINT && p >= np)
+                    break;
+                __syncthreads();
+                publish();
+                if (p + 1 < kNP && p + 1 < np)
+                    stage(cur, p + 1 < kNP ? p + 1 : 0, j, wq + 1);
+                else
+                    stage(next, 0, j - 1, wq + 2);
+                if (p == 0 && j + 2 < K)
+                    finish(j + 2, wq[0]);
+            }
+#pragma unroll
+            for (int d = 0; d < NPF + 3; ++d)
+                wq[d] = wq[d + 1];
+            wq[NPF + 3] = wnext;
+        };
+        for (int64_t j = K - 2; j >= 0; j -= NPF) {
+            slot(pf[0], pf[NPF - 1], j);
+            if (NPF == 2 && j >= 1)
+                slot(pf[NPF - 1], pf[0], j - 1);
+        }
+        __syncthreads();
+        publish();
+        if (K >= 2)
+            finish(1, blocks(1));
+        __syncthreads();
+        publish();
+        finish(0, blocks(0));
+        if (args.progress) {
+            __syncthreads();
+            publish();
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t launch_chain_wide_f32x(const ChainLaunch &c)
+{
+    void *params[] = {(void *)&c.args};
+    auto pick = [&](auto aff, auto hint) -> const void * {
+        constexpr bool AFF = decltype(aff)::value;
+        constexpr int HINT = decltype(hint)::value;
+        if constexpr (HINT != kHintCompact)
+            if (c.out == kOutComposite)
+                return (const void *)&scan_wide_kernel<AFF, HINT, kOutComposite>;
+        return (const void *)&scan_wide_kernel<AFF, HINT, kOutLambda>;
+    };
+    auto form = [&](auto hint) {
+        return c.aff ? pick(std::true_type{}, hint) : pick(std::false_type{}, hint);
+    };
+    const void *f = !c.hint ? form(std::integral_constant<int, kHintNone>{})
+                    : c.args.compact ? form(std::integral_constant<int, kHintCompact>{})
+                                     : form(std::integral_constant<int, kHintWidths>{});
+    return hipLaunchKernel(f, dim3((unsigned)(c.B * c.args.S)), dim3(512), params, 0, c.stream);
+}
+
+}  // namespace lbi

@@ -101,6 +101,10 @@ int ring_lds_bytes(int ring, bool aff);
 bool chain_ksplit_supported(const ChainLaunch &c);
 hipError_t launch_chain_ksplit_f32x(const ChainLaunch &c);
 
+// The chain kernel's work for fp32 storage at r = 128 in the split arithmetic:
+// every form of a launch that the chain kernel takes.
+hipError_t launch_chain_wide_f32x(const ChainLaunch &c);
+
 // The log-depth (tree) scan: one launch over chunks of tree_chunk(r) slots
 // of a chain level of K slots (S = ceil(K / chunk) chunks per chain, B * S
 // workgroups).  AGG: each chunk's aggregate (P [B][S][r][r], c [B][S][r]);

@@ -14,9 +14,14 @@
 // Both are matrix-vector work on fp32 composites: TPR lanes per row, each
 // lane CPR consecutive columns (16-byte loads, coalesced across the row's
 // lanes), the row sum reduced by DPP within the lane group.  The carry gives
-// each chain one 256-thread workgroup and walks its S aggregates serially,
-// with the loads of the next two issued ahead; the apply pass gives each
-// workgroup one or more whole slots, 16 KB of composites or more.
+// each chain one workgroup of 16 matrix values per thread (one wave, and no
+// cross-wave wait, at R <= 32) and walks its S aggregates serially with eight
+// of them in flight (four at R = 128): the chain of steps is what bounds it,
+// and with two in flight each step waited for memory.  500 slots, carry of 32
+// aggregates: whole call 46.7 -> 44.0 us at r = 64 (4 chains), 20.6 -> 17.6 at
+// r = 16, 32.1 -> 30.0 at r = 32 bf16 (16 chains), 132 -> 102 at r = 128 bf16
+// (1 chain).  The apply pass gives each workgroup one or more whole slots, 16
+// KB of composites or more.
 
 #include "lbi_device.hpp"
 #include "lbi_internal.h"
@@ -26,10 +31,14 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// The carry of one chain: 16 columns per lane (4 at R = 16), AHEAD aggregates
+// in flight.
 template <int R> struct MatVec {
-    static constexpr int TPR = kThreads / R;  // lanes per row
-    static constexpr int CPR = R / TPR;       // columns per lane
-    static_assert(TPR >= 2 && TPR <= 16 && (CPR % 4 == 0 || CPR == 1), "matvec geometry");
+    static constexpr int T = R <= 32 ? 64 : R * R / 16;  // threads
+    static constexpr int TPR = T / R;                    // lanes per row
+    static constexpr int CPR = R / TPR;                  // columns per lane
+    static constexpr int AHEAD = R == 128 ? 4 : 8;
+    static_assert(TPR >= 2 && TPR <= 16 && CPR % 4 == 0, "matvec geometry");
 };
 
 // Sum over this lane's CPR columns of p[e] x[col0 + e], then over the row's
@@ -38,14 +47,10 @@ template <int CPR, int TPR>
 __device__ __forceinline__ float row_dot(const float (&p)[CPR], const float *x, int col0)
 {
     float acc = 0.0f;
-    if constexpr (CPR >= 4) {
 #pragma unroll
-        for (int e = 0; e < CPR; e += 4) {
-            const f4 xv = *(const f4 *)&x[col0 + e];
-            acc += p[e] * xv[0] + p[e + 1] * xv[1] + p[e + 2] * xv[2] + p[e + 3] * xv[3];
-        }
-    } else {
-        acc = p[0] * x[col0];
+    for (int e = 0; e < CPR; e += 4) {
+        const f4 xv = *(const f4 *)&x[col0 + e];
+        acc += p[e] * xv[0] + p[e + 1] * xv[1] + p[e + 2] * xv[2] + p[e + 3] * xv[3];
     }
     float q[1] = {acc};
     group_reduce<TPR, 1>(q, threadIdx.x % TPR);
@@ -56,26 +61,22 @@ __device__ __forceinline__ float row_dot(const float (&p)[CPR], const float *x, 
 template <int CPR>
 __device__ __forceinline__ void load_row(float (&p)[CPR], const float *Prow)
 {
-    if constexpr (CPR >= 4) {
 #pragma unroll
-        for (int e = 0; e < CPR; e += 4) {
-            const f4 v = *(const f4 *)&Prow[e];
-            p[e] = v[0];
-            p[e + 1] = v[1];
-            p[e + 2] = v[2];
-            p[e + 3] = v[3];
-        }
-    } else {
-        p[0] = Prow[0];
+    for (int e = 0; e < CPR; e += 4) {
+        const f4 v = *(const f4 *)&Prow[e];
+        p[e] = v[0];
+        p[e + 1] = v[1];
+        p[e + 2] = v[2];
+        p[e + 3] = v[3];
     }
 }
 
 template <int R, bool BF16>
-__global__ __launch_bounds__(kThreads) void carry_kernel(const float *Pa, const float *ca,
+__global__ __launch_bounds__(MatVec<R>::T) void carry_kernel(const float *Pa, const float *ca,
                                                         const void *lamK, float *carry, int32_t S,
                                                         int64_t cstride, int64_t dstride)
 {
-    constexpr int TPR = MatVec<R>::TPR, CPR = MatVec<R>::CPR;
+    constexpr int TPR = MatVec<R>::TPR, CPR = MatVec<R>::CPR, AHEAD = MatVec<R>::AHEAD;
     __shared__ __attribute__((aligned(16))) float sl[2][R];
     const int tid = threadIdx.x;
     const int64_t beta = blockIdx.x;
@@ -87,40 +88,36 @@ __global__ __launch_bounds__(kThreads) void carry_kernel(const float *Pa, const 
         sl[0][tid] = v;
         carry[(beta * S + S - 1) * R + tid] = v;
     }
-    // aggregates of segments d = S-1 .. 1, prefetched two steps ahead (the
-    // loads are independent of lambda; only the products wait for it)
-    auto fetch = [&](int32_t d, float(&p)[CPR], float &c) {
+    // aggregates of segments d = S-1 .. 1, AHEAD of them in flight (the loads
+    // are independent of lambda; only the products wait for it)
+    float p[AHEAD][CPR], c[AHEAD];
+    auto fetch = [&](int32_t d, int u) {
         if (d >= 1) {
             const int64_t agg = beta * cstride + d * dstride;  // aggregate of segment d
-            load_row<CPR>(p, Pa + (agg * R + row) * R + col0);
-            c = ca && owner ? ca[agg * R + row] : 0.0f;
+            load_row<CPR>(p[u], Pa + (agg * R + row) * R + col0);
+            c[u] = ca && owner ? ca[agg * R + row] : 0.0f;
         }
     };
-    int cur = 0;
-    auto step = [&](int32_t d, const float(&p)[CPR], float c) {
-        const float sum = row_dot<CPR, TPR>(p, sl[cur], col0);
-        if (owner) {
-            const float v = sum + c;
-            sl[cur ^ 1][row] = v;
-            carry[(beta * S + d - 1) * R + row] = v;
-        }
-        __syncthreads();
-        cur ^= 1;
-    };
-    float p0[CPR], p1[CPR], p2[CPR], c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-    fetch(S - 1, p0, c0);
-    fetch(S - 2, p1, c1);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+        fetch(S - 1 - u, u);
     __syncthreads();
-    for (int32_t d = S - 1; d >= 1; d -= 3) {
-        fetch(d - 2, p2, c2);
-        step(d, p0, c0);
-        if (d - 1 >= 1) {
-            fetch(d - 3, p0, c0);
-            step(d - 1, p1, c1);
-        }
-        if (d - 2 >= 1) {
-            fetch(d - 4, p1, c1);
-            step(d - 2, p2, c2);
+    int cur = 0;
+    for (int32_t d0 = S - 1; d0 >= 1; d0 -= AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int32_t d = d0 - u;
+            if (d < 1)
+                break;
+            const float sum = row_dot<CPR, TPR>(p[u], sl[cur], col0);
+            if (owner) {
+                const float v = sum + c[u];
+                sl[cur ^ 1][row] = v;
+                carry[(beta * S + d - 1) * R + row] = v;
+            }
+            fetch(d - AHEAD, u);
+            __syncthreads();
+            cur ^= 1;
         }
     }
 }
@@ -170,10 +167,10 @@ hipError_t carry_r(const float *Pa, const float *ca, const void *lamK, bool bf16
                    int64_t B, int32_t S, int64_t cstride, int64_t dstride, hipStream_t st)
 {
     if (bf16)
-        hipLaunchKernelGGL((carry_kernel<R, true>), dim3((unsigned)B), dim3(kThreads), 0, st, Pa,
+        hipLaunchKernelGGL((carry_kernel<R, true>), dim3((unsigned)B), dim3(MatVec<R>::T), 0, st, Pa,
                            ca, lamK, carry, S, cstride, dstride);
     else
-        hipLaunchKernelGGL((carry_kernel<R, false>), dim3((unsigned)B), dim3(kThreads), 0, st, Pa,
+        hipLaunchKernelGGL((carry_kernel<R, false>), dim3((unsigned)B), dim3(MatVec<R>::T), 0, st, Pa,
                            ca, lamK, carry, S, cstride, dstride);
     return hipGetLastError();
 }

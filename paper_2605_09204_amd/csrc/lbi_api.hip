@@ -571,20 +571,44 @@ constexpr int kRegionParts = 20;
 struct RegionPlan {
     size_t off[kRegionParts];
     size_t bytes;
+    int32_t nsplit;
 };
+
+// Parts that the token product's row tiles (128 tokens) are cut into.  One
+// workgroup per (sequence, region, 128 columns of X) may leave half of the 512
+// places (two per CU) idle in its last round; the parts that make the fewest
+// tile steps in a row, a half step counted for each workgroup's start and end.
+int32_t token_parts(int64_t B, int64_t K, int64_t L, int32_t X)
+{
+    const int64_t wg = B * K * (X / 128), tiles = (L + 127) / 128;
+    int32_t best = 1;
+    double least = 0.0;
+    for (int32_t n = 1; n <= 16 && n <= tiles; ++n) {
+        const double cost = (double)((wg * n + 511) / 512) * ((double)((tiles + n - 1) / n) + 0.5);
+        if (n == 1 || cost < 0.99 * least) {
+            best = n;
+            least = cost;
+        }
+    }
+    return best;
+}
 
 // Workspace parts, each 256-byte aligned: su, sa, d, cvec, xpart, xbar, sbar,
 // gbar, p, sue, se, encv, zhat, isig, JencT (fp32) and P1, JdT, UT, dpT, TT (bf16).
-RegionPlan region_plan(int64_t B, int64_t K, int64_t L, int32_t D, int32_t X, int32_t r)
+// (token_product: the block has one, whose parts sbar and gbar hold)
+RegionPlan region_plan(int64_t B, int64_t K, int64_t L, int32_t D, int32_t X, int32_t r,
+                       bool token_product)
 {
+    RegionPlan p;
+    p.nsplit = token_product ? token_parts(B, K, L, X) : 1;
     const size_t BK = (size_t)B * K, Br = (size_t)B * r, nch = (size_t)((L + 63) / 64);
     const size_t n[kRegionParts] = {
         BK * D * 4, BK * D * 4, BK * D * 4, BK * X * 4, (size_t)B * nch * D * 4,
-        (size_t)B * D * 4, BK * X * 4, BK * X * 4, BK * D * 4, BK * D * 4, BK * D * 4,
+        (size_t)B * D * 4, p.nsplit * BK * X * 4, p.nsplit * BK * X * 4, BK * D * 4, BK * D * 4,
+        BK * D * 4,
         BK * r * 4, BK * r * 4, BK * 4, (size_t)K * Br * r * 4,
         (size_t)K * Br * D * 2, (size_t)K * Br * D * 2, (size_t)K * Br * X * 2,
         (size_t)K * Br * D * 2, (size_t)K * Br * D * 2};
-    RegionPlan p;
     size_t o = 0;
     for (int i = 0; i < kRegionParts; ++i) {
         p.off[i] = o;
@@ -614,7 +638,7 @@ struct SsmPlan {
 SsmPlan ssm_plan(int64_t B, int64_t K, int64_t L, int32_t D, int32_t X, int32_t r)
 {
     SsmPlan p;
-    p.base = region_plan(B, K, L, D, X, r);
+    p.base = region_plan(B, K, L, D, X, r, false);
     const size_t LD = (size_t)L * D, LX = (size_t)L * X, Lr = (size_t)L * r;
     const size_t mtiles = (Lr + 255) / 256;  // the tangent products' row tiles
     const size_t pair = align256(LD * 2) + align256(LX * 2) + align256(Lr * X * 2) +
@@ -742,6 +766,7 @@ RegionArgs region_args(const lbi_region_params &p, const void *x_embed, const fl
     q.D = D;
     q.X = X;
     q.r = r;
+    q.nsplit = plan.nsplit;
     char *w = (char *)workspace;
     float **f32[15] = {&q.su,  &q.sa, &q.d,   &q.cvec, &q.xpart, &q.xbar, &q.sbar, &q.gbar,
                        &q.p,   &q.sue, &q.se, &q.encv, &q.zhat,  &q.isig, &q.JencT};
@@ -919,7 +944,7 @@ size_t lbi_region_jacobians_workspace_bytes(int64_t B, int64_t K, int64_t L, int
 {
     if (!region_sizes_ok(B, K, L, D, X, r))
         return 0;
-    return region_plan(B, K, L, D, X, r).bytes;
+    return region_plan(B, K, L, D, X, r, true).bytes;
 }
 
 
@@ -930,7 +955,7 @@ lbi_status lbi_region_jacobians(const lbi_region_params *params, const void *x_e
 {
     if (!region_sizes_ok(B, K, L, D, X, r))
         return r > 0 && !supported_r(r) ? LBI_ERR_UNSUPPORTED_R : LBI_ERR_SHAPE;
-    const RegionPlan plan = region_plan(B, K, L, D, X, r);
+    const RegionPlan plan = region_plan(B, K, L, D, X, r, true);
     const lbi_status st = region_check(params, nullptr, false, x_embed, m, A, m_next, B, K, L, D,
                                        r, workspace, workspace_bytes, plan.bytes);
     if (st != LBI_OK || B == 0)

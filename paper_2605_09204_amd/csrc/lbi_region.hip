@@ -32,16 +32,19 @@
 // same bf16 operand for every region, and d enters in fp32 through the column
 // vector W1 d, added in the epilogue.
 //
-// Kernels, in launch order:
-//   bmv x2      per region, all sequences: a -> silu(a), silu'(a); d = Dec_k(m)
-//   p1          per (b, k): P1 = (diag(silu'(a)) W_d1)^T
-//   bmv         cvec = W1 d
-//   xpart/xfin  per b: mean_l x_embed (two-stage)
-//   region_dma  per (k, b, 128 columns of X): the token product and its reductions
-//   bmv x3      p = mean x_embed + d + W2 sbar; e -> silu(e), silu'(e); Enc_k
-//   ln_fwd      per (b, k): z = m + alpha Enc, LayerNorm -> m_{k+1}, zhat, 1/sigma
-//   gemm_nt x5  per k: Jdec^T, U'^T = (W1 Jdec)^T scaled by gbar, dp^T, T'^T, Jenc^T
-//   ln_jac      per (b, k): J, stored transposed as A[b][k]
+// Launches (each line one; steps that do not need each other share a launch):
+//   bmv a -> silu(a), silu'(a) | xpart: 64-token partial means of x_embed
+//   bmv d = Dec_k(m) | p1: P1 = (diag(silu'(a)) W_d1)^T | xfin: mean_l x_embed
+//   gemm Jdec^T | bmv cvec = W1 d
+//   region_dma  per (k, 128 columns of X, part of the tokens, b): the token
+//               product and its reductions
+//   gemm U'^T = (W1 Jdec)^T scaled by gbar | bmv p = mean x_embed + d + W2 sbar
+//   gemm dp^T | bmv e -> silu(e), silu'(e)
+//   gemm T'^T | bmv Enc_k
+//   gemm Jenc^T | ln_fwd: z = m + alpha Enc, LayerNorm -> m_{k+1}, zhat, 1/sigma
+//   ln_jac: J, stored transposed as A[b][k]
+
+#include <type_traits>
 
 #include "lbi_device.hpp"
 #include "lbi_internal.h"
@@ -186,12 +189,13 @@ __device__ __forceinline__ void mma_bk(f4 (&acc)[4][4], const __bf16 *sA, const 
 // ---- bmv: y[b][k] = W[k] v[b][k] (+ bias[k]) (+ add1[b][k]) (+ add2[b][k]) -----
 // for every sequence b of region k, fp32 sums of bf16 weights times fp32
 // vectors; outputs y, silu(y) and silu'(y) (each optional).  A wave takes 8
-// rows and 8 sequences: each weight row is read once per region and 8
-// sequences, each vector chunk serves 8 rows.
+// rows and NB sequences: each weight row is read once per region and NB
+// sequences.  The workgroup's vectors go through LDS, kBmvCols / NB columns of
+// each at a time, so that a step of a wave waits for its weights only.
 struct BmvArgs {
     const __bf16 *W;
     int64_t sW;  // region stride (elements); rows N of C columns
-    const float *v;
+    const float *v;  // the sum of nv vectors v_ss apart (nv 0: one)
     int64_t v_sb, v_sk;
     const float *bias;
     int64_t s_bias;
@@ -203,70 +207,90 @@ struct BmvArgs {
     int64_t y_sb, y_sk;
     int64_t B;
     int N, C;
+    int nv = 0;
+    int64_t v_ss = 0;
 };
 
-__global__ __launch_bounds__(kT) void bmv_kernel(BmvArgs a)
+// Workgroups of a bmv over K regions (rows fastest, then regions, then groups
+// of NB sequences).
+__host__ __device__ __forceinline__ int64_t bmv_blocks(int N, int64_t K, int64_t B, int NB)
 {
+    return (int64_t)((N + 31) / 32) * K * ((B + NB - 1) / NB);
+}
+
+constexpr int kBmvCols = 8192;  // 32 KB of LDS
+template <int NB>
+__device__ __forceinline__ void bmv_block(const BmvArgs &a, int64_t K, int64_t blk, char *smem)
+{
+    static_assert(NB == 2 || NB == 8, "sequences per wave");
+    const int nx = (a.N + 31) / 32;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t k = blockIdx.y, b0 = (int64_t)blockIdx.z * 8;
-    const int n0 = blockIdx.x * 32 + w * 8;
+    const int64_t k = (blk / nx) % K, b0 = blk / nx / K * NB;
+    const int n0 = (int)(blk % nx) * 32 + w * 8;
     const __bf16 *W = a.W + k * a.sW;
-    float acc[64];  // [row rr][sequence bb]
+    constexpr int LIVE = 8 * NB;
+    float acc[LIVE];  // [row rr][sequence bb]
 #pragma unroll
-    for (int i = 0; i < 64; ++i)
+    for (int i = 0; i < LIVE; ++i)
         acc[i] = 0.0f;
-    for (int c = lane * 8; c < a.C; c += 64 * 8) {
-        float v[8][8];
+    constexpr int CH = kBmvCols / NB;
+    float *sv = (float *)smem;  // [NB][CH]
+    for (int c0 = 0; c0 < a.C; c0 += CH) {
+        const int cn = a.C - c0 < CH ? a.C - c0 : CH;
+        if (c0 > 0)
+            __syncthreads();
 #pragma unroll
-        for (int bb = 0; bb < 8; ++bb) {
-            if (b0 + bb < a.B) {
-                const float *vp = a.v + (b0 + bb) * a.v_sb + k * a.v_sk + c;
-                const f4 x0 = *(const f4 *)vp, x1 = *(const f4 *)(vp + 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[bb][e] = x0[e];
-                    v[bb][4 + e] = x1[e];
+        for (int bb = 0; bb < NB; ++bb)
+            for (int c = 4 * threadIdx.x; c < cn; c += 4 * kT) {
+                f4 x = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (b0 + bb < a.B) {
+                    const float *vp = a.v + (b0 + bb) * a.v_sb + k * a.v_sk + c0 + c;
+                    x = *(const f4 *)vp;
+                    for (int u = 1; u < a.nv; ++u)
+                        x += *(const f4 *)(vp + u * a.v_ss);
                 }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[bb][e] = 0.0f;
+                *(f4 *)&sv[bb * CH + c] = x;
             }
-        }
+        __syncthreads();
+#pragma unroll 2
+        for (int c = lane * 8; c < cn; c += 64 * 8) {
+            bf16x8 wv[8];
 #pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-            if (n0 + rr < a.N) {
-                const bf16x8 wv = *(const bf16x8 *)(W + (int64_t)(n0 + rr) * a.C + c);
+            for (int rr = 0; rr < 8; ++rr)
+                wv[rr] = n0 + rr < a.N
+                             ? *(const bf16x8 *)(W + (int64_t)(n0 + rr) * a.C + c0 + c)
+                             : bf16x8{};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float wf = (float)wv[e];
+            for (int bb = 0; bb < NB; ++bb) {
+                const f4 x0 = *(const f4 *)&sv[bb * CH + c], x1 = *(const f4 *)&sv[bb * CH + c + 4];
 #pragma unroll
-                    for (int bb = 0; bb < 8; ++bb)
-                        acc[rr * 8 + bb] += wf * v[bb][e];
-                }
+                for (int rr = 0; rr < 8; ++rr)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc[rr * NB + bb] += (float)wv[rr][e] * (e < 4 ? x0[e & 3] : x1[e & 3]);
             }
         }
     }
-    // the 64 partial sums over the 64 lanes: lane l ends with index l
+    // the LIVE partial sums over the 64 lanes: the first lane of each 64 / LIVE
+    // ends with one of them
     {
         const bool upper = (lane >> 5) & 1;
+        float q[LIVE / 2];
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            const float keep = upper ? acc[i + 32] : acc[i];
-            const float send = upper ? acc[i] : acc[i + 32];
-            acc[i] = keep + __shfl_xor(send, 32);
+        for (int i = 0; i < LIVE / 2; ++i) {
+            const float keep = upper ? acc[i + LIVE / 2] : acc[i];
+            const float send = upper ? acc[i] : acc[i + LIVE / 2];
+            q[i] = keep + __shfl_xor(send, 32);
         }
-        float q[32];
-#pragma unroll
-        for (int i = 0; i < 32; ++i)
-            q[i] = acc[i];
-        group_reduce<32, 32>(q, lane & 31);
+        group_reduce<32, LIVE / 2>(q, lane & 31);
         acc[0] = q[0];
     }
-    const int rr = lane >> 3, bb = lane & 7;
+    constexpr int SH = 5 - ilog2(LIVE / 2);
+    const int idx = (lane >> 5) * (LIVE / 2) + ((lane & 31) >> SH);
+    const int rr = idx / NB, bb = idx % NB;
     const int n = n0 + rr;
     const int64_t b = b0 + bb;
-    if (n < a.N && b < a.B) {
+    if ((lane & ((1 << SH) - 1)) == 0 && n < a.N && b < a.B) {
         float y = acc[0];
         if (a.bias)
             y += a.bias[k * a.s_bias + n];
@@ -287,12 +311,12 @@ __global__ __launch_bounds__(kT) void bmv_kernel(BmvArgs a)
 // ---- p1: P1[k][b r + j][h] = W_d1[k][h][j] silu'(a)[b][k][h], the A operand of
 //      Jdec^T; 64 values of h per workgroup, transposed through LDS so that
 //      both the reads of W_d1 rows and the writes of P1 rows are contiguous
-__global__ __launch_bounds__(kT) void p1_kernel(RegionArgs q)
+__device__ __forceinline__ void p1_block(const RegionArgs &q, int64_t blk, char *smem)
 {
-    __shared__ float tile[64][129];  // [h - h0][j], r <= 128
-    const int64_t bk = blockIdx.x, b = bk / q.K, k = bk % q.K;
+    float(*tile)[129] = (float(*)[129])smem;  // [h - h0][j], r <= 128
+    const int64_t bk = blk % (q.B * q.K), b = bk / q.K, k = bk % q.K;
     const int D = q.D, r = q.r;
-    const int h0 = blockIdx.y * 64;
+    const int h0 = (int)(blk / (q.B * q.K)) * 64;
     const __bf16 *Wd1 = (const __bf16 *)q.W_d1 + k * (int64_t)D * r;
     const float *sa = q.sa + bk * D;
     for (int idx = threadIdx.x; idx < 64 * r; idx += kT) {
@@ -308,10 +332,10 @@ __global__ __launch_bounds__(kT) void p1_kernel(RegionArgs q)
 }
 
 // ---- xpart / xfin: mean over the tokens of x_embed, 64-token partial sums first
-__global__ __launch_bounds__(kT) void xpart_kernel(RegionArgs q)
+__device__ __forceinline__ void xpart_block(const RegionArgs &q, int64_t blk)
 {
     // thread t sums the 8 columns 8t .. 8t + 7 over the workgroup's 64 tokens
-    const int64_t b = blockIdx.y, ch = blockIdx.x;
+    const int64_t nch = (q.L + 63) / 64, b = blk / nch, ch = blk % nch;
     const int64_t l0 = ch * 64, l1 = l0 + 64 < q.L ? l0 + 64 : q.L;
     const int c = threadIdx.x * 8;
     if (c >= q.D)
@@ -326,17 +350,16 @@ __global__ __launch_bounds__(kT) void xpart_kernel(RegionArgs q)
         for (int e = 0; e < 8; ++e)
             s[e] += (float)v[e];
     }
-    const int64_t nch = (q.L + 63) / 64;
     float *o = q.xpart + (b * nch + ch) * q.D + c;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
         o[e] = s[e];
 }
 
-__global__ __launch_bounds__(kT) void xfin_kernel(RegionArgs q)
+__device__ __forceinline__ void xfin_block(const RegionArgs &q, int64_t blk)
 {
-    const int64_t b = blockIdx.y;
-    const int c = blockIdx.x * kT + threadIdx.x;
+    const int64_t b = blk % q.B;
+    const int c = (int)(blk / q.B) * kT + threadIdx.x;
     if (c >= q.D)
         return;
     const int64_t nch = (q.L + 63) / 64;
@@ -370,9 +393,14 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     int64_t lg = blockIdx.x;
     if (G % 8 == 0)
         lg = (lg % 8) * (G / 8) + lg / 8;
+    // (this workgroup's row tiles: t0 .. t0 + ntile - 1, part sp of q.nsplit)
     const int64_t b = lg % q.B;
-    const int64_t xt = (lg / q.B) % nxt;
-    const int64_t k = lg / (q.B * nxt);
+    const int sp = (int)((lg / q.B) % q.nsplit);
+    const int64_t xt = (lg / (q.B * q.nsplit)) % nxt;
+    const int64_t k = lg / (q.B * q.nsplit * nxt);
+    const int ntl = (int)((q.L + BM - 1) / BM), per = (ntl + q.nsplit - 1) / q.nsplit;
+    const int t0 = sp * per;
+    const int ntile = t0 + per < ntl ? per : (ntl > t0 ? ntl - t0 : 0);
     const int D = q.D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
@@ -385,7 +413,6 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     for (int j = 0; j < 4; ++j)
         cv[j] = q.cvec[bk * q.X + xt * BN + wn * 64 + j * 16 + (lane & 15)];
     const int nk = D / BK;
-    const int ntile = (int)((q.L + BM - 1) / BM);
     const int nstep = ntile * nk;
     // load d of a wave: rows 8 d' .. 8 d' + 7 (d' = w + 4 d) of a tile, lane ->
     // line rp = 4 d' + lane / 16, row 2 rp + (lane & 15) / 8, chunk (lane & 7) ^ (rp & 7)
@@ -397,7 +424,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
     auto issue = [&](int s) {
         const int t = s / nk, kb = s - t * nk;
-        const int64_t row0 = (int64_t)t * BM;
+        const int64_t row0 = (int64_t)(t0 + t) * BM;
         const int vA = q.L - row0 < BM ? (int)(q.L - row0) : BM;
         const i4 rsA = dma_rsrc(Xe + row0 * D, (uint32_t)vA * D * 2);
         const uint32_t st = lbase + (uint32_t)((s & 1) * STG);
@@ -421,7 +448,8 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    issue(0);
+    if (nstep > 0)
+        issue(0);
     for (int s = 0; s < nstep; ++s) {
         dma_barrier<0>();  // stage s complete; stage s - 1 read by every wave
         if (s + 1 < nstep)
@@ -453,7 +481,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             // may hold anything); with s = sigmoid(h), silu = h s and
             // silu' = s + silu - silu s, the sums of s, silu and silu s carry
             // both reductions
-            const int64_t rbase = (int64_t)t * BM + wm * 64 + 4 * (lane >> 4);
+            const int64_t rbase = (int64_t)(t0 + t) * BM + wm * 64 + 4 * (lane >> 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -498,17 +526,17 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __syncthreads();
     if (tid < BN) {
         const float inv = 1.0f / (float)q.L;
-        const int64_t o = bk * q.X + xt * BN + tid;
+        const int64_t o = (sp * q.B * q.K + bk) * q.X + xt * BN + tid;
         q.sbar[o] = (sred[0][0][tid] + sred[0][1][tid]) * inv;
         q.gbar[o] = (sred[1][0][tid] + sred[1][1][tid]) * inv;
     }
 }
 
 // ---- ln_fwd: z = m + alpha Enc, LayerNorm -> m_{k+1}, zhat, 1/sigma ------------
-__global__ __launch_bounds__(64) void ln_fwd_kernel(RegionArgs q)
+__device__ __forceinline__ void ln_fwd_wave(const RegionArgs &q, int64_t bk)
 {
-    const int r = q.r, lane = threadIdx.x;
-    const int64_t bk = blockIdx.x, k = bk % q.K;
+    const int r = q.r, lane = threadIdx.x & 63;
+    const int64_t k = bk % q.K;
     const float alpha = q.alpha[k];
     float z[2];
     float s = 0.0f;
@@ -550,7 +578,7 @@ struct GemmOp {
     int64_t ldc, sC;
     int64_t M, N;
     int K;
-    const float *scale;  // NULL: 1
+    const float *scale;  // NULL: 1; the sum of nscale arrays scale_ss apart (0: one)
     int64_t s_scale_b, s_scale_g;
     int grp_shift;  // rows per scale row: 2^grp_shift (1, or the interface width)
     const __bf16 *add;  // NULL: 0 (ld ldc, batch stride sC)
@@ -561,14 +589,90 @@ struct GemmOp {
     // act: C = silu(v) (bf16) and C2 = silu'(v) (fp32, same index) in place of v
     bool act = false;
     float *C2 = nullptr;
+    int nscale = 0;
+    int64_t scale_ss = 0;
 };
 
-__global__ __launch_bounds__(kT) void gemm_nt_kernel(GemmOp g)
+// The epilogue of a wave's NI x NJ blocks from (row0, col0).  Every load comes
+// before the first store (which the compiler could not move them across), so
+// that they take one latency.  A 16-row block has one scale row: grp_shift >= 4.
+template <int NI, int NJ>
+__device__ __forceinline__ void gemm_out(const GemmOp &g, int64_t z, int64_t row0, int64_t col0,
+                                         f4 (&acc)[NI][NJ])
 {
-    __shared__ __attribute__((aligned(16))) __bf16 sA[2][TILE];
-    __shared__ __attribute__((aligned(16))) __bf16 sB[2][TILE];
-    const int64_t z = blockIdx.z;
-    const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
+    const int lane = threadIdx.x & 63, q = lane >> 4, li = lane & 15;
+    if (g.scale) {
+        float f[NI][NJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                f[i][j] = 0.0f;
+        int u = 0;
+        do {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const int64_t row = row0 + 16 * i, col = col0 + 16 * j + li;
+                    if (row < g.M && col < g.N)
+                        f[i][j] += g.scale[z * g.s_scale_b + (row >> g.grp_shift) * g.s_scale_g +
+                                           col + u * g.scale_ss];
+                }
+        } while (++u < g.nscale);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    acc[i][j][v] *= f[i][j];
+    }
+    if (g.add) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t row = row0 + 16 * i + 4 * q + v, col = col0 + 16 * j + li;
+                    if (row < g.M && col < g.N)
+                        acc[i][j][v] += (float)g.add[z * g.sC + row * g.ldc + col];
+                }
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t row = row0 + 16 * i + 4 * q + v;
+            if (row >= g.M)
+                continue;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int64_t col = col0 + 16 * j + li;
+                if (col >= g.N)
+                    continue;
+                const int64_t o = z * g.sC + row * g.ldc + col;
+                const float val = acc[i][j][v];
+                if (g.act) {
+                    ((__bf16 *)g.C)[o] = (__bf16)silu(val);
+                    g.C2[o] = dsilu(val);
+                } else if (g.out_bf16) {
+                    ((__bf16 *)g.C)[o] = (__bf16)val;
+                } else {
+                    ((float *)g.C)[o] = val;
+                }
+            }
+        }
+}
+
+// 128 x 128 tiles: tile (tn, tm) of batch z; smem 64 KB
+__device__ __forceinline__ void gemm128_block(const GemmOp &g, int64_t tn, int64_t tm, int64_t z,
+                                              char *smem)
+{
+    __bf16(*sA)[TILE] = (__bf16(*)[TILE])smem;
+    __bf16(*sB)[TILE] = (__bf16(*)[TILE])(smem + 2 * TILE * sizeof(__bf16));
+    const int64_t m0 = tm * BM, n0 = tn * BN;
     const __bf16 *A = g.A + z * g.sA;
     const __bf16 *B = g.B + (g.bdiv ? (g.bz0 + z) / g.bdiv : z) * g.sB;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
@@ -615,34 +719,205 @@ __global__ __launch_bounds__(kT) void gemm_nt_kernel(GemmOp g)
         if (!body(ra1, rb1))
             break;
     }
+    gemm_out(g, z, m0 + wm * 64, n0 + wn * 64, acc);
+}
+
+// TM x 64 tiles (TM 64 or 32) for products too small to fill the GPU with 128 x
+// 128 ones: four waves of TM / 2 x 32, operands straight into LDS (dma_b128,
+// the row layout of lds_off), a ring of four 64-deep stages with three in
+// flight.  At this size a step is a few hundred cycles of products against a
+// load latency of one to two thousand, so what counts is workgroups and bytes
+// in flight.
+constexpr int kGSt = 4;            // stages
+constexpr int kGOp = 64 * BK * 2;  // bytes of the 64-row operand's stage (8 KB)
+template <int TM> constexpr int gemm_small_lds() { return kGSt * (kGOp + TM * BK * 2); }
+template <int TM>
+__device__ __forceinline__ void gemm_small_block(const GemmOp &g, int64_t tn, int64_t tm, int64_t z,
+                                                 char *smem)
+{
+    typedef __attribute__((address_space(3))) char lchar;
+    constexpr int NI = TM / 32;            // 16-row blocks per wave
+    constexpr int OPA = TM * BK * 2;       // bytes of A's stage
+    constexpr int NLA = OPA / 1024 / 4;    // 1 KB loads per wave and stage: A,
+    constexpr int NLB = kGOp / 1024 / 4;   // B
+    constexpr int NL = NLA + NLB;
+    const uint32_t lbase = (uint32_t)(uintptr_t)(lchar *)smem;
+    const int64_t m0 = tm * TM, n0 = tn * 64;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w >> 1, wn = w & 1;
+    const int vA = g.M - m0 < TM ? (int)(g.M - m0) : TM, vB = g.N - n0 < 64 ? (int)(g.N - n0) : 64;
+    const int lda = (int)g.lda, ldb = (int)g.ldb;
+    const i4 rsA = dma_rsrc(g.A + z * g.sA + m0 * g.lda, (uint32_t)(vA * lda * 2));
+    const i4 rsB = dma_rsrc(g.B + (g.bdiv ? (g.bz0 + z) / g.bdiv : z) * g.sB + n0 * g.ldb,
+                            (uint32_t)(vB * ldb * 2));
+    // load d of a wave: rows 8 d' .. 8 d' + 7 (d' = w + 4 d) of an operand, lane ->
+    // line rp = 4 d' + lane / 16, row 2 rp + (lane & 15) / 8, chunk (lane & 7) ^ (rp & 7)
+    int voA[NLA], voB[NLB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int d = 0; d < NLB; ++d) {
+        const int rp = 4 * (w + 4 * d) + (lane >> 4), row = 2 * rp + ((lane & 15) >> 3);
+        const int ch = ((lane & 7) ^ (rp & 7)) << 4;
+        if (d < NLA)
+            voA[d < NLA ? d : 0] = row * lda * 2 + ch;
+        voB[d] = row * ldb * 2 + ch;
+    }
+    const int nk = g.K / BK;
+    auto issue = [&](int s) {
+        const uint32_t st = lbase + (uint32_t)((s % kGSt) * (kGOp + OPA));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t row = m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + v;
-            if (row >= g.M)
-                continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t col = n0 + wn * 64 + j * 16 + (lane & 15);
-                if (col >= g.N)
-                    continue;
-                float val = acc[i][j][v];
-                if (g.scale)
-                    val *= g.scale[z * g.s_scale_b + (row >> g.grp_shift) * g.s_scale_g + col];
-                const int64_t o = z * g.sC + row * g.ldc + col;
-                if (g.add)
-                    val += (float)g.add[o];
-                if (g.act) {
-                    ((__bf16 *)g.C)[o] = (__bf16)silu(val);
-                    g.C2[o] = dsilu(val);
-                } else if (g.out_bf16) {
-                    ((__bf16 *)g.C)[o] = (__bf16)val;
-                } else {
-                    ((float *)g.C)[o] = val;
-                }
-            }
+        for (int d = 0; d < NLB; ++d) {
+            const uint32_t blk = (uint32_t)((w + 4 * d) * 1024);
+            if (d < NLA)
+                dma_b128(__builtin_amdgcn_readfirstlane(st + blk), rsA, voA[d < NLA ? d : 0],
+                         s * BK * 2);
+            dma_b128(__builtin_amdgcn_readfirstlane(st + OPA + blk), rsB, voB[d], s * BK * 2);
         }
+    };
+    f4 acc[NI][2];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < kGSt - 1; ++s)
+        if (s < nk)
+            issue(s);
+    uint32_t ro[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+        ro[ks] = (uint32_t)(lds_off(lane & 15, 4 * ks + (lane >> 4)) * 2);
+    for (int s = 0; s < nk; ++s) {
+        // stage s complete (at most the two after it in flight), and stage
+        // s - 1, whose place stage s + 3 takes, read by every wave
+        if (s + 2 < nk)
+            dma_barrier<2 * NL>();
+        else if (s + 1 < nk)
+            dma_barrier<NL>();
+        else
+            dma_barrier<0>();
+        if (s + kGSt - 1 < nk)
+            issue(s + kGSt - 1);
+        const uint32_t st = lbase + (uint32_t)((s % kGSt) * (kGOp + OPA));
+        bf16x8 a[2][NI], b[2][2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                a[ks][i] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + ro[ks] +
+                                                                  (wm * (TM / 2) + i * 16) * 128);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                b[ks][j] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + OPA + ro[ks] +
+                                                                  (wn * 32 + j * 16) * 128);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j],
+                                                                         acc[i][j], 0, 0, 0);
+    }
+    gemm_out(g, z, m0 + wm * (TM / 2), n0 + wn * 32, acc);
+}
+
+// The tiles of a product, by their rows TM (128 x 128, 64 x 64, 32 x 64):
+// columns fastest, then rows, then the batch.  Workgroup i runs on XCD i % 8
+// (the workgroups before a product's in its launch are a multiple of 8), and
+// each XCD takes one range of tiles, so that a region's weights go to one L2:
+// dealt out one by one, the tiles that share a weight tile sat on different
+// XCDs, and each read it from beyond its L2.
+constexpr int tile_cols(int TM) { return TM == 128 ? 128 : 64; }
+__host__ __device__ __forceinline__ int64_t gemm_tiles(const GemmOp &g, int64_t batch, int TM)
+{
+    const int TN = tile_cols(TM);
+    return (g.N + TN - 1) / TN * ((g.M + TM - 1) / TM) * batch;
+}
+int64_t round8(int64_t n) { return (n + 7) / 8 * 8; }
+int64_t gemm_blocks(const GemmOp &g, int64_t batch, int TM)
+{
+    return round8(gemm_tiles(g, batch, TM));
+}
+template <int TM>
+__device__ __forceinline__ void gemm_block(const GemmOp &g, int64_t batch, int64_t i, char *smem)
+{
+    constexpr int TN = tile_cols(TM);
+    const int64_t ntn = (g.N + TN - 1) / TN, ntm = (g.M + TM - 1) / TM;
+    const int64_t n = gemm_tiles(g, batch, TM), blk = i % 8 * ((n + 7) / 8) + i / 8;
+    if (i / 8 >= (n + 7) / 8 || blk >= n)
+        return;
+    const int64_t tn = blk % ntn, tm = blk / ntn % ntm, z = blk / ntn / ntm;
+    if constexpr (TM == 128)
+        gemm128_block(g, tn, tm, z, smem);
+    else
+        gemm_small_block<TM>(g, tn, tm, z, smem);
+}
+template <int TM> constexpr int gemm_lds()
+{
+    return TM == 128 ? 4 * TILE * 2 : gemm_small_lds<TM>();
+}
+
+template <int TM> __global__ __launch_bounds__(kT) void gemm_nt_kernel(GemmOp g, int64_t batch)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
+    gemm_block<TM>(g, batch, blockIdx.x, smem);
+}
+
+// ---- launches that join independent steps ------------------------------------------
+// A step of the small ones takes 5 to 10 us, most of it latency, and two that
+// do not need each other take as long together (19 launches became 9).
+
+// in: a = W_d1 m (bmv), and the 64-token partial sums of x_embed
+template <int NB>
+__global__ __launch_bounds__(kT) void in_kernel(RegionArgs q, BmvArgs v, int64_t nb)
+{
+    __shared__ __attribute__((aligned(16))) char smem[kBmvCols * 4];
+    if ((int64_t)blockIdx.x < nb)
+        bmv_block<NB>(v, q.K, blockIdx.x, smem);
+    else
+        xpart_block(q, blockIdx.x - nb);
+}
+
+// dec: d (bmv), P1, and the token mean of x_embed
+template <int NB>
+__global__ __launch_bounds__(kT) void dec_kernel(RegionArgs q, BmvArgs v, int64_t nb, int64_t np)
+{
+    __shared__ __attribute__((aligned(16))) char smem[64 * 129 * 4];
+    const int64_t i = blockIdx.x;
+    if (i < nb)
+        bmv_block<NB>(v, q.K, i, smem);
+    else if (i < nb + np)
+        p1_block(q, i - nb, smem);
+    else
+        xfin_block(q, i - nb - np);
+}
+
+// a bmv and a product
+template <int NB, int TM>
+__global__ __launch_bounds__(kT) void gemm_bmv_kernel(GemmOp g, BmvArgs v, int64_t nb, int64_t K)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
+    // (nb is rounded up to a multiple of 8)
+    if ((int64_t)blockIdx.x >= nb)
+        gemm_block<TM>(g, K, blockIdx.x - nb, smem);
+    else if ((int64_t)blockIdx.x < bmv_blocks(v.N, K, v.B, NB))
+        bmv_block<NB>(v, K, blockIdx.x, smem);
+}
+
+// a product and the LayerNorm of the forward, a wave per (sequence, region)
+template <int TM>
+__global__ __launch_bounds__(kT) void gemm_ln_kernel(GemmOp g, int64_t ng, RegionArgs q)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
+    if ((int64_t)blockIdx.x < ng) {
+        gemm_block<TM>(g, q.K, blockIdx.x, smem);
+    } else {
+        const int64_t bk = (blockIdx.x - ng) * 4 + threadIdx.x / 64;
+        if (bk < q.B * q.K)
+            ln_fwd_wave(q, bk);
+    }
 }
 
 // ---- ln_jac: J = diag(gamma) / sigma (I - 11^T/r - zhat zhat^T/r)(I + alpha Jenc),
@@ -661,15 +936,24 @@ __global__ __launch_bounds__(kT) void ln_jac_kernel(RegionArgs q)
     for (int i = threadIdx.x; i < r; i += kT)
         zh[i] = q.zhat[bk * r + i];
     __syncthreads();
-    for (int j = threadIdx.x; j < r; j += kT) {
-        float s = 0.0f, t = 0.0f;
-        for (int i = 0; i < r; ++i) {
-            const float v = (i == j ? 1.0f : 0.0f) + alpha * JT[(int64_t)j * r + i];
-            s += v;
-            t += zh[i] * v;
-        }
-        cm[j] = s / (float)r;
-        cd[j] = t / (float)r;
+    // kT / r lanes per column j of dz, each r^2 / kT of its rows
+    const int tpr = kT / r, cpr = r / tpr;
+    const int jc = threadIdx.x / tpr, i0 = (threadIdx.x % tpr) * cpr;
+    float s = 0.0f, t = 0.0f;
+#pragma unroll 4
+    for (int e = 0; e < cpr; ++e) {
+        const int i = i0 + e;
+        const float v = (i == jc ? 1.0f : 0.0f) + alpha * JT[(int64_t)jc * r + i];
+        s += v;
+        t += zh[i] * v;
+    }
+    for (int o = 1; o < tpr; o <<= 1) {
+        s += __shfl_xor(s, o);
+        t += __shfl_xor(t, o);
+    }
+    if (i0 == 0) {
+        cm[jc] = s / (float)r;
+        cd[jc] = t / (float)r;
     }
     __syncthreads();
     const float is = q.isig[bk];
@@ -1092,18 +1376,128 @@ __global__ __launch_bounds__(kT) void tfin_kernel(RegionArgs q, int64_t p0)
     q.dpT[o] = (__bf16)((float)q.JdT[o] * (1.0f + q.wv[z * D + dch]) + t / (float)q.L);
 }
 
+// Rows of a product's tiles: 128 while such tiles give every CU two, else 64,
+// and 32 where 64-row tiles do not give every CU one.  At M = 128, N = K = 768
+// over 8 regions 128-wide tiles are 48 workgroups of 12 serial steps (19.5 us),
+// 32-row ones 384 (18 us with the bmv of 3072 rows beside it); the whole
+// token-wise call of 2 sequences, 8 regions, 2048 tokens 442 -> 273 us with
+// the joined launches and the token parts, 3 x 5 x 333 tokens (D 320, r 32)
+// 172 -> 65, 1 x 1 x 17 93 -> 41, 8 x 16 x 2048 1660 -> 1566.
+int gemm_tile(const GemmOp &g, int64_t batch)
+{
+    return gemm_blocks(g, batch, 128) >= 512 ? 128 : gemm_blocks(g, batch, 64) > 256 ? 64 : 32;
+}
+// Sequences per wave of a bmv: 2 where there are no more.
+int bmv_nb(int64_t B) { return B <= 2 ? 2 : 8; }
+
+// f(integral_constant) for a runtime choice of tile rows
+template <typename F> void with_tile(int tm, F &&f)
+{
+    if (tm == 128)
+        f(std::integral_constant<int, 128>{});
+    else if (tm == 64)
+        f(std::integral_constant<int, 64>{});
+    else
+        f(std::integral_constant<int, 32>{});
+}
+
 hipError_t gemm(const GemmOp &g, int64_t batch, hipStream_t st)
 {
-    const dim3 grid((unsigned)((g.N + BN - 1) / BN), (unsigned)((g.M + BM - 1) / BM),
-                    (unsigned)batch);
-    hipLaunchKernelGGL(gemm_nt_kernel, grid, dim3(kT), 0, st, g);
+    const int tm = gemm_tile(g, batch);
+    const dim3 grid((unsigned)gemm_blocks(g, batch, tm));
+    with_tile(tm, [&](auto tag) {
+        hipLaunchKernelGGL(gemm_nt_kernel<decltype(tag)::value>, grid, dim3(kT), 0, st, g, batch);
+    });
+    return hipGetLastError();
+}
+
+// a product over the K regions beside a bmv
+hipError_t gemm_bmv(const GemmOp &g, const BmvArgs &v, int64_t K, hipStream_t st)
+{
+    const int tm = gemm_tile(g, K), nb = bmv_nb(v.B);
+    const int64_t nv = round8(bmv_blocks(v.N, K, v.B, nb));
+    const dim3 grid((unsigned)(nv + gemm_blocks(g, K, tm)));
+    with_tile(tm, [&](auto tag) {
+        constexpr int TM = decltype(tag)::value;
+        if (nb == 2)
+            hipLaunchKernelGGL((gemm_bmv_kernel<2, TM>), grid, dim3(kT), 0, st, g, v, nv, K);
+        else
+            hipLaunchKernelGGL((gemm_bmv_kernel<8, TM>), grid, dim3(kT), 0, st, g, v, nv, K);
+    });
     return hipGetLastError();
 }
 
 hipError_t bmv(const BmvArgs &a, int64_t K, hipStream_t st)
 {
-    const dim3 grid((unsigned)((a.N + 31) / 32), (unsigned)K, (unsigned)((a.B + 7) / 8));
-    hipLaunchKernelGGL(bmv_kernel, grid, dim3(kT), 0, st, a);
+    GemmOp none{};
+    none.M = none.N = 0;  // no tiles
+    return gemm_bmv(none, a, K, st);
+}
+
+// a product over the K regions beside the forward's LayerNorm
+hipError_t gemm_ln(const GemmOp &g, const RegionArgs &q, hipStream_t st)
+{
+    const int tm = gemm_tile(g, q.K);
+    const int64_t ng = gemm_blocks(g, q.K, tm);
+    const dim3 grid((unsigned)(ng + (q.B * q.K + 3) / 4));
+    with_tile(tm, [&](auto tag) {
+        hipLaunchKernelGGL(gemm_ln_kernel<decltype(tag)::value>, grid, dim3(kT), 0, st, g, ng, q);
+    });
+    return hipGetLastError();
+}
+
+// Dec_k and its operands, for both blocks: a = W_d1 m + b_d1 -> silu(a),
+// silu'(a) beside the partial means of x_embed; then d = W_d2 silu(a) + b_d2,
+// P1 and the means.
+hipError_t dec(const RegionArgs &q, hipStream_t st)
+{
+    const int64_t K = q.K;
+    const int D = q.D, r = q.r, nb = bmv_nb(q.B);
+    const int64_t nch = (q.L + 63) / 64;
+    BmvArgs v{(const __bf16 *)q.W_d1, (int64_t)D * r, q.m, K * r, r, q.b_d1, D, nullptr, 0, 0,
+              nullptr, 0, 0, nullptr, q.su, q.sa, K * D, D, q.B, D, r};
+    int64_t n0 = bmv_blocks(D, K, q.B, nb);
+    dim3 grid((unsigned)(n0 + nch * q.B));
+    if (nb == 2)
+        hipLaunchKernelGGL(in_kernel<2>, grid, dim3(kT), 0, st, q, v, n0);
+    else
+        hipLaunchKernelGGL(in_kernel<8>, grid, dim3(kT), 0, st, q, v, n0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    v = BmvArgs{(const __bf16 *)q.W_d2, (int64_t)D * D, q.su, K * D, D, q.b_d2, D, nullptr, 0, 0,
+                nullptr, 0, 0, q.d, nullptr, nullptr, K * D, D, q.B, D, D};
+    const int64_t np = q.B * K * (D / 64);
+    grid = dim3((unsigned)(n0 + np + q.B * ((D + kT - 1) / kT)));
+    if (nb == 2)
+        hipLaunchKernelGGL(dec_kernel<2>, grid, dim3(kT), 0, st, q, v, n0, np);
+    else
+        hipLaunchKernelGGL(dec_kernel<8>, grid, dim3(kT), 0, st, q, v, n0, np);
+    return hipGetLastError();
+}
+
+// The end of both blocks, from p, dp^T and silu(e), silu'(e): Enc_k beside T',
+// the LayerNorm beside Jenc, and the Jacobian.
+hipError_t enc(const RegionArgs &q, int rs, hipStream_t st)
+{
+    const int64_t K = q.K, Br = q.B * (int64_t)q.r;
+    const int D = q.D, r = q.r;
+    hipError_t e;
+    // T'^T[k] = (dp^T W_e1[k]^T) * silu'(e)[b][k][h]    (B r x D, K = D)
+    GemmOp g{q.dpT, D, Br * D, (const __bf16 *)q.W_e1, D, (int64_t)D * D, q.TT, D, Br * D, Br, D,
+             D, q.se, D, K * (int64_t)D, rs, nullptr, true};
+    // Enc = W_e2 silu(e) + b_e2
+    const BmvArgs v{(const __bf16 *)q.W_e2, (int64_t)r * D, q.sue, K * D, D, q.b_e2, r, nullptr, 0,
+                    0, nullptr, 0, 0, q.encv, nullptr, nullptr, K * r, r, q.B, r, D};
+    if ((e = gemm_bmv(g, v, K, st)) != hipSuccess)
+        return e;
+    // Jenc^T[k] = T'^T W_e2[k]^T                        (B r x r, K = D), fp32
+    g = GemmOp{q.TT, D, Br * D, (const __bf16 *)q.W_e2, D, (int64_t)r * D, q.JencT, r, Br * r, Br,
+               r, D, nullptr, 0, 0, 0, nullptr, false};
+    if ((e = gemm_ln(g, q, st)) != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(ln_jac_kernel, dim3((unsigned)(q.B * K)), dim3(kT),
+                       (size_t)3 * r * sizeof(float), st, q);
     return hipGetLastError();
 }
 
@@ -1111,95 +1505,48 @@ hipError_t bmv(const BmvArgs &a, int64_t K, hipStream_t st)
 
 hipError_t launch_region_jacobians(const RegionArgs &q, hipStream_t st)
 {
-    const int64_t BKn = q.B * q.K;
     const int64_t Br = q.B * (int64_t)q.r;
     const int D = q.D, X = q.X, r = q.r;
     const int64_t K = q.K;
+    const __bf16 *Wd2 = (const __bf16 *)q.W_d2, *W1 = (const __bf16 *)q.W1;
+    const __bf16 *W2 = (const __bf16 *)q.W2;
+    // the interface width is a power of two (16 .. 128): scale rows by shift
+    const int rs = r == 16 ? 4 : (r == 32 ? 5 : (r == 64 ? 6 : 7));
     hipError_t e;
-    // a = W_d1 m + b_d1 -> silu(a) (su), silu'(a) (sa)
-    BmvArgs v{};
-    v = BmvArgs{(const __bf16 *)q.W_d1, (int64_t)D * r, q.m, K * r, r, q.b_d1, D, nullptr, 0, 0,
-                nullptr, 0, 0, nullptr, q.su, q.sa, K * D, D, q.B, D, r};
-    if ((e = bmv(v, K, st)) != hipSuccess)
+    if ((e = dec(q, st)) != hipSuccess)
         return e;
-    // d = W_d2 silu(a) + b_d2
-    v = BmvArgs{(const __bf16 *)q.W_d2, (int64_t)D * D, q.su, K * D, D, q.b_d2, D, nullptr, 0, 0,
-                nullptr, 0, 0, q.d, nullptr, nullptr, K * D, D, q.B, D, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(p1_kernel, dim3((unsigned)BKn, (unsigned)(D / 64)), dim3(kT), 0, st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
+    // Jdec^T[k] = P1[k] W_d2[k]^T                      (B r x D, K = D)
+    GemmOp g{q.P1, D, Br * D, Wd2, D, (int64_t)D * D, q.JdT, D, Br * D, Br, D, D,
+             nullptr, 0, 0, 0, nullptr, true};
     // cvec = W1 d
-    v = BmvArgs{(const __bf16 *)q.W1, (int64_t)X * D, q.d, K * D, D, nullptr, 0, nullptr, 0, 0,
-                nullptr, 0, 0, q.cvec, nullptr, nullptr, K * X, X, q.B, X, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
+    BmvArgs v{W1, (int64_t)X * D, q.d, K * D, D, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, q.cvec,
+              nullptr, nullptr, K * X, X, q.B, X, D};
+    if ((e = gemm_bmv(g, v, K, st)) != hipSuccess)
         return e;
-    hipLaunchKernelGGL(xpart_kernel, dim3((unsigned)((q.L + 63) / 64), (unsigned)q.B), dim3(kT), 0,
-                       st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(xfin_kernel, dim3((unsigned)((D + kT - 1) / kT), (unsigned)q.B), dim3(kT),
+    hipLaunchKernelGGL(region_dma_kernel, dim3((unsigned)(K * q.B * (X / BN) * q.nsplit)), dim3(kT),
                        0, st, q);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
-    hipLaunchKernelGGL(region_dma_kernel, dim3((unsigned)(K * q.B * (X / BN))), dim3(kT), 0, st,
-                       q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    // p = W2 sbar + d + mean_l x_embed
-    v = BmvArgs{(const __bf16 *)q.W2, (int64_t)D * X, q.sbar, K * X, X, nullptr, 0, q.d, K * D, D,
-                q.xbar, D, 0, q.p, nullptr, nullptr, K * D, D, q.B, D, X};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    // e = W_e1 p + b_e1 -> silu(e) (sue), silu'(e) (se)
-    v = BmvArgs{(const __bf16 *)q.W_e1, (int64_t)D * D, q.p, K * D, D, q.b_e1, D, nullptr, 0, 0,
-                nullptr, 0, 0, nullptr, q.sue, q.se, K * D, D, q.B, D, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    // Enc = W_e2 silu(e) + b_e2
-    v = BmvArgs{(const __bf16 *)q.W_e2, (int64_t)r * D, q.sue, K * D, D, q.b_e2, r, nullptr, 0, 0,
-                nullptr, 0, 0, q.encv, nullptr, nullptr, K * r, r, q.B, r, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(ln_fwd_kernel, dim3((unsigned)BKn), dim3(64), 0, st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-
-    const __bf16 *Wd2 = (const __bf16 *)q.W_d2, *W1 = (const __bf16 *)q.W1;
-    const __bf16 *W2 = (const __bf16 *)q.W2, *We1 = (const __bf16 *)q.W_e1;
-    const __bf16 *We2 = (const __bf16 *)q.W_e2;
-    // the interface width is a power of two (16 .. 128): scale rows by shift
-    const int rs = r == 16 ? 4 : (r == 32 ? 5 : (r == 64 ? 6 : 7));
-    GemmOp g;
-    // Jdec^T[k] = P1[k] W_d2[k]^T                      (B r x D, K = D)
-    g = GemmOp{q.P1, D, Br * D, Wd2, D, (int64_t)D * D, q.JdT, D, Br * D, Br, D, D,
-               nullptr, 0, 0, 0, nullptr, true};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
-        return e;
     // U'^T[k] = (Jdec^T W1[k]^T) * gbar[b][k][x]        (B r x X, K = D)
+    const int64_t part = q.B * K * X;  // sbar, gbar: nsplit partial means
     g = GemmOp{q.JdT, D, Br * D, W1, D, (int64_t)X * D, q.UT, X, Br * X, Br, X, D,
-               q.gbar, X, q.K * (int64_t)X, rs, nullptr, true};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
+               q.gbar, X, K * (int64_t)X, rs, nullptr, true};
+    g.nscale = q.nsplit;
+    g.scale_ss = part;
+    // p = W2 sbar + d + mean_l x_embed
+    v = BmvArgs{W2, (int64_t)D * X, q.sbar, K * X, X, nullptr, 0, q.d, K * D, D,
+                q.xbar, D, 0, q.p, nullptr, nullptr, K * D, D, q.B, D, X, q.nsplit, part};
+    if ((e = gemm_bmv(g, v, K, st)) != hipSuccess)
         return e;
     // dp^T[k] = U'^T W2[k]^T + Jdec^T                   (B r x D, K = X)
     g = GemmOp{q.UT, X, Br * X, W2, X, (int64_t)D * X, q.dpT, D, Br * D, Br, D, X,
                nullptr, 0, 0, 0, q.JdT, true};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
+    // e = W_e1 p + b_e1 -> silu(e) (sue), silu'(e) (se)
+    v = BmvArgs{(const __bf16 *)q.W_e1, (int64_t)D * D, q.p, K * D, D, q.b_e1, D, nullptr, 0, 0,
+                nullptr, 0, 0, nullptr, q.sue, q.se, K * D, D, q.B, D, D};
+    if ((e = gemm_bmv(g, v, K, st)) != hipSuccess)
         return e;
-    // T'^T[k] = (dp^T W_e1[k]^T) * silu'(e)[b][k][h]    (B r x D, K = D)
-    g = GemmOp{q.dpT, D, Br * D, We1, D, (int64_t)D * D, q.TT, D, Br * D, Br, D, D,
-               q.se, D, q.K * (int64_t)D, rs, nullptr, true};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
-        return e;
-    // Jenc^T[k] = T'^T W_e2[k]^T                        (B r x r, K = D), fp32
-    g = GemmOp{q.TT, D, Br * D, We2, D, (int64_t)r * D, q.JencT, r, Br * r, Br, r, D,
-               nullptr, 0, 0, 0, nullptr, false};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(ln_jac_kernel, dim3((unsigned)BKn), dim3(kT), (size_t)3 * r * sizeof(float),
-                       st, q);
-    return hipGetLastError();
+    return enc(q, rs, st);
 }
 
 }  // namespace lbi
@@ -1214,29 +1561,9 @@ hipError_t launch_region_jacobians_ssm(const RegionArgs &q, hipStream_t st)
     const int64_t K = q.K, L = q.L;
     const int rs = r == 16 ? 4 : (r == 32 ? 5 : (r == 64 ? 6 : 7));
     const __bf16 *Wd2 = (const __bf16 *)q.W_d2, *W1 = (const __bf16 *)q.W1;
-    const __bf16 *W2 = (const __bf16 *)q.W2, *We1 = (const __bf16 *)q.W_e1;
-    const __bf16 *We2 = (const __bf16 *)q.W_e2;
+    const __bf16 *W2 = (const __bf16 *)q.W2;
     hipError_t e;
-    // Dec_k: a = W_d1 m + b_d1 -> silu(a), silu'(a); d = W_d2 silu(a) + b_d2
-    BmvArgs v{};
-    v = BmvArgs{(const __bf16 *)q.W_d1, (int64_t)D * r, q.m, K * r, r, q.b_d1, D, nullptr, 0, 0,
-                nullptr, 0, 0, nullptr, q.su, q.sa, K * D, D, q.B, D, r};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    v = BmvArgs{(const __bf16 *)q.W_d2, (int64_t)D * D, q.su, K * D, D, q.b_d2, D, nullptr, 0, 0,
-                nullptr, 0, 0, q.d, nullptr, nullptr, K * D, D, q.B, D, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(p1_kernel, dim3((unsigned)BKn, (unsigned)(D / 64)), dim3(kT), 0, st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(xpart_kernel, dim3((unsigned)((L + 63) / 64), (unsigned)q.B), dim3(kT), 0,
-                       st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(xfin_kernel, dim3((unsigned)((D + kT - 1) / kT), (unsigned)q.B), dim3(kT),
-                       0, st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
+    if ((e = dec(q, st)) != hipSuccess)
         return e;
     GemmOp g;
     // Jdec^T[k] = P1[k] W_d2[k]^T                      (B r x D, K = D)
@@ -1297,29 +1624,13 @@ hipError_t launch_region_jacobians_ssm(const RegionArgs &q, hipStream_t st)
             return e;
     }
 
-    // Enc_k and the LayerNorm, as for the token-wise block
-    v = BmvArgs{(const __bf16 *)q.W_e1, (int64_t)D * D, q.p, K * D, D, q.b_e1, D, nullptr, 0, 0,
-                nullptr, 0, 0, nullptr, q.sue, q.se, K * D, D, q.B, D, D};
+    // e = W_e1 p + b_e1 -> silu(e), silu'(e), and the end as for the token-wise
+    // block
+    const BmvArgs v{(const __bf16 *)q.W_e1, (int64_t)D * D, q.p, K * D, D, q.b_e1, D, nullptr, 0, 0,
+                    nullptr, 0, 0, nullptr, q.sue, q.se, K * D, D, q.B, D, D};
     if ((e = bmv(v, K, st)) != hipSuccess)
         return e;
-    v = BmvArgs{(const __bf16 *)q.W_e2, (int64_t)r * D, q.sue, K * D, D, q.b_e2, r, nullptr, 0, 0,
-                nullptr, 0, 0, q.encv, nullptr, nullptr, K * r, r, q.B, r, D};
-    if ((e = bmv(v, K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(ln_fwd_kernel, dim3((unsigned)BKn), dim3(64), 0, st, q);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    g = GemmOp{q.dpT, D, Br * D, We1, D, (int64_t)D * D, q.TT, D, Br * D, Br, D, D,
-               q.se, D, q.K * (int64_t)D, rs, nullptr, true};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
-        return e;
-    g = GemmOp{q.TT, D, Br * D, We2, D, (int64_t)r * D, q.JencT, r, Br * r, Br, r, D,
-               nullptr, 0, 0, 0, nullptr, false};
-    if ((e = gemm(g, q.K, st)) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(ln_jac_kernel, dim3((unsigned)BKn), dim3(kT), (size_t)3 * r * sizeof(float),
-                       st, q);
-    return hipGetLastError();
+    return enc(q, rs, st);
 }
 
 }  // namespace lbi

@@ -24,6 +24,8 @@ struct RegionArgs {
     float *su, *sa, *d, *cvec, *xpart, *xbar, *sbar, *gbar, *p, *sue, *se, *encv, *zhat, *isig,
         *JencT;
     __bf16 *P1, *JdT, *UT, *dpT, *TT;
+    int32_t nsplit;  // parts of the tokens in the token product (sbar, gbar: one
+                     // array [B][K][X] of partial means each)
     // the token-mixing block: per-channel decay [K][D]; (sequence, region)
     // pairs p = k B + b taken G at a time, each with its states s (bf16 and
     // fp32) and the constant-input states c [L][D], silu / silu' of W1 s

@@ -71,6 +71,20 @@ def test_region_shapes(r, shape):
     _check(synth.generate_region(wl), wl.name)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 300, 64, 1280, 16), (3, 2, 130, 64, 4224, 16),
+                                   (2, 1, 129, 64, 4224, 32), (9, 1, 40, 128, 128, 16),
+                                   (5, 3, 385, 192, 640, 64), (1, 7, 64, 576, 256, 128)])
+def test_region_tile_and_part_choices(shape):
+    """Token parts that do not divide the row tiles (3 and 4 tiles, the last
+    partly filled); vectors longer than the matrix-vector step's LDS part, by
+    8 and by 2 sequences per wave, and a ninth sequence; products whose last
+    32- and 64-row tiles are partly filled and whose tile count is no multiple
+    of 8; one and three sequences' worth of rows."""
+    B, K, L, D, X, r = shape
+    wl = synth.RegionWorkload(f"region_B{B}_K{K}_L{L}_D{D}_X{X}_r{r}", B, K, L, D, X, r, seed=23)
+    _check(synth.generate_region(wl), wl.name)
+
+
 def test_region_alpha_zero_is_layernorm_exactly():
     wl = synth.RegionWorkload("region_alpha0", 2, 2, 128, 128, 256, 32, seed=13)
     x = synth.generate_region(wl)

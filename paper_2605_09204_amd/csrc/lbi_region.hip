@@ -977,6 +977,7 @@ __global__ __launch_bounds__(kT) void ln_jac_kernel(RegionArgs q)
 // two products of r times the size of the forward's token products per
 // sequence and region (Eq. "jacobian-work"), which nothing here shortcuts.
 
+constexpr int64_t kCUs = 256;  // workgroups of the two tangent products: one per CU
 constexpr int kSsmChunks = 8;  // token chunks per channel in the recurrence kernels
 
 // ---- ssm_fwd: s (bf16, fp32) and c for 64 channels of one pair -------------------
@@ -1079,6 +1080,7 @@ struct GenArgs {
     int64_t L, p0, Bn;
     int D, X, rs;
     int ntn, ntm;       // 256-wide column tiles, 256-row tiles of a pair
+    int64_t ntiles;
 };
 
 // ---- the second tangent product: Tpart[z][c][j][d] = sum over the tokens l of
@@ -1090,6 +1092,7 @@ struct TokArgs {
     float *Tpart;       // [G][nchunk][r][D], nchunk = the 256-row tiles of L r
     int64_t L, p0, Bn;  // pair z is p0 + z, of region (p0 + z) / Bn
     int X, D, r, rs, nchunk;
+    int64_t ntiles;
 };
 
 // ---- ssm_s: the first tangent product's left operand S (GenArgs above), rounded
@@ -1126,16 +1129,48 @@ __global__ __launch_bounds__(kT) void ssm_s_kernel(RegionArgs q, int64_t p0)
 // LDS-write instructions; the rows (128 B) sit two to a 256-byte line with
 // chunk q of row R in slot ((R & 1) 8 + q) ^ ((R / 2) & 7), the layout of
 // lds_off, and each lane loads the global chunk that its LDS slot holds.
+//
+// A workgroup per CU takes one tile after another, and a tile's first stage
+// loads while the tile before it is weighted and stored: with a workgroup per
+// tile, its start, the latency of that first stage and of the weights, and the
+// end of its stores came on top of every tile.  The weights of a tile (the rows
+// of a [tokens][columns] fp32 array, 16 KB at most) load into LDS beside the
+// second stage.  2 sequences x 4 regions, L 1024, D 768, X 1536, r 64: gen_dma
+// 1448 -> 1391 us, tok_dma 1250 -> 1140, the call 3074 -> 2890.  Both are held
+// by the operands' way from L2 to LDS: 64 KB per stage and CU are 9.6 TB/s of L2
+// reads, the matrix cores 43% and 52% busy; reading half a stage ahead of the
+// products, or other row pitches of S and Vt, changed nothing.
 constexpr int kDT = 512;                  // threads
 constexpr int kDOp = 256 * BK * 2;        // bytes of one operand's stage (32 KB)
 constexpr int kDStage = 2 * kDOp;         // A and B
 constexpr int kDLoads = kDOp / 1024 / 8;  // 1 KB loads per wave, operand and stage
+constexpr int kDWeights = 16 * 256 * 4;   // weights of a tile: at most 16 tokens
+constexpr int kDLds = 2 * kDStage + kDWeights;
 
-// acc += the tile product over K (a multiple of 64); rows of A from rsA, of B
-// from rsB (resources that end at the last valid row, so no load leaves them;
-// the callers do not rely on what the products of rows past it hold)
-__device__ __forceinline__ void dtile_product(f4 (&acc)[8][4], i4 rsA, i4 rsB, int K, int w,
-                                              int lane, uint32_t lbase)
+// A tile: resources of its operands' rows (ending at the last valid row, so no
+// load leaves them; the epilogues do not rely on what the products of rows past
+// it hold) and of its weights (from the tile's first token and column, rows ldw
+// bytes apart), and whether its epilogue issues at least AFTER memory operations
+// in this wave (the wait for the next tile's first stage then counts past them).
+struct DTile {
+    i4 rsA, rsB, rsW;
+    bool many;
+};
+
+// x, as a value that the compiler does not know to be the same in every tile: an
+// epilogue's addresses, worked out before the loop and kept, do not fit the
+// registers beside the product.
+__device__ __forceinline__ int fresh(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// The tiles i = blockIdx.x, + gridDim.x, ... below n: setup(i) gives the tile,
+// epilogue(i, acc) weights and stores it.
+template <int AFTER, typename Setup, typename Epi>
+__device__ __forceinline__ void dtile_loop(int64_t n, int K, int tokens, int ldw, int w, int lane,
+                                           uint32_t lbase, Setup &&setup, Epi &&epilogue)
 {
     typedef __attribute__((address_space(3))) char lchar;
     const int wm = w >> 2, wn = w & 3;
@@ -1148,13 +1183,14 @@ __device__ __forceinline__ void dtile_product(f4 (&acc)[8][4], i4 rsA, i4 rsB, i
         const int rp = 4 * (w + 8 * d) + (lane >> 4);
         vo[d] = (2 * rp + ((lane & 15) >> 3)) * K * 2 + (((lane & 7) ^ (rp & 7)) << 4);
     }
-    auto issue = [&](int s) {
-        const uint32_t st = lbase + (uint32_t)((s & 1) * kDStage);
+    // stage s of a tile into buffer buf
+    auto issue = [&](const DTile &t, int s, int buf) {
+        const uint32_t st = lbase + (uint32_t)(buf * kDStage);
 #pragma unroll
         for (int d = 0; d < kDLoads; ++d) {
             const uint32_t blk = (uint32_t)((w + 8 * d) * 1024);
-            dma_b128(__builtin_amdgcn_readfirstlane(st + blk), rsA, vo[d], s * BK * 2);
-            dma_b128(__builtin_amdgcn_readfirstlane(st + kDOp + blk), rsB, vo[d], s * BK * 2);
+            dma_b128(__builtin_amdgcn_readfirstlane(st + blk), t.rsA, vo[d], s * BK * 2);
+            dma_b128(__builtin_amdgcn_readfirstlane(st + kDOp + blk), t.rsB, vo[d], s * BK * 2);
         }
     };
     // operand reads: row lane & 15 of a 16-row block, chunk 4 ks + lane / 16
@@ -1163,190 +1199,265 @@ __device__ __forceinline__ void dtile_product(f4 (&acc)[8][4], i4 rsA, i4 rsB, i
     for (int ks = 0; ks < 2; ++ks)
         ro[ks] = (uint32_t)(lds_off(lane & 15, 4 * ks + (lane >> 4)) * 2);
     const int nk = K / BK;
-    issue(0);
-    for (int t = 0; t < nk; ++t) {
-        dma_barrier<0>();  // stage t complete; stage t - 1 read by every wave
-        if (t + 1 < nk)
-            issue(t + 1);
-        const uint32_t st = lbase + (uint32_t)((t & 1) * kDStage);
-        bf16x8 a[2][8], b[2][4];
+    int64_t i = blockIdx.x;
+    if (i >= n)
+        return;
+    DTile cur = setup(i);
+    issue(cur, 0, 0);
+    int buf = 0;          // of the tile's next stage
+    bool counted = false; // AFTER operations follow the stage of the loop's first wait
+    for (;;) {
+        const int64_t inext = i + gridDim.x;
+        f4 acc[8][4];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+        for (int a = 0; a < 8; ++a)
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                a[ks][i] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + ro[ks] +
-                                                                  (wm * 128 + i * 16) * 128);
+            for (int b = 0; b < 4; ++b)
+                acc[a][b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        DTile next = cur;
+        for (int t = 0; t < nk; ++t) {
+            // stage t complete; stage t - 1 (or the last tile's) read by every wave
+            if (t == 0 && counted)
+                dma_barrier<AFTER>();
+            else
+                dma_barrier<0>();
+            if (t == 0)
+                for (int l = w; l < tokens; l += 8)
+                    dma_b128(__builtin_amdgcn_readfirstlane(
+                                 lbase + (uint32_t)(2 * kDStage + l * 1024)),
+                             cur.rsW, l * ldw + lane * 16, 0);
+            if (t + 1 < nk) {
+                issue(cur, t + 1, buf ^ 1);
+            } else if (inext < n) {
+                next = setup(inext);
+                issue(next, 0, buf ^ 1);
+            }
+            const uint32_t st = lbase + (uint32_t)(buf * kDStage);
+            buf ^= 1;
+            bf16x8 a[2][8], b[2][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                b[ks][j] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + kDOp + ro[ks] +
-                                                                  (wn * 64 + j * 16) * 128);
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    a[ks][e] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + ro[ks] +
+                                                                      (wm * 128 + e * 16) * 128);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    b[ks][e] = *(const bf16x8 *)(lchar *)(uintptr_t)(st + kDOp + ro[ks] +
+                                                                      (wn * 64 + e * 16) * 128);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int f = 0; f < 4; ++f)
+                        acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][e], b[ks][f],
+                                                                             acc[e][f], 0, 0, 0);
+            // all operand reads first, then the MFMAs (each waits only for its own)
+            __builtin_amdgcn_sched_group_barrier(0x100, 24, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 64, 0);
         }
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j],
-                                                                         acc[i][j], 0, 0, 0);
-        // all operand reads first, then the MFMAs (each waits only for its own)
-        __builtin_amdgcn_sched_group_barrier(0x100, 24, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 64, 0);
+        if (nk == 1)
+            dma_barrier<0>();  // the weights
+        epilogue(i, acc);
+        if (inext >= n)
+            return;
+        counted = cur.many && nk > 1;
+        cur = next;
+        i = inext;
     }
 }
 
-// ---- gen_dma: the first tangent product (GenArgs above), one 256 x 256 tile of
-//      one pair per workgroup; the epilogue scales by silu'(u) and stores bf16 ---
+// ---- gen_dma: the first tangent product (GenArgs above); the epilogue scales a
+//      tile by silu'(u) and stores it in bf16 -------------------------------------
 __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gen_dma_kernel(
     GenArgs a)
 {
-    __shared__ __attribute__((aligned(1024))) char smem[2 * kDStage];  // 128 KB
+    __shared__ __attribute__((aligned(1024))) char smem[kDLds];
     typedef __attribute__((address_space(3))) char lchar;
     const uint32_t lbase = (uint32_t)(uintptr_t)(lchar *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t lg = xcd_order(blockIdx.x, (int64_t)gridDim.x);
-    const int tn = (int)(lg % a.ntn);
-    const int tm = (int)((lg / a.ntn) % a.ntm);
-    const int64_t z = lg / ((int64_t)a.ntn * a.ntm);
-    const int64_t k = (a.p0 + z) / a.Bn;
     const int64_t Lr = a.L << a.rs;
-    const int64_t row0 = (int64_t)tm * 256, col0 = (int64_t)tn * 256;
-    const int vA = Lr - row0 < 256 ? (int)(Lr - row0) : 256;
-    const int vB = a.X - col0 < 256 ? (int)(a.X - col0) : 256;
     const int D = a.D;
-    const i4 rsA = dma_rsrc(a.S + (z * Lr + row0) * D, (uint32_t)vA * D * 2);
-    const i4 rsB = dma_rsrc(a.W1 + (k * a.X + col0) * D, (uint32_t)vB * D * 2);
-    f4 acc[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    dtile_product(acc, rsA, rsB, D, w, lane, lbase);
-    // (a 16-row block is one token: r is a multiple of 16.)  The scale factors
-    // are all loaded before the first store, so that one wait covers them.
+    struct At {
+        int64_t z, row0, col0;
+    };
+    auto at = [&](int64_t i) {
+        const int64_t lg = xcd_order(i, a.ntiles);
+        return At{lg / ((int64_t)a.ntn * a.ntm), (lg / a.ntn) % a.ntm * 256, lg % a.ntn * 256};
+    };
+    auto setup = [&](int64_t i) {
+        const At t = at(i);
+        const int64_t k = (a.p0 + t.z) / a.Bn, l0 = t.row0 >> a.rs;
+        const int vA = Lr - t.row0 < 256 ? (int)(Lr - t.row0) : 256;
+        const int vB = a.X - t.col0 < 256 ? (int)(a.X - t.col0) : 256;
+        return DTile{dma_rsrc(a.S + (t.z * Lr + t.row0) * D, (uint32_t)vA * D * 2),
+                     dma_rsrc(a.W1 + (k * a.X + t.col0) * D, (uint32_t)vB * D * 2),
+                     dma_rsrc(a.g32 + (t.z * a.L + l0) * a.X + t.col0,
+                              (uint32_t)((((vA - 1) >> a.rs) * a.X + vB) * 4)),
+                     vA == 256 && vB == 256};
+    };
+    // (a 16-row block is one token: r is a multiple of 16)
     const int wm = w >> 2, wn = w & 3;
-    const float *gz = a.g32 + z * a.L * a.X;
-    __bf16 *out = a.Vt + z * Lr * a.X;
-    float gs[8][4];
+    auto epilogue = [&](int64_t i, f4(&acc)[8][4]) {
+        const At t = at(i);
+        const int ln = fresh(lane), li = ln & 15, g = ln >> 4;
+        // Lane (g, li) holds columns li of the four 16-column blocks; a transpose
+        // among the lanes of a quad gives it four neighbouring columns of block
+        // li & 3, so that a row's 64 columns are one 128-byte piece of a store
+        // (2-byte stores of 32-byte pieces drained for 5 us of a 29 us tile).
+        // Two rows go through it packed in one register.
+        const bool odd = li & 1, upper = li & 2;
+        auto swap = [](uint32_t &x, uint32_t &y, bool up, auto mask) {
+            const uint32_t got = fbits(xchg<decltype(mask)::value>(bitsf(up ? x : y)));
+            x = up ? got : x;
+            y = up ? y : got;
+        };
+        __bf16 *out = a.Vt + t.z * Lr * a.X;
+        const int col = wn * 64 + (li & 3) * 16 + (li >> 2) * 4;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int64_t rb = row0 + wm * 128 + i * 16;
+        for (int e = 0; e < 8; ++e) {
+            const int rl = wm * 128 + e * 16;
+            const int64_t rb = t.row0 + rl;
+            if (rb >= Lr)
+                break;
+            float gs[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = col0 + wn * 64 + j * 16 + (lane & 15);
-            gs[i][j] = rb < Lr && col < a.X ? gz[(rb >> a.rs) * a.X + col] : 0.0f;
-        }
-    }
+            for (int j = 0; j < 4; ++j)
+                gs[j] = *(const float *)(lchar *)(uintptr_t)(
+                    lbase + (uint32_t)(2 * kDStage +
+                                       ((rl >> a.rs) * 256 + wn * 64 + j * 16 + li) * 4));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int64_t rb = row0 + wm * 128 + i * 16;
+            for (int v = 0; v < 4; v += 2) {
+                uint32_t x[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = col0 + wn * 64 + j * 16 + (lane & 15);
-            if (rb < Lr && col < a.X) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    out[(rb + 4 * (lane >> 4) + v) * a.X + col] = (__bf16)(acc[i][j][v] * gs[i][j]);
+                for (int j = 0; j < 4; ++j)
+                    x[j] = __builtin_bit_cast(
+                        uint32_t, __builtin_convertvector(f2{acc[e][j][v] * gs[j],
+                                                             acc[e][j][v + 1] * gs[j]}, bf16x2));
+                swap(x[0], x[1], odd, std::integral_constant<int, 1>{});
+                swap(x[2], x[3], odd, std::integral_constant<int, 1>{});
+                swap(x[0], x[2], upper, std::integral_constant<int, 2>{});
+                swap(x[1], x[3], upper, std::integral_constant<int, 2>{});
+                if (t.col0 + col < a.X) {
+                    __bf16 *o = out + (rb + 4 * g + v) * a.X + t.col0 + col;
+                    *(u2 *)o = u2{(x[0] & 0xFFFFu) | x[1] << 16, (x[2] & 0xFFFFu) | x[3] << 16};
+                    *(u2 *)(o + a.X) = u2{x[0] >> 16 | (x[1] & kHighHalf),
+                                          x[2] >> 16 | (x[3] & kHighHalf)};
+                }
             }
         }
-    }
+    };
+    dtile_loop<32>(a.ntiles, D, 256 >> a.rs, a.X * 4, w, lane, lbase, setup, epilogue);
 }
 
-// ---- tok_dma: the second tangent product (TokArgs above) on 256 x 256 tiles ------
-// One workgroup: one column tile of D and one 256-row tile c of a pair (a tile
-// row's token is row / r, its j is row mod r); it writes the tile's partial
-// sum Tpart[z][c].  The product is weighted by silu(s_l) and summed over the
+// ---- tok_dma: the second tangent product (TokArgs above) -------------------------
+// A tile is one column tile of D and one 256-row tile c of a pair (a tile
+// row's token is row / r, its j is row mod r); its partial sum goes to
+// Tpart[z][c].  The product is weighted by silu(s_l) and summed over the
 // tile's tokens: first over a wave's row blocks that share j (blocks i and
 // i + NB, NB = min(r, 128) / 16), then across the tile's two row halves
-// through LDS.
+// through LDS, in the stage that the next tile does not load into.
 template <int RS>
 __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) void tok_dma_kernel(
     TokArgs a)
 {
     constexpr int NB = (RS >= 7 ? 128 : (1 << RS)) / 16;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * kDStage];  // 128 KB
+    constexpr int NR = NB < 4 ? NB : 4;  // row blocks exchanged at a time (64 KB)
+    __shared__ __attribute__((aligned(1024))) char smem[kDLds];
     typedef __attribute__((address_space(3))) char lchar;
     const uint32_t lbase = (uint32_t)(uintptr_t)(lchar *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 2, wn = w & 3;
     const int64_t nct = (a.D + 255) / 256;
-    const int64_t lg = xcd_order(blockIdx.x, (int64_t)gridDim.x);
-    const int64_t z = lg / (nct * a.nchunk);
-    const int c = (int)((lg / nct) % a.nchunk);
-    const int64_t col0 = (lg % nct) * 256;
-    const int64_t k = (a.p0 + z) / a.Bn;
     const int64_t Lr = a.L << RS;
-    const int64_t row0 = (int64_t)c * 256;
-    const int vA = Lr - row0 < 256 ? (int)(Lr - row0) : 256;
-    const int vB = a.D - col0 < 256 ? (int)(a.D - col0) : 256;
-    const i4 rsA = dma_rsrc(a.Vt + (z * Lr + row0) * a.X, (uint32_t)vA * a.X * 2);
-    const i4 rsB = dma_rsrc(a.W2 + (k * a.D + col0) * a.X, (uint32_t)vB * a.X * 2);
-    f4 acc[8][4];
+    struct At {
+        int64_t z, row0, col0;
+        int c;
+    };
+    auto at = [&](int64_t i) {
+        const int64_t lg = xcd_order(i, a.ntiles);
+        const int c = (int)((lg / nct) % a.nchunk);
+        return At{lg / (nct * a.nchunk), (int64_t)c * 256, lg % nct * 256, c};
+    };
+    auto setup = [&](int64_t i) {
+        const At t = at(i);
+        const int64_t k = (a.p0 + t.z) / a.Bn, l0 = t.row0 >> RS;
+        const int vA = Lr - t.row0 < 256 ? (int)(Lr - t.row0) : 256;
+        const int vB = a.D - t.col0 < 256 ? (int)(a.D - t.col0) : 256;
+        return DTile{dma_rsrc(a.Vt + (t.z * Lr + t.row0) * a.X, (uint32_t)vA * a.X * 2),
+                     dma_rsrc(a.W2 + (k * a.D + t.col0) * a.X, (uint32_t)vB * a.X * 2),
+                     dma_rsrc(a.s32 + (t.z * a.L + l0) * a.D + t.col0,
+                              (uint32_t)((((vA - 1) >> RS) * a.D + vB) * 4)),
+                     RS >= 6 && vA == 256 && vB == 256 && wm == 0};
+    };
+    const int nk = a.X / BK;
+    int done = 0;  // tiles finished: the last stage of tile t was in buffer (t + 1) nk - 1 mod 2
+    auto epilogue = [&](int64_t i, f4(&acc)[8][4]) {
+        const At t = at(i);
+        const int ln = fresh(lane), li = ln & 15, g = ln >> 4;
+        // (rows past L r are left out by selects: their products may be anything)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    dtile_product(acc, rsA, rsB, a.X, w, lane, lbase);
-    // weights, all loaded before they are used (rows past L r and columns past
-    // D are left out by selects: their products may be anything)
-    const float *sz = a.s32 + z * a.L * a.D;
-    float wt[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int64_t l = (row0 + wm * 128 + i * 16) >> RS;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = col0 + wn * 64 + j * 16 + (lane & 15);
-            wt[i][j] = l < a.L && col < a.D ? silu(sz[l * a.D + col]) : 0.0f;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const bool live = (row0 + wm * 128 + i * 16) < Lr;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float x = live ? wt[i][j] * acc[i][j][v] : 0.0f;
-                if (i < NB)
-                    acc[i][j][v] = x;
-                else
-                    acc[i % NB][j][v] += x;
-            }
-    }
-    // the lower row half adds the upper one's sums through LDS ([j][256] fp32)
-    __syncthreads();  // (every wave is past its operand reads)
-    float *red = (float *)smem;
-    if (wm == 1) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    red[(i * 16 + 4 * (lane >> 4) + v) * 256 + wn * 64 + j * 16 + (lane & 15)] =
-                        acc[i][j][v];
-    }
-    __syncthreads();
-    if (wm == 0) {
-        float *out = a.Tpart + (z * a.nchunk + c) * ((int64_t)a.D << RS);
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
+        for (int e = 0; e < 8; ++e) {
+            const int rl = wm * 128 + e * 16;
+            const bool live = t.row0 + rl < Lr;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int cl = wn * 64 + j * 16 + (lane & 15);
-                if (col0 + cl < a.D) {
+                const float wt = silu(*(const float *)(lchar *)(uintptr_t)(
+                    lbase + (uint32_t)(2 * kDStage +
+                                       ((rl >> RS) * 256 + wn * 64 + j * 16 + li) * 4)));
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int jr = i * 16 + 4 * (lane >> 4) + v;
-                        out[(int64_t)jr * a.D + col0 + cl] = acc[i][j][v] + red[jr * 256 + cl];
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const float x = live ? wt * acc[e][j][v] : 0.0f;
+                    if (e < NB)
+                        acc[e][j][v] = x;
+                    else
+                        acc[e % NB][j][v] += x;
                 }
             }
-    }
+        }
+        // the lower row half adds the upper one's sums through LDS ([j][256] fp32)
+        const uint32_t red = lbase + (uint32_t)((((done + 1) * nk - 1) & 1) * kDStage);
+        ++done;
+        float *out = a.Tpart + (t.z * a.nchunk + t.c) * ((int64_t)a.D << RS);
+#pragma unroll
+        for (int h = 0; h < NB; h += NR) {
+            __syncthreads();  // (the operand reads, or the sums before, are done)
+            if (wm == 1) {
+#pragma unroll
+                for (int e = 0; e < NR; ++e)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            *(float *)(lchar *)(uintptr_t)(
+                                red + (uint32_t)(((e * 16 + 4 * g + v) * 256 + wn * 64 +
+                                                  j * 16 + li) * 4)) = acc[h + e][j][v];
+            }
+            __syncthreads();
+            if (wm == 0) {
+#pragma unroll
+                for (int e = 0; e < NR; ++e)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int cl = wn * 64 + j * 16 + li;
+                        if (t.col0 + cl < a.D) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const int jr = e * 16 + 4 * g + v;
+                                out[(int64_t)(h * 16 + jr) * a.D + t.col0 + cl] =
+                                    acc[h + e][j][v] +
+                                    *(const float *)(lchar *)(uintptr_t)(
+                                        red + (uint32_t)((jr * 256 + cl) * 4));
+                            }
+                        }
+                    }
+            }
+        }
+    };
+    dtile_loop<63>(a.ntiles, a.X, 256 >> RS, a.D * 4, w, lane, lbase, setup, epilogue);
 }
 
 // ---- tfin: dp^T[pair][j][d] = Jdec^T (1 + w[d]) + (1/L) sum_c Tpart[z][c][j][d] ----
@@ -1602,12 +1713,15 @@ hipError_t launch_region_jacobians_ssm(const RegionArgs &q, hipStream_t st)
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         const int ntn = (X + 255) / 256, ntm = (int)((Lr + 255) / 256);
-        GenArgs ga{q.S16, W1, q.g32, q.Vt, L, p0, q.B, D, X, rs, ntn, ntm};
-        hipLaunchKernelGGL(gen_dma_kernel, dim3((unsigned)(ntn * ntm * gz)), dim3(kDT), 0, st, ga);
+        const int64_t gtiles = (int64_t)ntn * ntm * gz;
+        GenArgs ga{q.S16, W1, q.g32, q.Vt, L, p0, q.B, D, X, rs, ntn, ntm, gtiles};
+        hipLaunchKernelGGL(gen_dma_kernel, dim3((unsigned)(gtiles < kCUs ? gtiles : kCUs)),
+                           dim3(kDT), 0, st, ga);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
-        TokArgs ta{q.Vt, W2, q.s32, q.Tpart, L, p0, q.B, X, D, r, rs, q.nchunk};
-        const dim3 tgrid((unsigned)(nctw * q.nchunk * gz));
+        const int64_t ttiles = (int64_t)nctw * q.nchunk * gz;
+        TokArgs ta{q.Vt, W2, q.s32, q.Tpart, L, p0, q.B, X, D, r, rs, q.nchunk, ttiles};
+        const dim3 tgrid((unsigned)(ttiles < kCUs ? ttiles : kCUs));
         if (rs == 4)
             hipLaunchKernelGGL(tok_dma_kernel<4>, tgrid, dim3(kDT), 0, st, ta);
         else if (rs == 5)

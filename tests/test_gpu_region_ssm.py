@@ -70,6 +70,15 @@ def test_region_ssm_shapes(r, shape):
     _check(synth.generate_region(wl), wl.name)
 
 
+@pytest.mark.parametrize("r", [16, 32, 64, 128])
+def test_region_ssm_several_tiles_per_workgroup(r):
+    """More than 256 tiles in both tangent products, so that workgroups go from
+    one tile to the next: whole ones, the partial column tiles (X = 384, D =
+    320) and each pair's partial last row tile, in every order."""
+    wl = synth.RegionWorkload(f"ssm_tiles_r{r}", 1, 2, 21312 // r + 1, 320, 384, r, seed=47 + r)
+    _check(synth.generate_region(wl), wl.name)
+
+
 @pytest.mark.parametrize("decay", [0.0, 1.0])
 def test_region_ssm_limit_decays(decay):
     """a = 0: each state is its token (no mixing); a = 1: no token enters the

@@ -101,20 +101,25 @@ typedef enum {
 
 /* How the slots of a chain are scanned (lbi_scan_backward_ex). */
 typedef enum {
-    LBI_ALGO_AUTO = 0,      /* for K >= 16, the one a cost model fitted to
-                             * MI355X timings predicts faster: the chain scan
-                             * costs K serial slot steps, the two-level scan
-                             * K/S slot steps over B*S workgroups, S carry
-                             * steps and 8 B K r^2 bytes of composite traffic;
-                             * few long chains go two-level.  K < 16: chain.
+    LBI_ALGO_AUTO = 0,      /* for K >= 16, the one that MI355X timings put
+                             * ahead: the chain scan costs K serial slot steps,
+                             * the two-level scan 2 K/S slot steps over B*S
+                             * workgroups and S carry steps; few long chains go
+                             * two-level, up to a number of chains that depends
+                             * on the dtype and r (about 1350, 500, 126 and 100
+                             * for fp32 at r = 16, 32, 64, 128; 1600, 760, 255
+                             * and 104 for bf16, without b 1700, 500, 190 and
+                             * 104) and is lower for short chains.
+                             * K < 16: chain.
                              * Otherwise bf16 with r <= 32 and B <= 8192 goes
                              * to LBI_ALGO_CHAIN_WAVE, and fp32 with r = 64 in
                              * the split arithmetic and B <= 256 to
                              * LBI_ALGO_CHAIN_SPLITK.  Before all of these,
                              * chains that fit one tree chunk at r <= 32
                              * (K <= 16; K >= 5 for fp32, K >= 9 for bf16;
-                             * B <= 256; the default arithmetic) go to one
-                             * launch of LBI_ALGO_TREE.  Where AUTO would take
+                             * B <= 256, for fp32 with K >= 12 B <= 512; the
+                             * default arithmetic) go to one launch of
+                             * LBI_ALGO_TREE.  Where AUTO would take
                              * LBI_ALGO_CHAIN for bf16 stored at r = 128 (the
                              * default arithmetic) and the widths hint is one
                              * LBI_ALGO_CHAIN_RING takes, it takes that      */
@@ -226,9 +231,14 @@ size_t lbi_scan_backward_workspace_bytes(int64_t B, int64_t K, int32_t r, lbi_dt
  * LBI_ALGO_CHAIN, LBI_ALGO_CHAIN_WAVE, LBI_ALGO_CHAIN_SPLITK and
  * LBI_ALGO_CHAIN_RING; for
  * LBI_ALGO_TWO_LEVEL about 4 B S r (r + 2) bytes with S ~ sqrt(2K) (the
- * segment aggregates in float32, plus the carries), or 4 B K r (r + 2) while
- * every composite fits 256 MiB; for LBI_ALGO_TREE about 4 B (K / C) r (r + 2)
- * bytes summed over its levels (0 for K <= C).
+ * segment aggregates in float32, plus the carries), or 4 B K r (r + 2) for
+ * the smaller batches, whose composites are all kept (fp32: up to 100 MiB of
+ * them, 256 MiB at r = 128; bf16: below 16 chains, 32 at r = 16, up to
+ * 256 MiB); for LBI_ALGO_TREE about 4 B (K / C) r (r + 2) bytes summed over
+ * its levels (0 for K <= C).  LBI_ALGO_AUTO: enough for the algorithm it takes,
+ * with or without b, in every arithmetic and for every widths hint.  At the
+ * larger numbers of chains for which it takes the two-level scan, a call that
+ * is given less workspace (or none) runs the chain scan instead.
  */
 size_t lbi_scan_backward_workspace_bytes_ex(int64_t B, int64_t K, int32_t r, lbi_dtype dt,
                                             lbi_algo algo);
@@ -305,7 +315,7 @@ lbi_status lbi_scan_backward_ex(const void *A, const void *b, const void *lambda
  * The algorithm is the one lbi_scan_backward_ex would run.  A two-level scan
  * whose composites would not fit the array keeps only the segment aggregates
  * and scans each segment again from its carry (the form lbi_scan_backward_ex
- * takes past 256 MiB of composites); its results then agree with
+ * takes for the larger batches); its results then agree with
  * lbi_scan_backward_ex's to float32 rounding rather than bit for bit.  A call
  * whose aggregates do not fit either returns LBI_ERR_SCRATCH before anything
  * is enqueued.  The chain algorithms use no scratch and give exactly the

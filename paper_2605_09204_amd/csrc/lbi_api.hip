@@ -89,11 +89,21 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   * every composite kept (fp32, 4 B K r^2 bytes written and read again),
 //     then one parallel apply pass: the shorter span, for small batches;
 //   * aggregates only, then each segment scanned again from its carry: the
-//     composites never reach memory (A is read twice instead), for batches
-//     whose composites would not fit the 256 MB last-level cache.  Measured
-//     at r = 64 fp32, K = 512, same box: 2% slower at B = 16 (134 MB of
-//     composites), 14% faster at B = 64 (537 MB), 33% slower at B = 1.
-constexpr double kRescanBytes = 256.0 * (1 << 20);
+//     composites never reach memory (A is read twice instead).
+// Measured on MI355X (us, kept / scanned again).  bf16, whose A is half as many
+// bytes as its composites': r = 64, K = 128, 16 chains 34 / 26, 64 chains 59 /
+// 44, 128 chains 144 / 71; r = 32, K = 500, 16 chains 30 / 31, 128 chains 155 /
+// 71; r = 16, K = 500, 16 chains 21 / 23, 32 chains 25 / 24.  fp32: r = 64, 64
+// MB of composites 45 / 49, 125 MB 90 / 79, 250 MB 171 / 141; r = 32, 62 MB 41 /
+// 42, 125 MB 82 / 65; r = 128, 128 MB 106 / 102 and 109 / 126, 250 MB 227 / 245,
+// 500 MB 448 / 405 and 394 / 406.
+bool two_level_rescan(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
+{
+    const double mib = 4.0 * (double)B * K * r * r / (1 << 20);
+    if (dt == LBI_BF16)
+        return B >= (r == 16 ? 32 : 16) || mib > 256.0;
+    return mib > (r == 128 ? 256.0 : 100.0);
+}
 
 struct TwoLevelPlan {
     int64_t L;
@@ -103,7 +113,8 @@ struct TwoLevelPlan {
 };
 
 // (force_rescan: the aggregates-only form whatever the composites' size)
-TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, bool force_rescan = false)
+TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, lbi_dtype dt,
+                            bool force_rescan = false)
 {
     TwoLevelPlan p;
     int64_t S = (int64_t)ceil(sqrt(2.0 * (double)K));
@@ -113,7 +124,7 @@ TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, bool force_rescan =
         S = 1;
     p.L = (K + S - 1) / S;
     p.S = (int32_t)((K + p.L - 1) / p.L);
-    p.rescan = force_rescan || 4.0 * (double)B * K * r * r > kRescanBytes;
+    p.rescan = force_rescan || two_level_rescan(B, K, r, dt);
     const int64_t nslots = p.rescan ? (int64_t)p.S : K;  // composites kept per chain
     const size_t nP = (size_t)B * nslots * r * r * sizeof(float);
     const size_t nc = (size_t)B * nslots * r * sizeof(float);
@@ -216,8 +227,9 @@ hipError_t run_tree(const void *A, const void *b, const void *lamK, float *lam, 
     return hipSuccess;
 }
 
-// Microseconds per slot of one chain-kernel workgroup on an otherwise idle
-// MI355X (r = 16, 32, 64, 128; fp32 storage in the default arithmetic).
+// Microseconds per slot of one workgroup of the chain kernel on an otherwise
+// idle MI355X (r = 16, 32, 64, 128; fp32 storage: the split arithmetic up to r =
+// 64, the fp32 matrix cores at 128).
 double slot_us(lbi_dtype dt, int32_t r)
 {
     const int i = r == 16 ? 0 : (r == 32 ? 1 : (r == 64 ? 2 : 3));
@@ -227,16 +239,69 @@ double slot_us(lbi_dtype dt, int32_t r)
 
 // Chains per launch up to which AUTO takes LBI_ALGO_CHAIN_SPLITK: one per CU.
 constexpr int64_t kSplitKMaxB = 256;
-// Chains per launch up to which AUTO takes a single launch of LBI_ALGO_TREE
-// (the batches it was measured on).
-constexpr int64_t kTreeMaxB = 256;
+// Chains per launch up to which AUTO takes a single launch of LBI_ALGO_TREE; for
+// fp32 from 12 slots on two of its workgroups share a CU and are still the faster
+// scan (r = 32, 512 chains: 16 slots 10.3 us, the chain kernel 16.4; 13 slots 9.8
+// and 13.9; with 777 chains 19.6 against 17.5).
+constexpr int64_t kTreeMaxB = 256, kTreeLongMaxB = 512;
 
-// LBI_ALGO_AUTO: the cheaper of the two by a cost model fitted to MI355X
-// timings (B = 1..512, K = 32..512, every r; within 13% of the faster choice
-// everywhere on that grid).  Chain scan: K serial slot steps, slower once the
-// chains hold more than 1280 waves.  Two-level scan: K/S slot steps over B*S
-// workgroups, S carry steps, and the composites written and read once
-// (8 B K r^2 bytes at 5.8 TB/s).
+// The chain or the two-level scan, by a cost model fitted to MI355X timings of
+// the workgroup chain kernel (B = 1..512, K = 32..512, every r): chain scan, K
+// serial slot steps, slower once the chains hold more than 1280 waves; two-level
+// scan, K/S slot steps over B*S workgroups, S carry steps, and the composites
+// written and read once (8 B K r^2 bytes at 5.8 TB/s).  Used for the
+// arithmetics that are not the default.
+bool two_level_by_model(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
+{
+    if (K < 16 || !two_level_possible(B, K))
+        return false;
+    const double ts = slot_us(dt, r), w = waves_for_r(r), cap = 1280.0;
+    const double t_chain = 6.0 + (double)K * ts * fmax(1.0, (double)B * w / cap);
+    const TwoLevelPlan p = two_level_plan(B, K, r, dt);
+    // (three launches: 18 us of fixed cost, measured with HIP events at
+    // B = 1..16, K = 16..64, where the chain scan's one launch costs 6 us
+    // plus its slots)
+    const double two = 18.0 + (double)p.L * ts * fmax(1.0, (double)B * p.S * w / cap) +
+                       0.22 * p.S * sqrt(r / 64.0) + 8.0 * (double)B * K * r * r / 5.8e6;
+    return two < t_chain;
+}
+
+// The same choice for the default arithmetic, against the chain kernel that AUTO
+// would take (one wave per chain for bf16 up to r = 32, sixteen for fp32 at r =
+// 64, the panel kernel for fp32 at r = 128).  The two-level scan gains while its
+// segments find idle CUs, up to a number of chains that its fixed cost lowers
+// for short ones: B <= Bmax (1 - K0 / K).  Measured (us, chain / two-level), one
+// pair on each side of the line or one at it: fp32 r = 16, K = 48: 300 21 / 18,
+// 600 21 / 21; K = 250: 1024 140 / 118, 1280 155 / 159; r = 32, K = 20: 6 14 /
+// 15 (a two-level call costs the host about 15); K = 128: 448 113 / 104, 512 114 /
+// 125; r = 64, K = 64: 96 65 / 67, 80 65 / 59; K = 500: 112 501 / 491, 128 502 /
+// 552; K = 356: 119 407 / 372; r = 128, K = 40: 96 188 / 184, 112 190 /
+// 236.  bf16 without an affine term, where the chain kernels' slot is shorter by
+// a third to a half: r = 16, K = 128: 300 26 / 20, 600 28 / 28; r = 32, K = 128:
+// 200 39 / 33, 300 40 / 41; r = 64, K = 128: 144 81 / 68, 176 81 / 79; with one:
+// r = 16, K = 64: 512 23 / 23; r = 32, K = 500: 640 393 / 337, 768 396 / 404;
+// r = 64, K = 128: 224 121 / 121; K = 400: 240 411 / 381; r = 128 (either), K =
+// 64: 80 195 / 187, 96 196 / 221.  Where the model above chose differently it was
+// off by up to 2.8 times (bf16, r = 32, 256 chains of 500 slots: 369 us in the
+// chain scan, 135 here).
+bool two_level_by_size(int64_t B, int64_t K, int32_t r, lbi_dtype dt, bool aff)
+{
+    if (K < 16 || !two_level_possible(B, K))
+        return false;
+    const int i = r == 16 ? 0 : (r == 32 ? 1 : (r == 64 ? 2 : 3));
+    static const double f32[4][2] = {{1350, 36}, {500, 22}, {126, 12}, {100, 4}};
+    static const double bf16[4][2] = {{1600, 40}, {760, 24}, {255, 12}, {104, 9}};
+    static const double bf16_noaff[4][2] = {{1700, 80}, {500, 45}, {190, 16}, {104, 9}};
+    const double *c = dt != LBI_BF16 ? f32[i] : (aff ? bf16[i] : bf16_noaff[i]);
+    return (double)B <= c[0] * (1.0 - c[1] / (double)K);
+}
+
+bool default_math(lbi_math math)
+{
+    return math != LBI_MATH_F32_MFMA && math != LBI_MATH_BF16_SINGLE;
+}
+
+// LBI_ALGO_AUTO.
 // Chains that the two-level scan does not take: bf16 chains of width <= 32
 // go to the wavefront-per-chain kernel (no barrier, no LDS staging), which
 // measured 1.3-1.9x faster than the workgroup kernel up to B = 4096 and no
@@ -244,10 +309,10 @@ constexpr int64_t kTreeMaxB = 256;
 // workgroup kernel is faster.  fp32 chains at r = 64 in the split arithmetic,
 // at most one per CU, go to the sixteen-wave kernel (split contraction,
 // specialised staging waves): 1.2-1.3x faster than the workgroup kernel for
-// B <= 128 and 1.07-1.2x at B = 256, and slower once chains share CUs.  The choice between the
-// chain and two-level scans does not depend on the arithmetic, so the
-// workspace query needs none.
-lbi_algo resolve_algo(lbi_algo algo, int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math)
+// B <= 128 and 1.07-1.2x at B = 256, and slower once chains share CUs.
+// (no_two_level: the choice among the rest)
+lbi_algo resolve_algo(lbi_algo algo, int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math,
+                      bool aff, bool no_two_level = false)
 {
     if (algo != LBI_ALGO_AUTO)
         return algo;
@@ -257,25 +322,18 @@ lbi_algo resolve_algo(lbi_algo algo, int64_t B, int64_t K, int32_t r, lbi_dtype 
     // 12.7 us at r = 32), for bf16 only past K = 8 (at smaller K the
     // wavefront-per-chain kernel is as fast or faster); at r = 64 the chain
     // kernels win
-    if (r <= 32 && B <= kTreeMaxB && K <= tree_chunk(r) && math != LBI_MATH_F32_MFMA &&
-        math != LBI_MATH_BF16_SINGLE && K >= (dt == LBI_F32 ? 5 : 9))
+    if (r <= 32 && B <= (dt == LBI_F32 && K >= 12 ? kTreeLongMaxB : kTreeMaxB) &&
+        K <= tree_chunk(r) && default_math(math) &&
+        K >= (dt == LBI_F32 ? 5 : 9))
         return LBI_ALGO_TREE;
     const lbi_algo chain =
         dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r <= 32 && B <= 8192 ? LBI_ALGO_CHAIN_WAVE
         : dt == LBI_F32 && math != LBI_MATH_F32_MFMA && r == 64 && B <= kSplitKMaxB
             ? LBI_ALGO_CHAIN_SPLITK
             : LBI_ALGO_CHAIN;
-    if (K < 16 || !two_level_possible(B, K))
-        return chain;
-    const double ts = slot_us(dt, r), w = waves_for_r(r), cap = 1280.0;
-    const double t_chain = 6.0 + (double)K * ts * fmax(1.0, (double)B * w / cap);
-    const TwoLevelPlan p = two_level_plan(B, K, r);
-    // (three launches: 18 us of fixed cost, measured with HIP events at
-    // B = 1..16, K = 16..64, where the chain scan's one launch costs 6 us
-    // plus its slots)
-    const double two = 18.0 + (double)p.L * ts * fmax(1.0, (double)B * p.S * w / cap) +
-                       0.22 * p.S * sqrt(r / 64.0) + 8.0 * (double)B * K * r * r / 5.8e6;
-    return two < t_chain ? LBI_ALGO_TWO_LEVEL : chain;
+    const bool two = !no_two_level && (default_math(math) ? two_level_by_size(B, K, r, dt, aff)
+                                                          : two_level_by_model(B, K, r, dt));
+    return two ? LBI_ALGO_TWO_LEVEL : chain;
 }
 
 bool valid_algo(lbi_algo algo)
@@ -449,19 +507,30 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     const size_t nl = (size_t)B * r * esz, nout = (size_t)B * K * r * sizeof(float);
     if (overlaps(lam, nout, A, nA) || overlaps(lam, nout, b, nb) || overlaps(lam, nout, lamK, nl))
         return LBI_ERR_ALIAS;
-    lbi_algo use = resolve_algo(algo, B, K, r, dt, math);
+    // (bf16 chains at width 128 in widths of the LDS-ring kernel: its chain scan
+    // is faster than the one two_level_by_size knows)
+    const bool ring = dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r == 128 &&
+                      ring_plan(widths, K, r).ok;
+    lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr,
+                                ring && !two_level_by_model(B, K, r, dt));
+    // A two-level scan that the model would not take is an offer: without the
+    // workspace (or scratch) for it, the chain scan.
+    if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_TWO_LEVEL && !two_level_by_model(B, K, r, dt)) {
+        const size_t least = two_level_plan(B, K, r, dt, true).bytes;
+        if (scratch ? least > kScratchBytes : !ws || ws_bytes < two_level_plan(B, K, r, dt).bytes)
+            use = resolve_algo(algo, B, K, r, dt, math, b != nullptr, true);
+    }
     // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes
     // (the mixed-width case): that kernel, measured 1.45x faster there than
     // the workgroup kernel (188 against 275 us on 1024 chains of 64 slots of
     // widths 32/64/128); at width 64 the two tie
-    if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_CHAIN && dt == LBI_BF16 &&
-        math != LBI_MATH_BF16_SINGLE && r == 128 && ring_plan(widths, K, r).ok)
+    if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_CHAIN && ring)
         use = LBI_ALGO_CHAIN_RING;
-    TwoLevelPlan p = two_level_plan(B, K, r);
+    TwoLevelPlan p = two_level_plan(B, K, r, dt);
     size_t need = lbi_scan_backward_workspace_bytes_ex(B, K, r, dt, use);
     if (scratch && need > kScratchBytes) {
         if (use == LBI_ALGO_TWO_LEVEL) {
-            p = two_level_plan(B, K, r, true);
+            p = two_level_plan(B, K, r, dt, true);
             need = p.bytes;
         }
         if (need > kScratchBytes)
@@ -788,13 +857,18 @@ size_t lbi_scan_backward_workspace_bytes_ex(int64_t B, int64_t K, int32_t r, lbi
         return 0;
     if (!valid_algo(algo))
         return 0;
-    const lbi_algo use = resolve_algo(algo, B, K, r, dt, LBI_MATH_DEFAULT);
-    if (use == LBI_ALGO_TREE)
+    // AUTO: enough for the choice in every arithmetic
+    if (algo == LBI_ALGO_AUTO)
+        return two_level_by_size(B, K, r, dt, true) || two_level_by_size(B, K, r, dt, false) ||
+                       two_level_by_model(B, K, r, dt)
+                   ? two_level_plan(B, K, r, dt).bytes
+                   : 0;
+    if (algo == LBI_ALGO_TREE)
         // (sized for an affine term: enough with or without b)
         return r <= 64 && tree_possible(B, K, r) ? tree_plan(B, K, r, true).bytes : 0;
-    if (use != LBI_ALGO_TWO_LEVEL || !two_level_possible(B, K))
+    if (algo != LBI_ALGO_TWO_LEVEL || !two_level_possible(B, K))
         return 0;
-    return two_level_plan(B, K, r).bytes;
+    return two_level_plan(B, K, r, dt).bytes;
 }
 
 size_t lbi_scan_backward_workspace_bytes(int64_t B, int64_t K, int32_t r, lbi_dtype dt)

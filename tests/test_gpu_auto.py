@@ -1,0 +1,68 @@
+"""What LBI_ALGO_AUTO runs where its choice depends on the number of chains
+(needs a GPU): the two-level scan with the workspace that the query asks for,
+and, where that workspace is an offer (the cost model of the other arithmetics
+would take the chain scan), the chain scan without it; each bit for bit as the
+algorithm named by itself, and all of them against the oracle.
+
+Tolerance: the parity bars, 1e-5 (fp32) and 1e-3 (bf16 with the hi + lo
+feedback, which leaves about 1e-5).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_09204_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+TOL = {"f32": 1e-5, "bf16": 1e-3}
+
+
+def _err(lam, x):
+    return oracle.rel_frobenius(lam.cpu().numpy().astype(np.float64),
+                                oracle.recurrence(x.A, x.b, x.lamK))
+
+
+CHAIN, WAVE, TWO = (binding.LBI_ALGO_CHAIN, binding.LBI_ALGO_CHAIN_WAVE,
+                    binding.LBI_ALGO_TWO_LEVEL)
+# (B, K, r, dtype, affine, AUTO's algorithm, the chain scan without workspace or
+# None where the workspace is required)
+SHAPES = [(150, 100, 64, "bf16", True, TWO, CHAIN), (150, 70, 64, "bf16", False, CHAIN, CHAIN),
+          (256, 130, 32, "bf16", True, TWO, WAVE), (400, 100, 32, "bf16", False, WAVE, WAVE),
+          (260, 70, 32, "f32", True, TWO, CHAIN), (90, 33, 16, "bf16", True, WAVE, WAVE),
+          (90, 100, 64, "f32", False, TWO, None), (3, 200, 64, "f32", True, TWO, None),
+          (20, 37, 128, "f32", True, TWO, None)]
+
+
+@pytest.mark.parametrize("B,K,r,dtype,affine,algo,less", SHAPES)
+def test_auto_with_and_without_workspace(B, K, r, dtype, affine, algo, less):
+    x = synth.random_chain(B, K, r, dtype=dtype, seed=91)
+    if not affine:
+        x.b = None
+    g = x.to(DEV)
+    lam = binding.lbi_scan_backward(g.A, g.b, g.lamK)
+    assert _err(lam, x) <= TOL[dtype]
+    assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=algo))
+    assert _err(binding.lbi_scan_backward_noalloc(g.A, g.b, g.lamK), x) <= TOL[dtype]
+    little = torch.empty((16,), dtype=torch.uint8, device=DEV)
+    if less is not None:
+        lam = binding.lbi_scan_backward(g.A, g.b, g.lamK, workspace=little)
+        assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=less))
+    else:
+        with pytest.raises(binding.LbiError) as e:
+            binding.lbi_scan_backward(g.A, g.b, g.lamK, workspace=little)
+        assert e.value.status == 5  # LBI_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("K,r,most", [(13, 16, 512), (12, 32, 512), (11, 32, 256)])
+def test_auto_tree_batch_limit(K, r, most):
+    """fp32 chains within a tree chunk: one tree launch up to a number of them."""
+    for B in (most, most + 1):
+        x = synth.random_chain(B, K, r, seed=93)
+        g = x.to(DEV)
+        lam = binding.lbi_scan_backward(g.A, g.b, g.lamK)
+        assert _err(lam, x) <= TOL["f32"]
+        algo = binding.LBI_ALGO_TREE if B == most else binding.LBI_ALGO_CHAIN
+        assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=algo))

@@ -107,7 +107,7 @@ typedef enum {
                              * workgroups and S carry steps; few long chains go
                              * two-level, up to a number of chains that depends
                              * on the dtype and r (about 1350, 500, 126 and 100
-                             * for fp32 at r = 16, 32, 64, 128; 1600, 760, 255
+                             * for fp32 at r = 16, 32, 64, 128; 1350, 530, 222
                              * and 104 for bf16, without b 1700, 500, 190 and
                              * 104) and is lower for short chains.
                              * K < 16: chain.

@@ -276,21 +276,21 @@ bool two_level_by_model(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
 // 15 (a two-level call costs the host about 15); K = 128: 448 113 / 104, 512 114 /
 // 125; r = 64, K = 64: 96 65 / 67, 80 65 / 59; K = 500: 112 501 / 491, 128 502 /
 // 552; K = 356: 119 407 / 372; r = 128, K = 40: 96 188 / 184, 112 190 /
-// 236.  bf16 without an affine term, where the chain kernels' slot is shorter by
-// a third to a half: r = 16, K = 128: 300 26 / 20, 600 28 / 28; r = 32, K = 128:
-// 200 39 / 33, 300 40 / 41; r = 64, K = 128: 144 81 / 68, 176 81 / 79; with one:
-// r = 16, K = 64: 512 23 / 23; r = 32, K = 500: 640 393 / 337, 768 396 / 404;
-// r = 64, K = 128: 224 121 / 121; K = 400: 240 411 / 381; r = 128 (either), K =
-// 64: 80 195 / 187, 96 196 / 221.  Where the model above chose differently it was
-// off by up to 2.8 times (bf16, r = 32, 256 chains of 500 slots: 369 us in the
-// chain scan, 135 here).
+// 236.  bf16 without an affine term, where the chain kernels' slot is shorter by up to
+// a third: r = 16, K = 128: 300 26 / 20, 600 28 / 28; r = 32, K = 128: 200 39 / 33,
+// 300 40 / 41; r = 64, K = 128: 144 81 / 68, 176 81 / 79; with one: r = 16, K = 90:
+// 300 23 / 20, 600 27 / 29; K = 400: 900 121 / 114, 1200 156 / 156; r = 32, K =
+// 128: 300 56 / 51, 400 56 / 62; K = 400: 500 215 / 215; r = 64, K = 128: 208 112 /
+// 107, 240 114 / 128; r = 128 (either), K = 64: 80 195 / 187, 96 196 / 221.  Where
+// the model above chose differently it was off by up to 2.5 times (bf16, r = 32,
+// 248 chains of 395 slots: 258 us in the chain scan as it then was, 103 here).
 bool two_level_by_size(int64_t B, int64_t K, int32_t r, lbi_dtype dt, bool aff)
 {
     if (K < 16 || !two_level_possible(B, K))
         return false;
     const int i = r == 16 ? 0 : (r == 32 ? 1 : (r == 64 ? 2 : 3));
     static const double f32[4][2] = {{1350, 36}, {500, 22}, {126, 12}, {100, 4}};
-    static const double bf16[4][2] = {{1600, 40}, {760, 24}, {255, 12}, {104, 9}};
+    static const double bf16[4][2] = {{1350, 55}, {530, 36}, {222, 14}, {104, 9}};
     static const double bf16_noaff[4][2] = {{1700, 80}, {500, 45}, {190, 16}, {104, 9}};
     const double *c = dt != LBI_BF16 ? f32[i] : (aff ? bf16[i] : bf16_noaff[i]);
     return (double)B <= c[0] * (1.0 - c[1] / (double)K);

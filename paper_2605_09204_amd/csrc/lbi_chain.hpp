@@ -525,7 +525,9 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
             }
         }
     };
-    // b_j at the row this lane owns after the staging reduce (raw bits)
+    // b_j at the row this lane owns after the staging reduce (raw bits: a bf16
+    // value is moved into the upper half where it is used; beside the load that
+    // shift waited for memory in every slot)
     auto load_b = [&](int64_t j, bool valid, int wr) -> uint32_t {
         if constexpr (AFF) {
             int nrow = R, soff = 0;
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
             if constexpr (G::ESZ == 4)
                 return __builtin_amdgcn_raw_buffer_load_b32(rs, off, soff, 0);
             else
-                return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, soff, 0) << 16;
+                return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, soff, 0);
         } else {
             return 0u;
         }
@@ -617,7 +619,7 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
         if constexpr (AFF) {
             group_reduce<LPR, CPT>(st_part, sgi);
             if (oown)
-                sC[ring(j)][orow] = st_part[0] + bitsf(braw);
+                sC[ring(j)][orow] = st_part[0] + bitsf(G::ESZ == 4 ? braw : braw << 16);
         }
     };
     auto stage = [&](const u4 (&src)[CPT], int buf, uint32_t braw, int64_t j, bool first,

@@ -19,10 +19,17 @@
 //   * P_{K-1} = A_{K-1} I is one pass with an identity B operand (exact).
 //   * Per slot, before the multiply overwrites P_{j+1} in place: the affine
 //     update (each lane's 16 products of its A pieces with c_{j+1}, summed
-//     over the four lane groups), the apply (each lane's P values times
+//     over the four lane groups by lane swaps), the apply (each lane's P values times
 //     lambda_K, summed over the column blocks in the lane, then over the 16
 //     lanes of a row), and the hi/lo split of P_{j+1}.
-//   * c_j sits in a wave-private LDS ring of two vectors.
+//   * c_j sits in a wave-private LDS ring of two vectors, read back as the next
+//     slot's operand as soon as it is written.
+//
+// With few chains a slot is bound by its serial latency (one wave per SIMD hides
+// none): the affine term costs the lane sums and one LDS round trip.  Both passed
+// through LDS shuffles, and the b_j prefetch waited for memory (its shift into
+// place stood beside the load), at 0.67 us per slot of r = 32 against 0.31 without
+// the term; now 0.43 (200 chains of 128 slots: 86 -> 56 us; r = 16 44 -> 32).
 //
 // All HIP code here is built with packed fp32 math disabled.
 
@@ -31,6 +38,19 @@
 
 namespace lbi {
 namespace {
+
+// x summed over lanes l and l ^ 32 in the lower half of the wave, y in the upper.
+__device__ __forceinline__ float add_swap32(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(fbits(x), fbits(y), false, false);
+    return bitsf(r[0]) + bitsf(r[1]);
+}
+// x summed over lanes l and l ^ 16 in the even rows of 16 lanes, y in the odd.
+__device__ __forceinline__ float add_swap16(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(fbits(x), fbits(y), false, false);
+    return bitsf(r[0]) + bitsf(r[1]);
+}
 
 template <int R, bool AFF>
 __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
@@ -41,7 +61,7 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
     constexpr int VV = 4 * NB;         // apply values per lane before the row sums
     constexpr int VFF = VV >= 16 ? VV / 16 : 1;
     constexpr int SH = VV >= 16 ? 0 : (VV == 8 ? 1 : 2);
-    __shared__ __attribute__((aligned(16))) float sc[AFF ? 2 : 1][AFF ? R : 4];
+    __shared__ __attribute__((aligned(16))) float sc[AFF ? 2 : 1][AFF ? R + 64 : 4];
 
     const int lane = threadIdx.x;
     const int g = lane >> 4, li = lane & 15;
@@ -51,9 +71,16 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
     const __bf16 *bv = AFF ? (const __bf16 *)args.b + beta * K * (int64_t)R : nullptr;
     float *lam = args.lam + beta * K * (int64_t)R;
     auto ring = [&](int64_t s) { return (int)((K - 1 - s) & 1); };
+    // the row of c_j that this lane holds after the sum over the lane groups
+    const int crow = 16 * (NB == 4 ? g : (NB == 2 ? g >> 1 : 0)) + li;
+    const bool cown = NB == 4 || (NB == 2 ? (g & 1) == 0 : g == 0);
+    // (lanes with no row write past the vector: no branch)
+    const int cput = cown ? crow : R + lane;
 
     // ---- loads (branch-free: a slot outside the chain reads zeros) ----------
-    // areg[set][I][p][piece]; breg[set]: b_j at row 16 g + li (raw bits << 16)
+    // areg[set][I][p][piece]; breg[set]: b_j at the row of c_j that this lane
+    // sums (raw bits, lanes with no row: zero; moved into place where they are
+    // used, since a shift beside the load waits for it)
     u2 areg[2][NB][NKP][2];
     uint32_t breg[2];
     auto load_slot = [&](u2 (&dst)[NB][NKP][2], uint32_t &bdst, int64_t j) {
@@ -73,8 +100,8 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
         if constexpr (AFF) {
             const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)(bv + (valid ? j : 0) * (int64_t)R), 0, R * 2, kBufferWord3);
-            const int off = valid && g < NB ? (16 * g + li) * 2 : kOutOfRange;
-            bdst = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rb, off, 0, 0) << 16;
+            const int off = valid && cown ? crow * 2 : kOutOfRange;
+            bdst = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rb, off, 0, 0);
         }
     };
     auto a_op = [&](const u2 (&src)[NB][NKP][2], int I, int p) {
@@ -91,6 +118,29 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
     f4 P[NB][NB];  // [I][cb]
 
     // ---- lambda_s = P_s lambda_K + c_s, stored --------------------------------
+    // c_s as the next slot's operand (columns 32 p + 16 h + 4 g ..) and at the
+    // rows that this lane stores; read right after c_s is written, a slot's work
+    // before either is used
+    f4 cop[AFF ? NKP : 1][2];
+    float cst[AFF ? VFF : 1];
+    auto fetch_c = [&](int64_t s) {
+        if constexpr (AFF) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int p = 0; p < NKP; ++p)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (32 * p + 16 * h < R)
+                        cop[p][h] = *(const f4 *)&sc[ring(s)][32 * p + 16 * h + 4 * g];
+#pragma unroll
+            for (int e = 0; e < VFF; ++e) {
+                const int idx = (li >> SH) * VFF + e;
+                cst[e] = sc[ring(s)][16 * (idx >> 2) + 4 * g + (idx & 3)];
+            }
+        }
+    };
     auto apply = [&](int64_t s) {
         float q[VV];
 #pragma unroll
@@ -113,7 +163,7 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
             const int row = 16 * (idx >> 2) + 4 * g + (idx & 3);
             float val = q[e];
             if constexpr (AFF)
-                val += sc[ring(s)][row];
+                val += cst[e];
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), rs,
                                                   mine ? row * 4 : kOutOfRange, 0, 0);
         }
@@ -145,8 +195,8 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
                                                                        P[I][cb], 0, 0, 0);
             }
         if constexpr (AFF) {
-            if (g < NB)
-                sc[ring(K - 1)][16 * g + li] = bitsf(breg[0]);
+            sc[ring(K - 1)][cput] = bitsf(breg[0] << 16);
+            fetch_c(K - 1);
         }
     }
     load_slot(areg[0], breg[0], K - 3);
@@ -164,7 +214,13 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
             u2 (&aj)[NB][NKP][2] = cur ? areg[1] : areg[0];
             uint32_t &bj = cur ? breg[1] : breg[0];
 
-            // c_j = A_j c_{j+1} + b_j
+            // lambda_{j+1} from P_{j+1} and c_{j+1}
+            apply(j + 1);
+
+            // c_j = A_j c_{j+1} + b_j: every lane group holds a quarter of each
+            // row's k range; the sum over the four leaves lane (g, li) the row
+            // crow.  A lane swap by vector instructions instead of a shuffle
+            // through LDS: one wave per SIMD hides no LDS latency.
             if constexpr (AFF) {
                 float part[NB];
 #pragma unroll
@@ -174,9 +230,8 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
                 for (int p = 0; p < NKP; ++p)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const int col = 32 * p + 16 * h + 4 * g;
-                        if (col < R) {
-                            const f4 cv = *(const f4 *)&sc[ring(j + 1)][col];
+                        if (32 * p + 16 * h < R) {
+                            const f4 cv = cop[p][h];
 #pragma unroll
                             for (int I = 0; I < NB; ++I) {
                                 const u2 w = aj[I][p][h];
@@ -185,25 +240,16 @@ __global__ __launch_bounds__(64) void scan_wave_kernel(const ScanArgs args)
                             }
                         }
                     }
-                // every lane group holds a quarter of each row's k range: sum
-                // over the four groups, then lane (g, li) keeps row 16 g + li
-                float mine = 0.0f;
-#pragma unroll
-                for (int I = 0; I < NB; ++I) {
-                    part[I] += __shfl_xor(part[I], 16);
-                    part[I] += __shfl_xor(part[I], 32);
-                    if (g == I)
-                        mine = part[I];
+                float sum;
+                if constexpr (NB == 4)
+                    sum = add_swap16(add_swap32(part[0], part[2]), add_swap32(part[1], part[3]));
+                else {
+                    const float half = add_swap32(part[0], part[NB - 1]);
+                    sum = add_swap16(half, half);
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                if (g < NB)
-                    sc[ring(j)][16 * g + li] = mine + bitsf(bj);
+                sc[ring(j)][cput] = sum + bitsf(bj << 16);
+                fetch_c(j);
             }
-
-            // lambda_{j+1} from P_{j+1}
-            apply(j + 1);
 
             // P_j = A_j (P_{j+1} as bf16 hi + lo), in place
             bf16x8 bh[NKP][NB], bl[NKP][NB];

@@ -66,3 +66,24 @@ def test_auto_tree_batch_limit(K, r, most):
         assert _err(lam, x) <= TOL["f32"]
         algo = binding.LBI_ALGO_TREE if B == most else binding.LBI_ALGO_CHAIN
         assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=algo))
+
+
+@pytest.mark.parametrize("algo", ["CHAIN_WAVE", "CHAIN"])
+@pytest.mark.parametrize("r", [16, 32, 64])
+def test_bf16_affine_exact(algo, r):
+    """Signed permutation matrices and small integers: every value that the scan
+    forms is an integer below 2^8, so the affine term's sums over lanes have to
+    give the oracle's adjoints exactly, from the shortest chains on."""
+    gen = torch.Generator().manual_seed(95)
+    for B, K in ((3, 1), (3, 2), (5, 3), (2, 4), (7, 40)):
+        A = torch.zeros((B, K, r, r))
+        for i in range(B):
+            for j in range(K):
+                sign = 1 - 2 * torch.randint(0, 2, (r,), generator=gen)
+                A[i, j, torch.arange(r), torch.randperm(r, generator=gen)] = sign.float()
+        b = torch.randint(-3, 4, (B, K, r), generator=gen).float()
+        lk = torch.randint(-3, 4, (B, r), generator=gen).float()
+        A, b, lk = (t.bfloat16() for t in (A, b, lk))
+        lam = binding.lbi_scan_backward_ex(A.to(DEV), b.to(DEV), lk.to(DEV),
+                                           algo=getattr(binding, "LBI_ALGO_" + algo))
+        assert np.array_equal(lam.cpu().numpy(), oracle.recurrence(A, b, lk)), (B, K)

@@ -26,6 +26,18 @@
 //     ahead (two slots with a widths hint; 16-byte buffer loads), split it, form c_j from the same registers
 //     and store lambda.  Neither role's registers are live in the other's loop.
 //
+//   * Range.  Three bf16 parts hold an fp32 value to its last bit from 2^-110 up
+//     to where it rounds to an infinity in bf16 (about 3.396e38); an infinity, or
+//     a value past that, leaves NaN parts, and a smaller one keeps only its bits
+//     from 2^-133 up.  A segment in which that can show is done again from its
+//     end on the fp32 matrix cores (exact_pass), so the kernel's results are those
+//     of float32 products over float32's whole range.  What shows it, with lambda:
+//     a row of P_s lambda_K that is not finite, or not zero and below 2^-96 of
+//     the largest entry of lambda_K or of the same row at s + 1 (what was lost is
+//     otherwise below 2^-29 of every row).  With composites, the largest magnitude
+//     of a quarter column of P_s (a lane's): 2^126 or more, or not zero and below 2^-96, or below 2^-96
+//     of the quarter's at s + 1; and a NaN in the segment's last composite.
+//
 // What bounds it: a slot is 384 MFMAs of 16 cycles per SIMD (2.6 us at the top
 // clock), with about 500 VALU instructions of the matrix wave beside them; with
 // every CU busy the MFMAs run at 1.0-1.2 PFLOP/s of bf16 products, where a
@@ -57,6 +69,9 @@ __device__ __forceinline__ int panel_pos(int r, int q)
     return line * 128 + ((r & 3) * 4 + (q ^ (line & 3))) * 8;
 }
 
+// The range checks' bounds (see Range above).
+constexpr float kShow = 0x1p-96f, kFull = 0x1p126f;
+
 // The three parts of a lane's B operand: 4 rows of two row blocks of P.
 struct Parts {
     bf16x8 h, m, l;
@@ -68,6 +83,15 @@ __device__ __forceinline__ Parts split_rows(const f4 &a, const f4 &b)
     return {__builtin_bit_cast(bf16x8, u4{s0.h, s1.h, s2.h, s3.h}),
             __builtin_bit_cast(bf16x8, u4{s0.m, s1.m, s2.m, s3.m}),
             __builtin_bit_cast(bf16x8, u4{s0.l, s1.l, s2.l, s3.l})};
+}
+
+// The larger of m and the magnitudes in a column's rows of two row blocks.
+__device__ __forceinline__ float column_top(float m, const f4 &a, const f4 &b)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        m = fmaxf(fmaxf(m, fabsf(a[v])), fabsf(b[v]));
+    return m;
 }
 
 // acc += A panel x b for the first NR row blocks and NT column blocks of a wave;
@@ -101,6 +125,212 @@ __device__ __forceinline__ void panel_product(f4 (&acc)[8][2], const __bf16 *pan
     }
 }
 
+// ---- a segment again, on the fp32 matrix cores (see Range above) ----------------
+// One barrier per slot: the matrix waves hold P_s and form P_{s-1} = A_{s-1} P_s with
+// their operands straight from global memory, the staging waves c_{s-1}; lambda is
+// stored again from slot worst on, composites from the segment's end, and what is
+// published counts on from npub publications.  c_s is in entry s & 1 of sC, the
+// apply's sums of slot s in entry s & 1 of sPart.  The arguments and the thread's
+// index are read anew, so that the loops before keep nothing for this in registers.
+template <bool AFF, int HINT, int OUT>
+__device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*sC)[kR],
+                                           float (*sPart)[4][kR])
+{
+    typedef const __attribute__((address_space(4))) ScanArgs *ArgsPtr;
+    ArgsPtr pa = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(pa));
+    const __attribute__((address_space(4))) ScanArgs &args = *pa;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    constexpr bool compact = HINT == kHintCompact;
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, li = lane & 15, st = tid - 256;
+    const int64_t beta = blockIdx.x / args.S;
+    const int64_t s0 = (int64_t)(blockIdx.x % args.S) * args.L;
+    const int64_t K = args.K - s0 < args.L ? args.K - s0 : args.L;
+    const int64_t first = beta * args.K + s0;
+    const int64_t cslot = args.agg_only ? (int64_t)blockIdx.x : first;
+    const float *A = (const float *)args.A +
+                     (compact ? beta * (int64_t)args.totalA : first * (int64_t)(kR * kR));
+    const float *bv = (const float *)args.b +
+                      (compact ? beta * (int64_t)args.totalR : first * (int64_t)kR);
+    auto blocks = [&](int64_t s) {
+        return !HINT ? 8
+               : s < 0 ? 0
+                       : (int)((args.wcode[(s0 + s) >> 3] >> (((s0 + s) & 7) * 4)) & 15u);
+    };
+    auto pitch = [](int wc) { return compact ? 16 * wc : kR; };
+    const int wK = blocks(K);
+    int32_t offA = args.totalA, offR = args.totalR;  // (compact storage)
+    if (compact) {
+        offA -= 16 * blocks(K - 1) * pitch(wK);
+        offR -= 16 * blocks(K - 1);
+    }
+    f4 P[8][2];
+    float lk[2] = {0.0f, 0.0f};
+    if (w < 4) {
+        const int nrow = 16 * blocks(K - 1), ld = pitch(wK);
+        const float *T = A + (compact ? (int64_t)offA : (K - 1) * (int64_t)(kR * kR));
+#pragma unroll
+        for (int I = 0; I < 8; ++I)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int row = 16 * I + 4 * g + v, col = 16 * (w + 4 * t) + li;
+                    P[I][t][v] = row < nrow && col < ld ? T[row * ld + col] : 0.0f;
+                }
+        if constexpr (OUT == kOutLambda) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int idx = 16 * (w + 4 * t) + li, rK = compact ? 16 * wK : kR;
+                lk[t] = idx >= rK     ? 0.0f
+                        : args.lamSeg ? args.lamSeg[(int64_t)blockIdx.x * kR + idx]
+                                      : ((const float *)args.lamK)[beta * rK + idx];
+            }
+        }
+    } else if (st < kR) {
+        const int nrow = compact ? 16 * blocks(K - 1) : kR;
+        const int64_t at = compact ? (int64_t)offR : (K - 1) * (int64_t)kR;
+        sC[(K - 1) & 1][st] = AFF && st < nrow ? bv[at + st] : 0.0f;
+    }
+    int32_t left = args.pchunk;
+    int64_t points = 0, pub = -1;  // publications up to this slot; the pending one
+    auto publish = [&]() {
+        if (pub >= 0 && st == 0 && points > npub) {
+            __hip_atomic_fetch_max(&args.progress[beta], (uint32_t)pub, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+            if (args.pub_clock)
+                args.pub_clock[beta * args.npub + npub] = __builtin_amdgcn_s_memrealtime();
+            ++npub;
+        }
+        pub = -1;
+    };
+#pragma unroll 1
+    for (int64_t s = K - 1; s >= 0; --s) {
+        // A_{s-1}: nr row and wc column blocks
+        const int wc = blocks(s), nr = blocks(s - 1), ld = pitch(wc);
+        if (w < 4) {
+            if constexpr (OUT == kOutLambda) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float q[16];
+#pragma unroll
+                    for (int I = 0; I < 4; ++I)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            q[4 * I + v] = P[4 * h + I][0][v] * lk[0] + P[4 * h + I][1][v] * lk[1];
+                    group_reduce<16, 16>(q, li);
+                    sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0];
+                }
+            } else if (!args.agg_only || s == 0) {
+                float *T = args.Pout + (cslot + s) * (int64_t)(kR * kR) + 16 * w + li;
+#pragma unroll
+                for (int I = 0; I < 8; ++I)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            T[(16 * I + 4 * g + v) * kR + 64 * t] = P[I][t][v];
+            }
+        }
+        __syncthreads();
+        if (compact && s > 0)
+            offA -= 16 * nr * ld;
+        const float *T = A + (compact ? (int64_t)offA : (s - 1) * (int64_t)(kR * kR));
+        if (w >= 4) {
+            publish();
+            const float c = sC[s & 1][st & (kR - 1)];
+            if (OUT == kOutLambda && st < (compact ? 16 * wc : kR) && s <= worst)
+                args.lam[(compact ? beta * (int64_t)args.totalR + offR
+                                  : (first + s) * (int64_t)kR) + st] =
+                    ((sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
+                     (sPart[s & 1][2][st] + sPart[s & 1][3][st])) +
+                    c;
+            if (OUT == kOutComposite && st < kR && args.cout && (!args.agg_only || s == 0))
+                args.cout[(cslot + s) * kR + st] = c;
+            if (OUT == kOutLambda && args.progress && (--left == 0 || s == 0)) {
+                pub = K - s;
+                ++points;
+                left = args.pchunk;
+                if (st < kR)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            }
+            if (compact)
+                offR -= 16 * nr;
+            // two threads a row, half of its columns each
+            const int row = st >> 1, nrow = compact ? 16 * nr : kR;
+            const int ncol = (HINT ? 16 * wc : kR) / 2, col0 = (st & 1) * ncol;
+            float x = 0.0f;
+            if (AFF && s > 0 && row < nrow)
+#pragma unroll 1
+                for (int i = col0; i < col0 + ncol; i += 4) {
+                    const f4 a = *(const f4 *)&T[row * ld + i], y = *(const f4 *)&sC[s & 1][i];
+                    x += a[0] * y[0] + a[1] * y[1] + a[2] * y[2] + a[3] * y[3];
+                }
+            x += xchg<1>(x);
+            if (AFF && s > 0 && row < nrow)
+                x += bv[(compact ? (int64_t)offR : (s - 1) * (int64_t)kR) + row];
+            if (s > 0 && (st & 1) == 0)
+                sC[(s - 1) & 1][row] = x;
+        } else if (s > 0) {
+            // element v of row block k of P is the B operand of an MFMA over the rows
+            // 16 k + 4 g + v; A's columns past wc blocks, and rows past nr, read as
+            // zero (nothing of P is at those columns)
+            const int voff = (li * ld + 4 * g) * 4;
+            const uint64_t base = (uint64_t)(uintptr_t)T;
+            void *const tile = (void *)(uintptr_t)(
+                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
+                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32);
+            auto load = [&](u4(&a)[8], int k) {
+                const int bytes = !HINT ? kTileBytes : k < wc ? 16 * nr * ld * 4 : 0;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    tile, 0, __builtin_amdgcn_readfirstlane(bytes), kBufferWord3);
+#pragma unroll
+                for (int I = 0; I < 8; ++I)
+                    a[I] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rs, voff, __builtin_amdgcn_readfirstlane((16 * I * ld + 16 * k) * 4), 0);
+            };
+            f4 Q[8][2];
+#pragma unroll
+            for (int I = 0; I < 8; ++I)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    Q[I][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            u4 a[2][8];
+            load(a[0], 0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (k < 7)
+                    load(a[(k + 1) & 1], k + 1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int I = 0; I < 8; ++I)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            Q[I][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                bitsf(a[k & 1][I][v]), P[k][t][v], Q[I][t], 0, 0, 0);
+                // (two steps' loads at a time: more do not fit the registers)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // (with a hint, rows and columns that are not there stay zero: no zero
+            // times an infinity)
+#pragma unroll
+            for (int I = 0; I < 8; ++I)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    P[I][t] = !HINT || (I < nr && w + 4 * t < wK) ? Q[I][t]
+                                                                  : f4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+    if (OUT == kOutLambda && args.progress) {
+        __syncthreads();
+        if (w >= 4)
+            publish();
+    }
+}
+
 template <bool AFF, int HINT, int OUT>
 __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 {
@@ -109,6 +339,13 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     // entry s & 1
     __shared__ __attribute__((aligned(16))) float sC[4][kR];
     __shared__ __attribute__((aligned(16))) float sPart[OUT == kOutLambda ? 2 : 1][4][kR];
+    // range: the latest slot whose results show a loss (-1: none).  Entry j & 1 holds
+    // j when that was found in the loop's slot j; all waves read it in the next slot
+    // and end the loop with that one (with a hint they go on to the last slot: another
+    // way out of those loops costs them registers that they do not have)
+    __shared__ int32_t sWorst, sLost[2];
+    __shared__ int64_t sNpub;  // (streaming) publications made
+    __shared__ float sTop[2];  // the largest entry of lambda_K in each half
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -144,18 +381,28 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     auto panels = [](int wc) { return HINT ? (wc + 1) >> 1 : kNP; };
     auto pitch = [](int wc) { return compact ? 16 * wc : kR; };
 
+    // entry idx of the segment end's lambda
+    auto lambda_end = [&](int idx) {
+        const int rK = compact ? 16 * blocks(K) : kR;
+        return idx >= rK     ? 0.0f
+               : args.lamSeg ? args.lamSeg[(int64_t)blockIdx.x * kR + idx]
+                             : ((const float *)args.lamK)[beta * rK + idx];
+    };
+    if (tid < 2)
+        sLost[tid] = -1;
+    if (tid == 2)
+        sWorst = -1;
+    if (tid == 3)
+        sNpub = 0;
+    bool again = false;  // the slot loop ended early: the segment is done again
+
     if (w < 4) {
         // ---- matrix waves ---------------------------------------------------
         float lk[2] = {0.0f, 0.0f};
         if constexpr (OUT == kOutLambda) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int idx = 16 * (w + 4 * t) + li;
-                const int rK = compact ? 16 * blocks(K) : kR;
-                lk[t] = idx >= rK     ? 0.0f
-                        : args.lamSeg ? args.lamSeg[(int64_t)blockIdx.x * kR + idx]
-                                      : ((const float *)args.lamK)[beta * rK + idx];
-            }
+            for (int t = 0; t < 2; ++t)
+                lk[t] = lambda_end(16 * (w + 4 * t) + li);
         }
         float *Pout = OUT == kOutComposite ? args.Pout + cslot * (int64_t)(kR * kR) : nullptr;
         // P_s, row blocks i0 .. i1 - 1, to global memory
@@ -204,11 +451,33 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         // (columns past the segment end's width are zero)
         const int nt = HINT && 4 + w >= blocks(K) ? 1 : 2;
         int buf = 0;  // the panel's LDS buffer
+        // (composites) the largest magnitudes in this lane's rows of P's two columns, of
+        // the row blocks split so far, and of a slot later
+        float top[2] = {column_top(0.0f, P[0][0], P[1][0]), column_top(0.0f, P[0][1], P[1][1])};
+        float before[2] = {0.0f, 0.0f};
         __syncthreads();
+        // the range check of the P whose row blocks are all in top, in the loop's slot j
+        // (-1: past it).  A NaN, which top leaves out, is in every row of every composite
+        // after it: the last slot's check finds it.
+        auto check_columns = [&](int64_t j, bool bad) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float c = top[t];
+                bad |= c >= kFull || (c > 0.0f && c < fmaxf(kShow, before[t] * kShow));
+                before[t] = c;
+            }
+            if (__builtin_expect(bad, 0)) {
+                sWorst = 0;
+                if (!HINT && j >= 0)
+                    sLost[j & 1] = (int32_t)j;
+            }
+        };
         // P_j (Pn) from P_{j+1} (P); b holds the split of P's first two row
         // blocks on entry, of Pn's on return
         int wr = blocks(K - 1), wnext = blocks(K - 2);
+        // (true: the segment is to be done again)
         auto slot = [&](const f4(&P)[8][2], f4(&Pn)[8][2], int64_t j) {
+            int32_t lost = 0;
             [[maybe_unused]] const int np = panels(wr), nr = wnext;
             wr = wnext;
             wnext = blocks(j - 1);
@@ -224,6 +493,8 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 __syncthreads();
                 const __bf16 *pan = sA[HINT ? buf : p & 1] + apos;
                 buf ^= 1;
+                if (!HINT && p == 0)
+                    lost = sLost[(j + 1) & 1];
                 Parts bn[2] = {b[0], b[1]};
                 if constexpr (kShapes) {
                     // (blocks past nr hold zeros)
@@ -245,8 +516,11 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 }
                 if (p < kNP - 1) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < 2; ++t) {
                         bn[t] = split_rows(P[2 * p + 2][t], P[2 * p + 3][t]);
+                        if constexpr (OUT == kOutComposite)
+                            top[t] = column_top(top[t], P[2 * p + 2][t], P[2 * p + 3][t]);
+                    }
                 }
                 if constexpr (OUT == kOutLambda) {
                     // (a hinted slot may have one panel only)
@@ -263,9 +537,15 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 b[0] = bn[0];
                 b[1] = bn[1];
             }
+            if constexpr (OUT == kOutComposite)
+                check_columns(j, false);
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t) {
                 b[t] = split_rows(Pn[0][t], Pn[1][t]);
+                if constexpr (OUT == kOutComposite)
+                    top[t] = column_top(0.0f, Pn[0][t], Pn[1][t]);
+            }
+            return !HINT && __builtin_amdgcn_readfirstlane(lost) == (int32_t)(j + 1);
         };
         auto last = [&](const f4(&X)[8][2]) {
             __syncthreads();
@@ -274,6 +554,17 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 apply(X, 0, 1);
             } else {
                 store_rows(X, 0, 0, 8);
+                bool bad = false;
+#pragma unroll
+                for (int I = 0; I < 8; ++I)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        top[t] = column_top(top[t], X[I][t], X[I][t]);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            bad |= X[I][t][v] != X[I][t][v];
+                    }
+                check_columns(-1, bad);
             }
         };
         // (the barrier: lambda_2's sums, in slot 0's entry, may still be read in
@@ -293,19 +584,26 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         } else {
             // (two slots per iteration, so that P and Q swap without copies)
             for (; j >= 1; j -= 2) {
-                slot(P, Q, j);
-                slot(Q, P, j - 1);
+                again = slot(P, Q, j);
+                if (again)
+                    break;
+                again = slot(Q, P, j - 1);
+                if (again)
+                    break;
             }
-            if (j == 0) {
-                slot(P, Q, 0);
-                last(Q);
-            } else {
+            if (!again && j == 0) {
+                again = slot(P, Q, 0);
+                if (!again)
+                    last(Q);
+            } else if (!again) {
                 last(P);
             }
         }
-        __syncthreads();
-        if (args.progress)
+        if (!again) {
             __syncthreads();
+            if (args.progress)
+                __syncthreads();
+        }
     } else {
         // ---- staging waves --------------------------------------------------
         // chunk i of this thread: row i * 32 + srow, columns 4 sgi .. + 3 of the
@@ -407,7 +705,9 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         int32_t pub_left = args.pchunk;
         int64_t pub = -1;  // slots final once the next barrier is passed, or -1
         int64_t npub = 0;  // publications so far
-        auto finish = [&](int64_t s, int wr) {
+        float show = 0.0f, row = 0.0f;  // of the range check: from lambda_K, from slot s + 1
+        // (j: the loop's slot, or -1 past it)
+        auto finish = [&](int64_t s, int wr, int64_t j) {
             const int nrow = compact ? 16 * wr : kR;
             if (compact)
                 curL -= nrow;
@@ -416,10 +716,17 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 if constexpr (OUT == kOutLambda) {
                     float *lam = args.lam + (compact ? beta * (int64_t)args.totalR + curL
                                                      : (first + s) * (int64_t)kR);
+                    const float p = (sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
+                                    (sPart[s & 1][2][st] + sPart[s & 1][3][st]);
                     if (st < nrow)
-                        lam[st] = ((sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
-                                   (sPart[s & 1][2][st] + sPart[s & 1][3][st])) +
-                                  c;
+                        lam[st] = p + c;
+                    const float a = fabsf(p);
+                    if (__builtin_expect(!(a < kFull) || (a > 0.0f && a < fmaxf(show, row)), 0)) {
+                        atomicMax(&sWorst, (int32_t)s);
+                        if (!HINT && j >= 0)
+                            sLost[j & 1] = (int32_t)j;
+                    }
+                    row = a * kShow;
                 } else if (args.cout && (!args.agg_only || s == 0)) {
                     args.cout[(cslot + s) * kR + st] = c;
                 }
@@ -442,13 +749,14 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         // XCD's L2) and records the clock
         auto publish = [&]() {
             if constexpr (OUT == kOutLambda) {
-                if (pub >= 0 && st == 0) {
+                // (nothing from the slot that shows a loss on)
+                if (pub >= 0 && st == 0 && sWorst < 0) {
                     __hip_atomic_fetch_max(&args.progress[beta], (uint32_t)pub, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_SYSTEM);
                     if (args.pub_clock)
                         args.pub_clock[beta * args.npub + npub] = __builtin_amdgcn_s_memrealtime();
+                    sNpub = ++npub;
                 }
-                npub += pub >= 0 ? 1 : 0;
                 pub = -1;
             }
         };
@@ -470,7 +778,19 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         if (compact)
             curB -= 16 * blocks(K - 1);
         load_b(K - 2, blocks(K - 2));
+        if constexpr (OUT == kOutLambda) {
+            if (st < kR) {
+                float top = fabsf(lambda_end(st));
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1)
+                    top = fmaxf(top, __shfl_xor(top, o));
+                if (lane == 0)
+                    sTop[st >> 6] = top;
+            }
+        }
         __syncthreads();
+        if constexpr (OUT == kOutLambda)
+            show = fmaxf(sTop[0], sTop[1]) * kShow;
         // wq[d]: blocks of slot j + 2 - d in the slot loop below
         int wq[NPF + 4];
 #pragma unroll
@@ -484,41 +804,51 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         auto slot = [&](u4(&cur)[kNP][4], u4(&next)[kNP][4], int64_t j) {
             const int np = panels(wq[1]);
             const int wnext = blocks(j - 2 - NPF);
+            int32_t lost = 0;
 #pragma unroll
             for (int p = 0; p < kNP; ++p) {
                 if (HINT && p >= np)
                     break;
                 __syncthreads();
                 publish();
+                if (!HINT && p == 0)
+                    lost = sLost[(j + 1) & 1];
                 if (p + 1 < kNP && p + 1 < np)
                     stage(cur, p + 1 < kNP ? p + 1 : 0, j, wq + 1);
                 else
                     stage(next, 0, j - 1, wq + 2);
                 if (p == 0 && j + 2 < K)
-                    finish(j + 2, wq[0]);
+                    finish(j + 2, wq[0], j);
             }
 #pragma unroll
             for (int d = 0; d < NPF + 3; ++d)
                 wq[d] = wq[d + 1];
             wq[NPF + 3] = wnext;
+            return !HINT && __builtin_amdgcn_readfirstlane(lost) == (int32_t)(j + 1);
         };
-        for (int64_t j = K - 2; j >= 0; j -= NPF) {
-            slot(pf[0], pf[NPF - 1], j);
+        for (int64_t j = K - 2; j >= 0 && !again; j -= NPF) {
+            again = slot(pf[0], pf[NPF - 1], j);
             if (NPF == 2 && j >= 1)
                 slot(pf[NPF - 1], pf[0], j - 1);
         }
-        __syncthreads();
-        publish();
-        if (K >= 2)
-            finish(1, blocks(1));
-        __syncthreads();
-        publish();
-        finish(0, blocks(0));
-        if (args.progress) {
+        if (!again) {
             __syncthreads();
             publish();
+            if (K >= 2)
+                finish(1, blocks(1), -1);
+            __syncthreads();
+            publish();
+            finish(0, blocks(0), -1);
+            if (args.progress) {
+                __syncthreads();
+                publish();
+            }
         }
     }
+
+    __syncthreads();
+    if (__builtin_expect(sWorst >= 0, 0))
+        exact_pass<AFF, HINT, OUT>(sWorst, sNpub, &sC[0], &sPart[0]);
 }
 
 }  // namespace

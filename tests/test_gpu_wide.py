@@ -2,7 +2,7 @@
 the oracle, through the C-ABI (needs a GPU): chains of one to a few slots
 (prologue, both parities of its slot loop, the last slot), hinted slots of one
 to four panels and one to eight row blocks in every order, compact storage,
-segments (two-level) and streaming.
+segments (two-level) and streaming; values that the split cannot hold.
 
 Tolerance: relative Frobenius 1e-5, the fp32 bar; a lost partial product of
 the split shows at 2^-16 = 1.5e-5 per slot and above.  Hinted, compact and
@@ -67,3 +67,93 @@ def test_wide_segments_and_products(B, K):
     Pr, cr = oracle.suffix_composites(x.A[:3], x.b[:3])
     assert oracle.rel_frobenius(P.cpu().numpy().astype(np.float64), Pr) <= TOL
     assert oracle.rel_frobenius(c.cpu().numpy().astype(np.float64), cr) <= TOL
+
+
+# A chain's tiles times 2^-e (per slot), and a value planted at row 5, column 7 of a
+# tile: what the three-part split cannot hold (infinities, NaN, magnitudes that round
+# to an infinity in bf16, values that keep bits below 2^-133).  The finite results
+# stay above 2^-116, so that float32 itself keeps all its bits.
+RANGE = {"inf": (0, {3: float("inf")}), "inf at the end": (0, {10: float("inf")}),
+         "both infinities": (0, {2: float("-inf"), 4: float("inf")}), "nan": (0, {3: float("nan")}),
+         "huge": (5, {3: 3.4e38}), "huge at the end": (5, {10: -3.4e38}), "decaying": (10, {}),
+         "small at the start": ([112] + [0] * 10, {}), "small at the end": ([0] * 10 + [112], {}),
+         "grown, then small": ([112] + [-10] * 10, {})}
+
+
+@pytest.mark.parametrize("cycle", [None, (32, 64, 128), (128, 16)], ids=["full", "mixed", "thin"])
+@pytest.mark.parametrize("affine", [True, False])
+@pytest.mark.parametrize("what", list(RANGE))
+def test_wide_whole_float32_range(what, affine, cycle):
+    """Over the whole range of float32 the default arithmetic gives what the fp32
+    matrix cores give: infinities and NaN in the same places (the affine terms are
+    finite and change neither; the padding of a hinted call is left out), and the
+    finite entries at the parity bar, slot by slot (a slot's norm may be 1e-30 of
+    another's), in every form of the launch.  A second, ordinary chain beside the
+    planted one keeps its results.
+
+    A finite planted value makes a row of its slot out of one entry of the adjoint
+    after it, so that row's relative error is that entry's: the bar times the norm of
+    the slot after it over that entry."""
+    K = 11
+    shift, planted = RANGE[what]
+    shift = torch.tensor([shift] * K if isinstance(shift, int) else shift)
+    widths = synth.cyclic_widths(K, cycle or (128,))
+    x = synth.random_chain(2, K, 128, seed=97, widths=widths, affine=affine)
+    x.A[0] = torch.ldexp(x.A[0], -shift[:, None, None])
+    if affine:  # as large as the adjoint beside it
+        x.b[0] = torch.ldexp(x.b[0], -shift.flip(0).cumsum(0).flip(0)[:, None])
+    tol = TOL
+    finite = [j for j, v in planted.items() if np.isfinite(v)]
+    if finite:
+        want = oracle.recurrence(x.A, x.b, x.lamK)
+        after = np.concatenate([want, x.lamK.double().numpy()[:, None]], axis=1)[0, finite[0] + 1]
+        tol = TOL * float(np.linalg.norm(after) / abs(after[7]))
+    for j, value in planted.items():
+        x.A[0, j, 5, 7] = value
+    g = x.to(DEV)
+    hint = None if cycle is None else list(widths)
+    live = torch.arange(128) < torch.tensor(widths[:K])[:, None]
+
+    def run(algo, math=binding.LBI_MATH_DEFAULT, b=g.b):
+        return binding.lbi_scan_backward_ex(g.A, b, g.lamK, hint, math, algo)
+
+    def check(got, exact, pattern, what):
+        got, exact, pattern = (t.cpu()[:, live] for t in (got, exact, pattern))
+        assert torch.equal(got.isnan(), pattern.isnan()), what
+        assert torch.equal(got.isinf(), pattern.isinf()), what
+        ok = got.isfinite() & exact.isfinite()
+        slot = torch.arange(K).repeat_interleave(torch.tensor(widths[:K]))
+        for j in range(K):
+            a, e = ((t * ok)[:, slot == j].nan_to_num(0, 0, 0).double() for t in (got, exact))
+            err = (a - e).flatten(1).norm(dim=1) / e.flatten(1).norm(dim=1).clamp(min=1e-45)
+            assert float(err[0]) <= tol and float(err[1]) <= TOL, (what, j, err)
+
+    fp32 = binding.LBI_MATH_F32_MFMA
+    lam = run(binding.LBI_ALGO_CHAIN)
+    check(lam, run(binding.LBI_ALGO_CHAIN, fp32), run(binding.LBI_ALGO_CHAIN, fp32, None), "chain")
+    two = binding.LBI_ALGO_TWO_LEVEL
+    check(run(two), run(two, fp32), run(two, fp32, None), "two-level")
+    P, c = binding.lbi_scan_suffix_products(g.A, g.b, hint)
+    Pm, _ = binding.lbi_scan_suffix_products(g.A, None, hint, fp32)
+    check(P[..., :widths[K]], Pm[..., :widths[K]], Pm[..., :widths[K]], "products")
+    if not planted:
+        want = oracle.recurrence(x.A, x.b, x.lamK)
+        check(lam, torch.from_numpy(want), torch.from_numpy(want), "oracle")
+        Pr, cr = oracle.suffix_composites(x.A, x.b)
+        check(P, torch.from_numpy(Pr), torch.from_numpy(Pr), "oracle's products")
+        if affine:
+            check(c, torch.from_numpy(cr), torch.from_numpy(cr), "oracle's affine parts")
+    for chunk in (1, 3):
+        progress = torch.zeros(2, dtype=torch.int32, device=DEV)
+        clock = torch.zeros((2, -(-K // chunk)), dtype=torch.int64, device=DEV)
+        streamed = binding.lbi_scan_backward_streaming(g.A, g.b, g.lamK, progress, chunk, hint,
+                                                       publish_clock=clock)
+        assert torch.equal(streamed.view(torch.int32), lam.view(torch.int32))
+        assert progress.tolist() == [K] * 2
+        assert bool((clock > 0).all()) and bool((clock.diff(dim=1) >= 0).all())
+    if cycle is not None:
+        p = synth.pack_ragged(x)
+        r = binding.lbi_scan_backward_ragged(p.A.to(DEV), None if p.b is None else p.b.to(DEV),
+                                             p.lamK.to(DEV), list(widths)).cpu()
+        r = synth.unpack_ragged(r, widths, 128)
+        assert torch.equal(r[:, live].view(torch.int32), lam.cpu()[:, live].view(torch.int32))

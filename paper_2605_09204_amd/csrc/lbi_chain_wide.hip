@@ -35,16 +35,20 @@
 //     a row of P_s lambda_K that is not finite, or not zero and below 2^-96 of
 //     the largest entry of lambda_K or of the same row at s + 1 (what was lost is
 //     otherwise below 2^-29 of every row).  With composites, the largest magnitude
-//     of a quarter column of P_s (a lane's): 2^126 or more, or not zero and below 2^-96, or below 2^-96
-//     of the quarter's at s + 1; and a NaN in the segment's last composite.
+//     of a quarter column of P_s (a lane's): 2^126 or more, or not zero and below
+//     2^-96, or below 2^-96 of the quarter's at s + 1; and a NaN in the segment's
+//     last composite.  The checks cost up to 2% of a lambda pass and 5% of a hinted composite pass; a
+//     segment done again takes about 11 us a slot (scan_chain_kernel on the fp32
+//     matrix cores 9), on top of the slots up to what showed the loss: 64 chains of
+//     200 slots that halve at each one 2.67 ms against 1.78.
 //
 // What bounds it: a slot is 384 MFMAs of 16 cycles per SIMD (2.6 us at the top
 // clock), with about 500 VALU instructions of the matrix wave beside them; with
 // every CU busy the MFMAs run at 1.0-1.2 PFLOP/s of bf16 products, where a
 // large library matrix product reaches 1.4 on the same card.  192 chains of 24
-// slots: 142 us against 233 with the workgroup kernel on the fp32 matrix cores;
-// 256 x 128: 835 against 1170; widths cycling 32/64/128, 1024 x 64: 713 against
-// 808 (compact storage 709 against 791).
+// slots: 119 us against 218 with the workgroup kernel on the fp32 matrix cores;
+// 256 x 128: 757 against 1163; widths cycling 32/64/128, 1024 x 64: 681 against
+// 807 (compact storage 701 against 790).
 //
 // All HIP code here is built with packed fp32 math disabled.
 
@@ -94,12 +98,22 @@ __device__ __forceinline__ float column_top(float m, const f4 &a, const f4 &b)
     return m;
 }
 
+// Row v of a lane's blocks P[t], times lk.
+template <int NT>
+__device__ __forceinline__ float column_sum(const f4 (&P)[NT], int v, const float (&lk)[NT])
+{
+    if constexpr (NT == 1)
+        return P[0][v] * lk[0];
+    else
+        return P[0][v] * lk[0] + P[1][v] * lk[1];
+}
+
 // acc += A panel x b for the first NR row blocks and NT column blocks of a wave;
 // pan: this lane's operand of row block 0 (row block I adds 512 I elements).
 // Row blocks go in groups that give four independent accumulators.
-template <int NR, int NT>
-__device__ __forceinline__ void panel_product(f4 (&acc)[8][2], const __bf16 *pan,
-                                              const Parts (&b)[2])
+template <int NR, int NT, int W>
+__device__ __forceinline__ void panel_product(f4 (&acc)[8][W], const __bf16 *pan,
+                                              const Parts (&b)[W])
 {
     constexpr int GI = NT == 1 && NR >= 4 ? 4 : 2;
 #pragma unroll
@@ -132,7 +146,7 @@ __device__ __forceinline__ void panel_product(f4 (&acc)[8][2], const __bf16 *pan
 // published counts on from npub publications.  c_s is in entry s & 1 of sC, the
 // apply's sums of slot s in entry s & 1 of sPart.  The arguments and the thread's
 // index are read anew, so that the loops before keep nothing for this in registers.
-template <bool AFF, int HINT, int OUT>
+template <bool AFF, int HINT, int OUT, int NT>
 __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*sC)[kR],
                                            float (*sPart)[4][kR])
 {
@@ -166,15 +180,15 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
         offA -= 16 * blocks(K - 1) * pitch(wK);
         offR -= 16 * blocks(K - 1);
     }
-    f4 P[8][2];
-    float lk[2] = {0.0f, 0.0f};
+    f4 P[8][NT];
+    float lk[NT] = {};
     if (w < 4) {
         const int nrow = 16 * blocks(K - 1), ld = pitch(wK);
         const float *T = A + (compact ? (int64_t)offA : (K - 1) * (int64_t)(kR * kR));
 #pragma unroll
         for (int I = 0; I < 8; ++I)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int row = 16 * I + 4 * g + v, col = 16 * (w + 4 * t) + li;
@@ -182,7 +196,7 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
                 }
         if constexpr (OUT == kOutLambda) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const int idx = 16 * (w + 4 * t) + li, rK = compact ? 16 * wK : kR;
                 lk[t] = idx >= rK     ? 0.0f
                         : args.lamSeg ? args.lamSeg[(int64_t)blockIdx.x * kR + idx]
@@ -219,7 +233,7 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
                     for (int I = 0; I < 4; ++I)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            q[4 * I + v] = P[4 * h + I][0][v] * lk[0] + P[4 * h + I][1][v] * lk[1];
+                            q[4 * I + v] = column_sum<NT>(P[4 * h + I], v, lk);
                     group_reduce<16, 16>(q, li);
                     sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0];
                 }
@@ -228,7 +242,7 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
 #pragma unroll
                 for (int I = 0; I < 8; ++I)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < NT; ++t)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
                             T[(16 * I + 4 * g + v) * kR + 64 * t] = P[I][t][v];
@@ -263,7 +277,7 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
             const int ncol = (HINT ? 16 * wc : kR) / 2, col0 = (st & 1) * ncol;
             float x = 0.0f;
             if (AFF && s > 0 && row < nrow)
-#pragma unroll 1
+#pragma unroll 4
                 for (int i = col0; i < col0 + ncol; i += 4) {
                     const f4 a = *(const f4 *)&T[row * ld + i], y = *(const f4 *)&sC[s & 1][i];
                     x += a[0] * y[0] + a[1] * y[1] + a[2] * y[2] + a[3] * y[3];
@@ -291,11 +305,11 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
                     a[I] = __builtin_amdgcn_raw_buffer_load_b128(
                         rs, voff, __builtin_amdgcn_readfirstlane((16 * I * ld + 16 * k) * 4), 0);
             };
-            f4 Q[8][2];
+            f4 Q[8][NT];
 #pragma unroll
             for (int I = 0; I < 8; ++I)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
                     Q[I][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
             u4 a[2][8];
             load(a[0], 0);
@@ -303,23 +317,23 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
             for (int k = 0; k < 8; ++k) {
                 if (k < 7)
                     load(a[(k + 1) & 1], k + 1);
+                // (here, a step of products ahead, and not later)
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
 #pragma unroll
                     for (int I = 0; I < 8; ++I)
 #pragma unroll
-                        for (int t = 0; t < 2; ++t)
+                        for (int t = 0; t < NT; ++t)
                             Q[I][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                                 bitsf(a[k & 1][I][v]), P[k][t][v], Q[I][t], 0, 0, 0);
-                // (two steps' loads at a time: more do not fit the registers)
-                __builtin_amdgcn_sched_barrier(0);
             }
             // (with a hint, rows and columns that are not there stay zero: no zero
             // times an infinity)
 #pragma unroll
             for (int I = 0; I < 8; ++I)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
                     P[I][t] = !HINT || (I < nr && w + 4 * t < wK) ? Q[I][t]
                                                                   : f4{0.0f, 0.0f, 0.0f, 0.0f};
         }
@@ -331,7 +345,7 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
     }
 }
 
-template <bool AFF, int HINT, int OUT>
+template <bool AFF, int HINT, int OUT, int NT>
 __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 {
     __shared__ __attribute__((aligned(16))) __bf16 sA[2][3 * kPlane];
@@ -398,21 +412,21 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 
     if (w < 4) {
         // ---- matrix waves ---------------------------------------------------
-        float lk[2] = {0.0f, 0.0f};
+        float lk[NT] = {};
         if constexpr (OUT == kOutLambda) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < NT; ++t)
                 lk[t] = lambda_end(16 * (w + 4 * t) + li);
         }
         float *Pout = OUT == kOutComposite ? args.Pout + cslot * (int64_t)(kR * kR) : nullptr;
         // P_s, row blocks i0 .. i1 - 1, to global memory
-        auto store_rows = [&](const f4(&P)[8][2], int64_t s, int i0, int i1) {
+        auto store_rows = [&](const f4(&P)[8][NT], int64_t s, int i0, int i1) {
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)(Pout + s * (int64_t)(kR * kR)), 0, kTileBytes, kBufferWord3);
 #pragma unroll
             for (int I = i0; I < i1; ++I)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         __builtin_amdgcn_raw_buffer_store_b32(
@@ -420,18 +434,18 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                             ((16 * I + 4 * g + v) * kR + 16 * (w + 4 * t) + li) * 4, 0, 0);
         };
         // P_s lambda over this wave's columns, rows 64 h .. 64 h + 63
-        auto apply = [&](const f4(&P)[8][2], int64_t s, int h) {
+        auto apply = [&](const f4(&P)[8][NT], int64_t s, int h) {
             float q[16];
 #pragma unroll
             for (int I = 0; I < 4; ++I)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    q[4 * I + v] = P[4 * h + I][0][v] * lk[0] + P[4 * h + I][1][v] * lk[1];
+                    q[4 * I + v] = column_sum<NT>(P[4 * h + I], v, lk);
             group_reduce<16, 16>(q, li);
             // lane li holds value li (= 4 I + v)
             sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0];
         };
-        f4 P[8][2];
+        f4 P[8][NT];
         {
             const int nrow = 16 * blocks(K - 1), ld = pitch(blocks(K));
             const float *T = A + (compact ? (int64_t)args.totalA - nrow * ld
@@ -439,7 +453,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 #pragma unroll
             for (int I = 0; I < 8; ++I)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int row = 16 * I + 4 * g + v, col = 16 * (w + 4 * t) + li;
@@ -447,21 +461,28 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     }
         }
         const int apos = panel_pos(li, g);  // row block I adds 512 I elements
-        Parts b[2] = {split_rows(P[0][0], P[1][0]), split_rows(P[0][1], P[1][1])};
+        Parts b[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            b[t] = split_rows(P[0][t], P[1][t]);
         // (columns past the segment end's width are zero)
         const int nt = HINT && 4 + w >= blocks(K) ? 1 : 2;
         int buf = 0;  // the panel's LDS buffer
         // (composites) the largest magnitudes in this lane's rows of P's two columns, of
         // the row blocks split so far, and of a slot later
-        float top[2] = {column_top(0.0f, P[0][0], P[1][0]), column_top(0.0f, P[0][1], P[1][1])};
-        float before[2] = {0.0f, 0.0f};
+        float top[NT], before[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            top[t] = column_top(0.0f, P[0][t], P[1][t]);
+            before[t] = 0.0f;
+        }
         __syncthreads();
         // the range check of the P whose row blocks are all in top, in the loop's slot j
         // (-1: past it).  A NaN, which top leaves out, is in every row of every composite
         // after it: the last slot's check finds it.
         auto check_columns = [&](int64_t j, bool bad) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const float c = top[t];
                 bad |= c >= kFull || (c > 0.0f && c < fmaxf(kShow, before[t] * kShow));
                 before[t] = c;
@@ -476,15 +497,16 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         // blocks on entry, of Pn's on return
         int wr = blocks(K - 1), wnext = blocks(K - 2);
         // (true: the segment is to be done again)
-        auto slot = [&](const f4(&P)[8][2], f4(&Pn)[8][2], int64_t j) {
+        auto slot = [&](const f4(&P)[8][NT], f4(&Pn)[8][NT], int64_t j) {
             int32_t lost = 0;
-            [[maybe_unused]] const int np = panels(wr), nr = wnext;
+            const int wc = wr;
+            [[maybe_unused]] const int np = panels(wc), nr = wnext;
             wr = wnext;
             wnext = blocks(j - 1);
 #pragma unroll
             for (int I = 0; I < 8; ++I)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
                     Pn[I][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int p = 0; p < kNP; ++p) {
@@ -495,28 +517,31 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 buf ^= 1;
                 if (!HINT && p == 0)
                     lost = sLost[(j + 1) & 1];
-                Parts bn[2] = {b[0], b[1]};
+                Parts bn[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    bn[t] = b[t];
                 if constexpr (kShapes) {
                     // (blocks past nr hold zeros)
                     auto rows_for = [&](auto ntag) {
-                        constexpr int NT = decltype(ntag)::value;
+                        constexpr int N = decltype(ntag)::value;
                         if (nr <= 2)
-                            panel_product<2, NT>(Pn, pan, b);
+                            panel_product<2, N>(Pn, pan, b);
                         else if (nr <= 4)
-                            panel_product<4, NT>(Pn, pan, b);
+                            panel_product<4, N>(Pn, pan, b);
                         else
-                            panel_product<8, NT>(Pn, pan, b);
+                            panel_product<8, N>(Pn, pan, b);
                     };
-                    if (nt == 1)
+                    if (NT == 1 || nt == 1)
                         rows_for(std::integral_constant<int, 1>{});
                     else
-                        rows_for(std::integral_constant<int, 2>{});
+                        rows_for(std::integral_constant<int, NT>{});
                 } else {
-                    panel_product<8, 2>(Pn, pan, b);
+                    panel_product<8, NT>(Pn, pan, b);
                 }
                 if (p < kNP - 1) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
+                    for (int t = 0; t < NT; ++t) {
                         bn[t] = split_rows(P[2 * p + 2][t], P[2 * p + 3][t]);
                         if constexpr (OUT == kOutComposite)
                             top[t] = column_top(top[t], P[2 * p + 2][t], P[2 * p + 3][t]);
@@ -526,7 +551,8 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     // (a hinted slot may have one panel only)
                     if (HINT ? p == 0 : p == 1)
                         apply(P, j + 1, 0);
-                    if (HINT ? p == 0 : p == 2)
+                    // (rows past wc blocks are zero, and finish() takes them so)
+                    if (HINT ? p == 0 && wc > 4 : p == 2)
                         apply(P, j + 1, 1);
                 } else if (!args.agg_only) {
                     if (!HINT)
@@ -534,20 +560,21 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     else if (p == 0)
                         store_rows(P, j + 1, 0, 8);
                 }
-                b[0] = bn[0];
-                b[1] = bn[1];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    b[t] = bn[t];
             }
             if constexpr (OUT == kOutComposite)
                 check_columns(j, false);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 b[t] = split_rows(Pn[0][t], Pn[1][t]);
                 if constexpr (OUT == kOutComposite)
                     top[t] = column_top(0.0f, Pn[0][t], Pn[1][t]);
             }
             return !HINT && __builtin_amdgcn_readfirstlane(lost) == (int32_t)(j + 1);
         };
-        auto last = [&](const f4(&X)[8][2]) {
+        auto last = [&](const f4(&X)[8][NT]) {
             __syncthreads();
             if constexpr (OUT == kOutLambda) {
                 apply(X, 0, 0);
@@ -558,7 +585,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 #pragma unroll
                 for (int I = 0; I < 8; ++I)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
+                    for (int t = 0; t < NT; ++t) {
                         top[t] = column_top(top[t], X[I][t], X[I][t]);
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
@@ -569,7 +596,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         };
         // (the barrier: lambda_2's sums, in slot 0's entry, may still be read in
         // the last phase)
-        f4 Q[8][2];
+        f4 Q[8][NT];
         int64_t j = K - 2;
         if constexpr (HINT) {
             for (; j >= 0; --j) {
@@ -577,7 +604,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 #pragma unroll
                 for (int I = 0; I < 8; ++I)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < NT; ++t)
                         P[I][t] = Q[I][t];
             }
             last(P);
@@ -716,8 +743,9 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 if constexpr (OUT == kOutLambda) {
                     float *lam = args.lam + (compact ? beta * (int64_t)args.totalR + curL
                                                      : (first + s) * (int64_t)kR);
-                    const float p = (sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
-                                    (sPart[s & 1][2][st] + sPart[s & 1][3][st]);
+                    const float sum = (sPart[s & 1][0][st] + sPart[s & 1][1][st]) +
+                                      (sPart[s & 1][2][st] + sPart[s & 1][3][st]);
+                    const float p = HINT && st >= 16 * wr ? 0.0f : sum;
                     if (st < nrow)
                         lam[st] = p + c;
                     const float a = fabsf(p);
@@ -848,7 +876,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 
     __syncthreads();
     if (__builtin_expect(sWorst >= 0, 0))
-        exact_pass<AFF, HINT, OUT>(sWorst, sNpub, &sC[0], &sPart[0]);
+        exact_pass<AFF, HINT, OUT, NT>(sWorst, sNpub, &sC[0], &sPart[0]);
 }
 
 }  // namespace
@@ -856,13 +884,24 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 hipError_t launch_chain_wide_f32x(const ChainLaunch &c)
 {
     void *params[] = {(void *)&c.args};
+    // r_K <= 64: P's columns from 64 on are zero, and a matrix wave that holds one column
+    // block instead of two has half of the splits, copies and sums beside its products,
+    // which is what bounds a slot of few row blocks (the same results: the rest adds
+    // exact zeros).  Two blocks / one, us: widths 32/64/128, 1024 x 64, with b 715 / 681,
+    // compact without b 693 / 641; width 32, 600 x 64 268 / 235; width 64 652 / 611.  The
+    // fp32 matrix cores take 807, 663, 392 and 542 there: chains of no width above 64
+    // belong in r = 64 storage.  (Segments end in widths of their own.)
+    const bool narrow = c.ncol <= 4 && c.args.S == 1;
     auto pick = [&](auto aff, auto hint) -> const void * {
         constexpr bool AFF = decltype(aff)::value;
         constexpr int HINT = decltype(hint)::value;
         if constexpr (HINT != kHintCompact)
             if (c.out == kOutComposite)
-                return (const void *)&scan_wide_kernel<AFF, HINT, kOutComposite>;
-        return (const void *)&scan_wide_kernel<AFF, HINT, kOutLambda>;
+                return (const void *)&scan_wide_kernel<AFF, HINT, kOutComposite, 2>;
+        if constexpr (HINT != kHintNone)
+            if (narrow)
+                return (const void *)&scan_wide_kernel<AFF, HINT, kOutLambda, 1>;
+        return (const void *)&scan_wide_kernel<AFF, HINT, kOutLambda, 2>;
     };
     auto form = [&](auto hint) {
         return c.aff ? pick(std::true_type{}, hint) : pick(std::false_type{}, hint);

@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
 
 DEV = torch.device("cuda:0")
 TOL = 1e-5
-CYCLES = [(128,), (128, 16), (16, 128), (32, 64, 128), (112, 48, 16, 80), (96, 128, 64)]
+CYCLES = [(128,), (128, 16), (16, 128), (32, 64, 128), (112, 48, 16, 80), (96, 128, 64), (64,),
+          (80, 64)]
 
 
 def _err(lam, x):

@@ -690,8 +690,8 @@ RegionPlan region_plan(int64_t B, int64_t K, int64_t L, int32_t D, int32_t X, in
 // The token-mixing block adds, for G (sequence, region) pairs at a time: s16,
 // h16, Vt (bf16), s32, c32, g32, y32, wv, Tpart (fp32), S16 (bf16), after the
 // parts above.
-// G is what fits kSsmGroupBytes (at least 1, and few enough for a 1-D grid of
-// either tangent product's 256 x 256 tiles); the second tangent product
+// G is what fits kSsmGroupBytes (at least 1, at most what a grid's y dimension
+// holds, and less than 2^31 of the tangent products' tiles); the second tangent product
 // writes one partial sum per 256-row tile of a pair (nchunk of them).
 constexpr int kSsmParts = 10;
 constexpr size_t kSsmGroupBytes = (size_t)6 << 30;
@@ -748,15 +748,16 @@ bool region_sizes_ok(int64_t B, int64_t K, int64_t L, int32_t D, int32_t X, int3
         return false;
     if (D < 64 || D > 2048 || D % 64 != 0 || X < 128 || X > 8192 || X % 128 != 0)
         return false;
-    // launch grids: the tangent products put B r / 128 row tiles in y and K in z
+    // (what the entry points accept; the launches take lists of workgroups of any
+    // length)
     if (B > 65535 || K > 65535 || L > ((int64_t)1 << 24) ||
         (B * r + 127) / 128 > 65535)
         return false;
     return B * K * (X / 128) < ((int64_t)1 << 31) - 1;
 }
 
-// the token-mixing block's first tangent product has L r rows: L r / 128 row
-// tiles in a launch's y
+// (the token-mixing block's first tangent product has L r rows; what its entry point
+// accepts)
 bool ssm_sizes_ok(int64_t L, int32_t r) { return (L * r + 127) / 128 <= 65535; }
 
 }  // namespace

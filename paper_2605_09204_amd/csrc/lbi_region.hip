@@ -58,6 +58,21 @@ constexpr int BM = 128, BN = 128, BK = 64;
 constexpr int TILE = 128 * BK;  // bf16 elements of one LDS tile (no padding)
 constexpr float kLnEps = 1e-5f;
 
+// Workgroup lists.  A launch dimension holds fewer than 2^32 work items (2^24
+// workgroups of 256; past that the runtime refuses a launch, or starts what is left of
+// the number modulo 2^32), so a list goes over rows of kGridRow workgroups, a multiple
+// of 8 for the order over the XCDs.  Workgroups past the list do nothing.
+constexpr int64_t kGridRow = 1 << 20;
+dim3 list_grid(int64_t n)
+{
+    return n <= kGridRow ? dim3((unsigned)n)
+                         : dim3((unsigned)kGridRow, (unsigned)((n + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ int64_t list_index()
+{
+    return (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+}
+
 // The logistic function through the hardware reciprocal (1 ulp): it needs no
 // correctly rounded division, and rcp(inf) = 0 keeps the saturated end exact.
 __device__ __forceinline__ float sigm(float h) { return __builtin_amdgcn_rcpf(1.0f + __expf(-h)); }
@@ -389,8 +404,10 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     typedef __attribute__((address_space(3))) char lchar;
     const uint32_t lbase = (uint32_t)(uintptr_t)(lchar *)smem;
     const int nxt = q.X / BN;
-    const int64_t G = (int64_t)gridDim.x;
-    int64_t lg = blockIdx.x;
+    const int64_t G = q.K * q.B * nxt * q.nsplit;
+    int64_t lg = list_index();
+    if (lg >= G)
+        return;
     if (G % 8 == 0)
         lg = (lg % 8) * (G / 8) + lg / 8;
     // (this workgroup's row tiles: t0 .. t0 + ntile - 1, part sp of q.nsplit)
@@ -862,7 +879,7 @@ template <int TM> constexpr int gemm_lds()
 template <int TM> __global__ __launch_bounds__(kT) void gemm_nt_kernel(GemmOp g, int64_t batch)
 {
     __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
-    gemm_block<TM>(g, batch, blockIdx.x, smem);
+    gemm_block<TM>(g, batch, list_index(), smem);
 }
 
 // ---- launches that join independent steps ------------------------------------------
@@ -874,10 +891,11 @@ template <int NB>
 __global__ __launch_bounds__(kT) void in_kernel(RegionArgs q, BmvArgs v, int64_t nb)
 {
     __shared__ __attribute__((aligned(16))) char smem[kBmvCols * 4];
-    if ((int64_t)blockIdx.x < nb)
-        bmv_block<NB>(v, q.K, blockIdx.x, smem);
-    else
-        xpart_block(q, blockIdx.x - nb);
+    const int64_t i = list_index();
+    if (i < nb)
+        bmv_block<NB>(v, q.K, i, smem);
+    else if (i - nb < (q.L + 63) / 64 * q.B)
+        xpart_block(q, i - nb);
 }
 
 // dec: d (bmv), P1, and the token mean of x_embed
@@ -885,7 +903,7 @@ template <int NB>
 __global__ __launch_bounds__(kT) void dec_kernel(RegionArgs q, BmvArgs v, int64_t nb, int64_t np)
 {
     __shared__ __attribute__((aligned(16))) char smem[64 * 129 * 4];
-    const int64_t i = blockIdx.x;
+    const int64_t i = list_index();
     if (i < nb)
         bmv_block<NB>(v, q.K, i, smem);
     else if (i < nb + np)
@@ -900,10 +918,11 @@ __global__ __launch_bounds__(kT) void gemm_bmv_kernel(GemmOp g, BmvArgs v, int64
 {
     __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
     // (nb is rounded up to a multiple of 8)
-    if ((int64_t)blockIdx.x >= nb)
-        gemm_block<TM>(g, K, blockIdx.x - nb, smem);
-    else if ((int64_t)blockIdx.x < bmv_blocks(v.N, K, v.B, NB))
-        bmv_block<NB>(v, K, blockIdx.x, smem);
+    const int64_t i = list_index();
+    if (i >= nb)
+        gemm_block<TM>(g, K, i - nb, smem);
+    else if (i < bmv_blocks(v.N, K, v.B, NB))
+        bmv_block<NB>(v, K, i, smem);
 }
 
 // a product and the LayerNorm of the forward, a wave per (sequence, region)
@@ -911,10 +930,11 @@ template <int TM>
 __global__ __launch_bounds__(kT) void gemm_ln_kernel(GemmOp g, int64_t ng, RegionArgs q)
 {
     __shared__ __attribute__((aligned(1024))) char smem[gemm_lds<TM>()];
-    if ((int64_t)blockIdx.x < ng) {
-        gemm_block<TM>(g, q.K, blockIdx.x, smem);
+    const int64_t i = list_index();
+    if (i < ng) {
+        gemm_block<TM>(g, q.K, i, smem);
     } else {
-        const int64_t bk = (blockIdx.x - ng) * 4 + threadIdx.x / 64;
+        const int64_t bk = (i - ng) * 4 + threadIdx.x / 64;
         if (bk < q.B * q.K)
             ln_fwd_wave(q, bk);
     }
@@ -1515,7 +1535,7 @@ template <typename F> void with_tile(int tm, F &&f)
 hipError_t gemm(const GemmOp &g, int64_t batch, hipStream_t st)
 {
     const int tm = gemm_tile(g, batch);
-    const dim3 grid((unsigned)gemm_blocks(g, batch, tm));
+    const dim3 grid = list_grid(gemm_blocks(g, batch, tm));
     with_tile(tm, [&](auto tag) {
         hipLaunchKernelGGL(gemm_nt_kernel<decltype(tag)::value>, grid, dim3(kT), 0, st, g, batch);
     });
@@ -1527,7 +1547,7 @@ hipError_t gemm_bmv(const GemmOp &g, const BmvArgs &v, int64_t K, hipStream_t st
 {
     const int tm = gemm_tile(g, K), nb = bmv_nb(v.B);
     const int64_t nv = round8(bmv_blocks(v.N, K, v.B, nb));
-    const dim3 grid((unsigned)(nv + gemm_blocks(g, K, tm)));
+    const dim3 grid = list_grid(nv + gemm_blocks(g, K, tm));
     with_tile(tm, [&](auto tag) {
         constexpr int TM = decltype(tag)::value;
         if (nb == 2)
@@ -1550,7 +1570,7 @@ hipError_t gemm_ln(const GemmOp &g, const RegionArgs &q, hipStream_t st)
 {
     const int tm = gemm_tile(g, q.K);
     const int64_t ng = gemm_blocks(g, q.K, tm);
-    const dim3 grid((unsigned)(ng + (q.B * q.K + 3) / 4));
+    const dim3 grid = list_grid(ng + (q.B * q.K + 3) / 4);
     with_tile(tm, [&](auto tag) {
         hipLaunchKernelGGL(gemm_ln_kernel<decltype(tag)::value>, grid, dim3(kT), 0, st, g, ng, q);
     });
@@ -1568,7 +1588,7 @@ hipError_t dec(const RegionArgs &q, hipStream_t st)
     BmvArgs v{(const __bf16 *)q.W_d1, (int64_t)D * r, q.m, K * r, r, q.b_d1, D, nullptr, 0, 0,
               nullptr, 0, 0, nullptr, q.su, q.sa, K * D, D, q.B, D, r};
     int64_t n0 = bmv_blocks(D, K, q.B, nb);
-    dim3 grid((unsigned)(n0 + nch * q.B));
+    dim3 grid = list_grid(n0 + nch * q.B);
     if (nb == 2)
         hipLaunchKernelGGL(in_kernel<2>, grid, dim3(kT), 0, st, q, v, n0);
     else
@@ -1579,7 +1599,7 @@ hipError_t dec(const RegionArgs &q, hipStream_t st)
     v = BmvArgs{(const __bf16 *)q.W_d2, (int64_t)D * D, q.su, K * D, D, q.b_d2, D, nullptr, 0, 0,
                 nullptr, 0, 0, q.d, nullptr, nullptr, K * D, D, q.B, D, D};
     const int64_t np = q.B * K * (D / 64);
-    grid = dim3((unsigned)(n0 + np + q.B * ((D + kT - 1) / kT)));
+    grid = list_grid(n0 + np + q.B * ((D + kT - 1) / kT));
     if (nb == 2)
         hipLaunchKernelGGL(dec_kernel<2>, grid, dim3(kT), 0, st, q, v, n0, np);
     else
@@ -1634,8 +1654,8 @@ hipError_t launch_region_jacobians(const RegionArgs &q, hipStream_t st)
               nullptr, nullptr, K * X, X, q.B, X, D};
     if ((e = gemm_bmv(g, v, K, st)) != hipSuccess)
         return e;
-    hipLaunchKernelGGL(region_dma_kernel, dim3((unsigned)(K * q.B * (X / BN) * q.nsplit)), dim3(kT),
-                       0, st, q);
+    hipLaunchKernelGGL(region_dma_kernel, list_grid(K * q.B * (X / BN) * q.nsplit), dim3(kT), 0, st,
+                       q);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     // U'^T[k] = (Jdec^T W1[k]^T) * gbar[b][k][x]        (B r x X, K = D)

@@ -85,6 +85,25 @@ def test_region_tile_and_part_choices(shape):
     _check(synth.generate_region(wl), wl.name)
 
 
+def test_region_more_workgroups_than_a_dimension_holds():
+    """64 sequences of 2^24 tokens: the partial means of x_embed alone are 2^24
+    workgroups of 256 threads, one more than a launch dimension holds.  Every token
+    is the same 0.5, so the results are those of 64 tokens, up to the float32 sums
+    over the tokens (2^17 equal terms to a lane: at most 2^17 roundings of 2^-24
+    each)."""
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GiB of free GPU memory")
+    B, L, D, X, r = 64, 1 << 24, 64, 128, 16
+    _say(f"[region] B{B} L{L}")
+    x = synth.generate_region(synth.RegionWorkload("region_grid", B, 1, 64, D, X, r, seed=29))
+    x.x_embed.fill_(0.5)
+    A, mn = _run(x)
+    x.x_embed = torch.full((B, L, D), 0.5, dtype=torch.bfloat16, device=DEV)
+    Along, mlong = _run(x)
+    torch.cuda.empty_cache()
+    assert oracle.rel_frobenius(Along, A) <= 2 ** -7 and oracle.rel_frobenius(mlong, mn) <= 2 ** -7
+
+
 def test_region_alpha_zero_is_layernorm_exactly():
     wl = synth.RegionWorkload("region_alpha0", 2, 2, 128, 128, 256, 32, seed=13)
     x = synth.generate_region(wl)

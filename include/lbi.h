@@ -233,8 +233,8 @@ size_t lbi_scan_backward_workspace_bytes(int64_t B, int64_t K, int32_t r, lbi_dt
  * LBI_ALGO_TWO_LEVEL about 4 B S r (r + 2) bytes with S ~ sqrt(2K) (the
  * segment aggregates in float32, plus the carries), or 4 B K r (r + 2) for
  * the smaller batches, whose composites are all kept (fp32: up to 100 MiB of
- * them, 256 MiB at r = 128; bf16: below 16 chains, 32 at r = 16, up to
- * 256 MiB); for LBI_ALGO_TREE about 4 B (K / C) r (r + 2) bytes summed over
+ * them, 210 MiB at r = 64 and 256 at r = 128; bf16: below 16 chains, 32 at
+ * r = 16, up to 256 MiB); for LBI_ALGO_TREE about 4 B (K / C) r (r + 2) bytes summed over
  * its levels (0 for K <= C).  LBI_ALGO_AUTO: enough for the algorithm it takes,
  * with or without b, in every arithmetic and for every widths hint.  At the
  * larger numbers of chains for which it takes the two-level scan, a call that

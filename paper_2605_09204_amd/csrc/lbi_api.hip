@@ -93,15 +93,19 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Measured on MI355X (us, kept / scanned again).  bf16, whose A is half as many
 // bytes as its composites': r = 64, K = 128, 16 chains 34 / 26, 64 chains 59 /
 // 44, 128 chains 144 / 71; r = 32, K = 500, 16 chains 30 / 31, 128 chains 155 /
-// 71; r = 16, K = 500, 16 chains 21 / 23, 32 chains 25 / 24.  fp32: r = 64, 64
-// MB of composites 45 / 49, 125 MB 90 / 79, 250 MB 171 / 141; r = 32, 62 MB 41 /
-// 42, 125 MB 82 / 65; r = 128, 128 MB 106 / 102 and 109 / 126, 250 MB 227 / 245,
-// 500 MB 448 / 405 and 394 / 406.
-bool two_level_rescan(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
+// 71; r = 16, K = 500, 16 chains 21 / 23, 32 chains 25 / 24.  fp32, by the MiB of
+// composites: r = 32, 100 58 / 57, 109 64 / 57, 128 83 / 65; r = 64, 112 66 / 72, 125
+// 81 / 84, 128 83 / 76 and 92 / 83, 250 171 / 144; r = 128 has no clear line (128 106 /
+// 102 and 129 / 140, 192 156 / 174, 250 222 / 233 and 224 / 198, 384 300 / 301).  A second
+// scan costs more on the fp32 matrix cores: r = 64, 112 69 / 86, 128 94 / 97, 200 142 /
+// 152, 250 178 / 169; r = 32 as above.
+bool two_level_rescan(int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math)
 {
     const double mib = 4.0 * (double)B * K * r * r / (1 << 20);
     if (dt == LBI_BF16)
         return B >= (r == 16 ? 32 : 16) || mib > 256.0;
+    if (r == 64)
+        return mib > (math == LBI_MATH_F32_MFMA ? 210.0 : 126.0);
     return mib > (r == 128 ? 256.0 : 100.0);
 }
 
@@ -113,7 +117,7 @@ struct TwoLevelPlan {
 };
 
 // (force_rescan: the aggregates-only form whatever the composites' size)
-TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, lbi_dtype dt,
+TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math,
                             bool force_rescan = false)
 {
     TwoLevelPlan p;
@@ -124,7 +128,7 @@ TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, lbi_dtype dt,
         S = 1;
     p.L = (K + S - 1) / S;
     p.S = (int32_t)((K + p.L - 1) / p.L);
-    p.rescan = force_rescan || two_level_rescan(B, K, r, dt);
+    p.rescan = force_rescan || two_level_rescan(B, K, r, dt, math);
     const int64_t nslots = p.rescan ? (int64_t)p.S : K;  // composites kept per chain
     const size_t nP = (size_t)B * nslots * r * r * sizeof(float);
     const size_t nc = (size_t)B * nslots * r * sizeof(float);
@@ -134,6 +138,14 @@ TwoLevelPlan two_level_plan(int64_t B, int64_t K, int32_t r, lbi_dtype dt,
     p.offcarry = p.offc + align256(nc);
     p.bytes = p.offcarry + align256(ncar);
     return p;
+}
+
+// What the workspace queries answer: enough in every arithmetic.
+size_t two_level_bytes(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
+{
+    const size_t a = two_level_plan(B, K, r, dt, LBI_MATH_DEFAULT).bytes;
+    const size_t b = two_level_plan(B, K, r, dt, LBI_MATH_F32_MFMA).bytes;
+    return a > b ? a : b;
 }
 
 // The apply pass launches up to B*K workgroups.
@@ -257,7 +269,7 @@ bool two_level_by_model(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
         return false;
     const double ts = slot_us(dt, r), w = waves_for_r(r), cap = 1280.0;
     const double t_chain = 6.0 + (double)K * ts * fmax(1.0, (double)B * w / cap);
-    const TwoLevelPlan p = two_level_plan(B, K, r, dt);
+    const TwoLevelPlan p = two_level_plan(B, K, r, dt, LBI_MATH_DEFAULT);
     // (three launches: 18 us of fixed cost, measured with HIP events at
     // B = 1..16, K = 16..64, where the chain scan's one launch costs 6 us
     // plus its slots)
@@ -516,8 +528,9 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     // A two-level scan that the model would not take is an offer: without the
     // workspace (or scratch) for it, the chain scan.
     if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_TWO_LEVEL && !two_level_by_model(B, K, r, dt)) {
-        const size_t least = two_level_plan(B, K, r, dt, true).bytes;
-        if (scratch ? least > kScratchBytes : !ws || ws_bytes < two_level_plan(B, K, r, dt).bytes)
+        const size_t least = two_level_plan(B, K, r, dt, math, true).bytes;
+        if (scratch ? least > kScratchBytes
+                    : !ws || ws_bytes < two_level_plan(B, K, r, dt, math).bytes)
             use = resolve_algo(algo, B, K, r, dt, math, b != nullptr, true);
     }
     // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes
@@ -526,11 +539,13 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     // widths 32/64/128); at width 64 the two tie
     if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_CHAIN && ring)
         use = LBI_ALGO_CHAIN_RING;
-    TwoLevelPlan p = two_level_plan(B, K, r, dt);
-    size_t need = lbi_scan_backward_workspace_bytes_ex(B, K, r, dt, use);
+    TwoLevelPlan p = two_level_plan(B, K, r, dt, math);
+    size_t need = use == LBI_ALGO_TWO_LEVEL
+                      ? p.bytes
+                      : lbi_scan_backward_workspace_bytes_ex(B, K, r, dt, use);
     if (scratch && need > kScratchBytes) {
         if (use == LBI_ALGO_TWO_LEVEL) {
-            p = two_level_plan(B, K, r, dt, true);
+            p = two_level_plan(B, K, r, dt, math, true);
             need = p.bytes;
         }
         if (need > kScratchBytes)
@@ -862,14 +877,14 @@ size_t lbi_scan_backward_workspace_bytes_ex(int64_t B, int64_t K, int32_t r, lbi
     if (algo == LBI_ALGO_AUTO)
         return two_level_by_size(B, K, r, dt, true) || two_level_by_size(B, K, r, dt, false) ||
                        two_level_by_model(B, K, r, dt)
-                   ? two_level_plan(B, K, r, dt).bytes
+                   ? two_level_bytes(B, K, r, dt)
                    : 0;
     if (algo == LBI_ALGO_TREE)
         // (sized for an affine term: enough with or without b)
         return r <= 64 && tree_possible(B, K, r) ? tree_plan(B, K, r, true).bytes : 0;
     if (algo != LBI_ALGO_TWO_LEVEL || !two_level_possible(B, K))
         return 0;
-    return two_level_plan(B, K, r, dt).bytes;
+    return two_level_bytes(B, K, r, dt);
 }
 
 size_t lbi_scan_backward_workspace_bytes(int64_t B, int64_t K, int32_t r, lbi_dtype dt)

@@ -453,20 +453,44 @@ def test_two_level_parity(B, K, r, dtype, arith):
                      f"two-level B{B} K{K} r{r} {dtype} {arith} affine={affine}")
 
 
+# (dtype, arithmetic, r, chains of 200 slots that keep every composite): one more
+# chain is scanned again from its carries
+FORMS = [("f32", "split", 64, 40), ("f32", "mfma", 64, 67), ("f32", "split", 32, 128),
+         ("f32", "mfma", 32, 128), ("f32", "split", 16, 512), ("f32", "split", 128, 20),
+         ("bf16", None, 64, 15), ("bf16", None, 128, 15), ("bf16", None, 32, 15),
+         ("bf16", None, 16, 31)]
+
+
 @pytest.mark.parametrize("affine", [True, False])
-@pytest.mark.parametrize("B", [81, 82])
-def test_two_level_both_forms(B, affine):
-    """At r = 64 and K = 200, B = 81 keeps every segment composite (253.1 MiB
-    of fp32) and applies them in one pass; B = 82 (256.3 MiB) keeps only the
-    segment aggregates and scans each segment again from its carry.  Both against the
-    oracle on every chain, with and without b, and the widths hint changing
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("dtype,arith,r,B", FORMS)
+def test_two_level_both_forms(dtype, arith, r, B, more, affine):
+    """The two-level scan keeps every segment composite up to a number of chains that
+    depends on the storage, the width and the arithmetic (125, 209.4, 100, 100, 100 and
+    250 MiB of them in fp32) and applies them in one pass; past it, it keeps only the
+    segment aggregates and scans each segment again from its carry.  Which form runs is
+    told by the workspace that it asks for: the aggregates' or every composite's.  Both
+    forms against the oracle, with and without b, and the widths hint changing
     nothing."""
-    K, r = 200, 64
-    _say(f"[two-level] B={B} K={K} affine={affine}")
-    x = synth.random_chain(B, K, r, dtype="f32", seed=61 + B, affine=affine, device="cuda:0")
-    lam = run_gpu(x, algo="two_level")
-    assert_close(lam.cpu().numpy(), ref(x.to("cpu")), TOL["f32"], f"two-level B{B}")
-    assert torch.equal(lam, run_gpu(x, widths=[r] * (K + 1), algo="two_level"))
+    K, B = 200, B + more
+    _say(f"[two-level] {dtype} {arith} r={r} B={B} K={K} affine={affine}")
+    x = synth.random_chain(B, K, r, dtype=dtype, seed=61 + B, affine=affine, device="cuda:0")
+    lam = run_gpu(x, math=arith, algo="two_level")
+    assert_close(lam.cpu().numpy(), ref(x.to("cpu")), TOL["f32"] if dtype == "f32" else BF16_EXPECTED,
+                 f"two-level B{B}")
+    assert torch.equal(lam, run_gpu(x, widths=[r] * (K + 1), math=arith, algo="two_level"))
+    S = 20  # segments of 10 slots
+    up = lambda n: (n + 255) // 256 * 256  # the workspace's parts are 256-byte aligned
+    least = up(4 * B * S * r * r) + 2 * up(4 * B * S * r)
+    ws = torch.empty((least,), dtype=torch.uint8, device="cuda:0")
+    call = lambda: binding.lbi_scan_backward_ex(x.A, x.b, x.lamK, None, MATH[arith] if arith else 0,
+                                                binding.LBI_ALGO_TWO_LEVEL, workspace=ws)
+    if more:
+        assert torch.equal(lam, call())
+    else:
+        with pytest.raises(binding.LbiError) as e:
+            call()
+        assert e.value.status == 5  # LBI_ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("arith", ["split", "mfma"])

@@ -312,8 +312,12 @@ lbi_status lbi_scan_backward_ex(const void *A, const void *b, const void *lambda
  *
  *   A, b, lambda_K, lambda, B, K, r, dt, stream, widths_host, math, algo: as
  *   for lbi_scan_backward_ex.
- * The algorithm is the one lbi_scan_backward_ex would run.  A two-level scan
- * whose composites would not fit the array keeps only the segment aggregates
+ * The algorithm is the one lbi_scan_backward_ex runs when it is given no
+ * workspace, and the array is used by exactly the calls for which that is
+ * LBI_ERR_WORKSPACE: LBI_ALGO_TWO_LEVEL, LBI_ALGO_TREE of more than one chunk,
+ * and LBI_ALGO_AUTO for the few long chains that it takes the two-level scan
+ * for in any case (where it takes that scan only if there is workspace for it,
+ * this call runs the chain scan).  A two-level scan whose composites would not fit the array keeps only the segment aggregates
  * and scans each segment again from its carry (the form lbi_scan_backward_ex
  * takes for the larger batches); its results then agree with
  * lbi_scan_backward_ex's to float32 rounding rather than bit for bit.  A call

@@ -526,11 +526,10 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr,
                                 ring && !two_level_by_model(B, K, r, dt));
     // A two-level scan that the model would not take is an offer: without the
-    // workspace (or scratch) for it, the chain scan.
+    // workspace for it, the chain scan.  The library's one scratch array is shared by
+    // every call on a GPU and is not offered: calls that need none stay independent.
     if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_TWO_LEVEL && !two_level_by_model(B, K, r, dt)) {
-        const size_t least = two_level_plan(B, K, r, dt, math, true).bytes;
-        if (scratch ? least > kScratchBytes
-                    : !ws || ws_bytes < two_level_plan(B, K, r, dt, math).bytes)
+        if (scratch || !ws || ws_bytes < two_level_plan(B, K, r, dt, math).bytes)
             use = resolve_algo(algo, B, K, r, dt, math, b != nullptr, true);
     }
     // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes

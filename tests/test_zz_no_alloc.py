@@ -76,6 +76,27 @@ def test_noalloc_without_scratch_use_matches_bit_for_bit():
         assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("B,K,r,dt,chain", [(150, 100, 64, "bf16", "CHAIN"),
+                                            (256, 130, 32, "bf16", "CHAIN_WAVE"),
+                                            (260, 70, 32, "f32", "CHAIN"),
+                                            (800, 100, 16, "f32", "CHAIN")])
+def test_noalloc_auto_leaves_the_array_alone(B, K, r, dt, chain):
+    """Where AUTO takes the two-level scan only if it is given workspace, the call
+    without one runs the chain scan and does not touch the array that all calls on
+    the GPU share: bit for bit the chain scan, and lbi_scan_backward_ex that is given
+    too little workspace."""
+    x = synth.random_chain(B, K, r, dtype=dt, seed=66 + K)
+    dev = torch.device("cuda:0")
+    A, b, lk = x.A.to(dev), x.b.to(dev), x.lamK.to(dev)
+    _say(f"[noalloc] B={B} K={K} r={r} {dt} auto")
+    assert binding.lbi_scan_backward_workspace_bytes(B, K, r, 0 if dt == "f32" else 1) > 0
+    lam = binding.lbi_scan_backward_noalloc(A, b, lk)
+    little = torch.empty((16,), dtype=torch.uint8, device=dev)
+    assert torch.equal(lam, binding.lbi_scan_backward_ex(A, b, lk, workspace=little))
+    algo = getattr(binding, "LBI_ALGO_" + chain)
+    assert torch.equal(lam, binding.lbi_scan_backward_ex(A, b, lk, algo=algo))
+
+
 @pytest.mark.parametrize("algo", ["ring", "auto"])
 def test_noalloc_ring_kernel_with_widths(algo):
     # the LDS-ring chain kernel (explicit, and AUTO's choice at width 128 with

@@ -108,8 +108,8 @@ typedef enum {
                              * two-level, up to a number of chains that depends
                              * on the dtype and r (about 1350, 500, 126 and 100
                              * for fp32 at r = 16, 32, 64, 128; 1350, 530, 222
-                             * and 104 for bf16, without b 1700, 500, 190 and
-                             * 104) and is lower for short chains.
+                             * and 90 for bf16, without b 1700, 500, 190 and
+                             * 90) and is lower for short chains.
                              * K < 16: chain.
                              * Otherwise bf16 with r <= 32 and B <= 8192 goes
                              * to LBI_ALGO_CHAIN_WAVE, and fp32 with r = 64 in

@@ -293,7 +293,10 @@ bool two_level_by_model(int64_t B, int64_t K, int32_t r, lbi_dtype dt)
 // 300 40 / 41; r = 64, K = 128: 144 81 / 68, 176 81 / 79; with one: r = 16, K = 90:
 // 300 23 / 20, 600 27 / 29; K = 400: 900 121 / 114, 1200 156 / 156; r = 32, K =
 // 128: 300 56 / 51, 400 56 / 62; K = 400: 500 215 / 215; r = 64, K = 128: 208 112 /
-// 107, 240 114 / 128; r = 128 (either), K = 64: 80 195 / 187, 96 196 / 221.  Where
+// 107, 240 114 / 128; r = 128 (either), K = 64: 80 195 / 187, 96 196 / 221.  (bf16 at
+// r = 128 stops where the model does, at most 14 chains earlier: past it a widths hint
+// makes the chain scan the faster one by up to 1.3 times, 90 x 100 of width 32 137 /
+// 176, and a hint is not to change the scan.)  Where
 // the model above chose differently it was off by up to 2.5 times (bf16, r = 32,
 // 248 chains of 395 slots: 258 us in the chain scan as it then was, 103 here).
 bool two_level_by_size(int64_t B, int64_t K, int32_t r, lbi_dtype dt, bool aff)
@@ -305,7 +308,9 @@ bool two_level_by_size(int64_t B, int64_t K, int32_t r, lbi_dtype dt, bool aff)
     static const double bf16[4][2] = {{1350, 55}, {530, 36}, {222, 14}, {104, 9}};
     static const double bf16_noaff[4][2] = {{1700, 80}, {500, 45}, {190, 16}, {104, 9}};
     const double *c = dt != LBI_BF16 ? f32[i] : (aff ? bf16[i] : bf16_noaff[i]);
-    return (double)B <= c[0] * (1.0 - c[1] / (double)K);
+    if (!((double)B <= c[0] * (1.0 - c[1] / (double)K)))
+        return false;
+    return !(dt == LBI_BF16 && r == 128) || two_level_by_model(B, K, r, dt);
 }
 
 bool default_math(lbi_math math)
@@ -519,12 +524,9 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     const size_t nl = (size_t)B * r * esz, nout = (size_t)B * K * r * sizeof(float);
     if (overlaps(lam, nout, A, nA) || overlaps(lam, nout, b, nb) || overlaps(lam, nout, lamK, nl))
         return LBI_ERR_ALIAS;
-    // (bf16 chains at width 128 in widths of the LDS-ring kernel: its chain scan
-    // is faster than the one two_level_by_size knows)
     const bool ring = dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r == 128 &&
                       ring_plan(widths, K, r).ok;
-    lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr,
-                                ring && !two_level_by_model(B, K, r, dt));
+    lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr);
     // A two-level scan that the model would not take is an offer: without the
     // workspace for it, the chain scan.  The library's one scratch array is shared by
     // every call on a GPU and is not offered: calls that need none stay independent.

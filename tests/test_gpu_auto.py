@@ -56,6 +56,25 @@ def test_auto_with_and_without_workspace(B, K, r, dtype, affine, algo, less):
         assert e.value.status == 5  # LBI_ERR_WORKSPACE
 
 
+def test_auto_hint_keeps_the_chain_scan():
+    """bf16 chains at r = 128, as many as the cost model leaves to the chain scan: they
+    run it with and without a widths hint, on the LDS-ring kernel for widths that it
+    takes and bit for bit as the unhinted call for others."""
+    B, K = 86, 64
+    for cycle, algo in (((32, 64, 128), binding.LBI_ALGO_CHAIN_RING), ((16, 128), CHAIN)):
+        widths = list(synth.cyclic_widths(K, cycle))
+        x = synth.random_chain(B, K, 128, dtype="bf16", seed=94, widths=tuple(widths))
+        g = x.to(DEV)
+        lam = binding.lbi_scan_backward(g.A, g.b, g.lamK)
+        assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=CHAIN))
+        hinted = binding.lbi_scan_backward_widths(g.A, g.b, g.lamK, widths)
+        assert torch.equal(hinted, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, widths,
+                                                                algo=algo))
+        assert _err(hinted, x) <= TOL["bf16"]
+        if algo == CHAIN:
+            assert torch.equal(hinted, lam)
+
+
 @pytest.mark.parametrize("K,r,most", [(13, 16, 512), (12, 32, 512), (11, 32, 256)])
 def test_auto_tree_batch_limit(K, r, most):
     """fp32 chains within a tree chunk: one tree launch up to a number of them."""

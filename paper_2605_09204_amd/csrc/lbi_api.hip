@@ -527,11 +527,13 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     const bool ring = dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r == 128 &&
                       ring_plan(widths, K, r).ok;
     lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr);
-    // A two-level scan that the model would not take is an offer: without the
-    // workspace for it, the chain scan.  The library's one scratch array is shared by
+    // A two-level scan that the model would not take is an offer: without a
+    // workspace that it can use, the chain scan.  The library's one scratch array is shared by
     // every call on a GPU and is not offered: calls that need none stay independent.
     if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_TWO_LEVEL && !two_level_by_model(B, K, r, dt)) {
-        if (scratch || !ws || ws_bytes < two_level_plan(B, K, r, dt, math).bytes)
+        const size_t n = two_level_plan(B, K, r, dt, math).bytes;
+        if (scratch || !ws || ws_bytes < n || overlaps(ws, n, A, nA) || overlaps(ws, n, b, nb) ||
+            overlaps(ws, n, lamK, nl) || overlaps(ws, n, lam, nout))
             use = resolve_algo(algo, B, K, r, dt, math, b != nullptr, true);
     }
     // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes

@@ -56,6 +56,21 @@ def test_auto_with_and_without_workspace(B, K, r, dtype, affine, algo, less):
         assert e.value.status == 5  # LBI_ERR_WORKSPACE
 
 
+def test_auto_takes_no_workspace_that_overlaps():
+    """A workspace that overlaps an argument was never looked at where AUTO ran the
+    chain scan; where it now takes the two-level scan if it can, it still does not
+    refuse or use such a workspace."""
+    x = synth.random_chain(150, 100, 64, dtype="bf16", seed=96)
+    g = x.to(DEV)
+    want = binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=CHAIN)
+    got = binding.lbi_scan_backward(g.A, g.b, g.lamK, workspace=g.A.view(torch.uint8).flatten())
+    assert torch.equal(got, want)
+    need = binding.lbi_scan_backward_workspace_bytes(150, 100, 64, 1)
+    ws = torch.empty((need,), dtype=torch.uint8, device=DEV)
+    lam = ws[:4 * want.numel()].view(torch.float32).view_as(want)
+    assert torch.equal(binding.lbi_scan_backward(g.A, g.b, g.lamK, lam=lam, workspace=ws), want)
+
+
 def test_auto_hint_keeps_the_chain_scan():
     """bf16 chains at r = 128, as many as the cost model leaves to the chain scan: they
     run it with and without a widths hint, on the LDS-ring kernel for widths that it

@@ -308,9 +308,7 @@ bool two_level_by_size(int64_t B, int64_t K, int32_t r, lbi_dtype dt, bool aff)
     static const double bf16[4][2] = {{1350, 55}, {530, 36}, {222, 14}, {104, 9}};
     static const double bf16_noaff[4][2] = {{1700, 80}, {500, 45}, {190, 16}, {104, 9}};
     const double *c = dt != LBI_BF16 ? f32[i] : (aff ? bf16[i] : bf16_noaff[i]);
-    if (!((double)B <= c[0] * (1.0 - c[1] / (double)K)))
-        return false;
-    return !(dt == LBI_BF16 && r == 128) || two_level_by_model(B, K, r, dt);
+    return (double)B <= c[0] * (1.0 - c[1] / (double)K);
 }
 
 bool default_math(lbi_math math)
@@ -318,39 +316,46 @@ bool default_math(lbi_math math)
     return math != LBI_MATH_F32_MFMA && math != LBI_MATH_BF16_SINGLE;
 }
 
-// LBI_ALGO_AUTO.
-// Chains that the two-level scan does not take: bf16 chains of width <= 32
-// go to the wavefront-per-chain kernel (no barrier, no LDS staging), which
-// measured 1.3-1.9x faster than the workgroup kernel up to B = 4096 and no
-// slower up to 8192; at r = 64 its registers allow two waves per SIMD and the
-// workgroup kernel is faster.  fp32 chains at r = 64 in the split arithmetic,
+// Whether AUTO takes the two-level scan: not, where there is workspace for it (an
+// offer), or in any case.
+enum class TwoLevel { no, offer, yes };
+TwoLevel two_level_choice(int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math, bool aff)
+{
+    if (!default_math(math))
+        return two_level_by_model(B, K, r, dt) ? TwoLevel::yes : TwoLevel::no;
+    if (!two_level_by_size(B, K, r, dt, aff))
+        return TwoLevel::no;
+    if (two_level_by_model(B, K, r, dt))
+        return TwoLevel::yes;
+    return dt == LBI_BF16 && r == 128 ? TwoLevel::no : TwoLevel::offer;
+}
+
+// LBI_ALGO_AUTO's choice among the scans that need no workspace.
+// A chain that fits one tree chunk (at r <= 32) is one tree launch: kernel
+// times on MI355X (rocprofv3, B = 1..256) put it ahead of the chain
+// kernels there, about twice as fast for fp32 at K = 16 (6.4 against
+// 12.7 us at r = 32), for bf16 only past K = 8 (at smaller K the
+// wavefront-per-chain kernel is as fast or faster); at r = 64 the chain
+// kernels win.
+// Other chains: bf16 of width <= 32 goes to the wavefront-per-chain kernel (no
+// barrier, no LDS staging), which measured 1.3-1.9x faster than the workgroup
+// kernel up to B = 4096 and no slower up to 8192; at r = 64 its registers allow
+// two waves per SIMD and the workgroup kernel is faster.  fp32 chains at r = 64 in the split arithmetic,
 // at most one per CU, go to the sixteen-wave kernel (split contraction,
 // specialised staging waves): 1.2-1.3x faster than the workgroup kernel for
 // B <= 128 and 1.07-1.2x at B = 256, and slower once chains share CUs.
-// (no_two_level: the choice among the rest)
-lbi_algo resolve_algo(lbi_algo algo, int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math,
-                      bool aff, bool no_two_level = false)
+bool auto_tree(int64_t B, int64_t K, int32_t r, lbi_dtype dt, lbi_math math)
 {
-    if (algo != LBI_ALGO_AUTO)
-        return algo;
-    // one launch of the tree scan (K within a chunk) at r <= 32: kernel
-    // times on MI355X (rocprofv3, B = 1..256) put it ahead of the chain
-    // kernels there, about twice as fast for fp32 at K = 16 (6.4 against
-    // 12.7 us at r = 32), for bf16 only past K = 8 (at smaller K the
-    // wavefront-per-chain kernel is as fast or faster); at r = 64 the chain
-    // kernels win
-    if (r <= 32 && B <= (dt == LBI_F32 && K >= 12 ? kTreeLongMaxB : kTreeMaxB) &&
-        K <= tree_chunk(r) && default_math(math) &&
-        K >= (dt == LBI_F32 ? 5 : 9))
-        return LBI_ALGO_TREE;
-    const lbi_algo chain =
-        dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r <= 32 && B <= 8192 ? LBI_ALGO_CHAIN_WAVE
-        : dt == LBI_F32 && math != LBI_MATH_F32_MFMA && r == 64 && B <= kSplitKMaxB
-            ? LBI_ALGO_CHAIN_SPLITK
-            : LBI_ALGO_CHAIN;
-    const bool two = !no_two_level && (default_math(math) ? two_level_by_size(B, K, r, dt, aff)
-                                                          : two_level_by_model(B, K, r, dt));
-    return two ? LBI_ALGO_TWO_LEVEL : chain;
+    return r <= 32 && B <= (dt == LBI_F32 && K >= 12 ? kTreeLongMaxB : kTreeMaxB) &&
+           K <= tree_chunk(r) && default_math(math) && K >= (dt == LBI_F32 ? 5 : 9);
+}
+lbi_algo auto_chain(int64_t B, int32_t r, lbi_dtype dt, lbi_math math)
+{
+    return dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r <= 32 && B <= 8192
+               ? LBI_ALGO_CHAIN_WAVE
+           : dt == LBI_F32 && math != LBI_MATH_F32_MFMA && r == 64 && B <= kSplitKMaxB
+               ? LBI_ALGO_CHAIN_SPLITK
+               : LBI_ALGO_CHAIN;
 }
 
 bool valid_algo(lbi_algo algo)
@@ -511,8 +516,12 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
         return LBI_ERR_UNSUPPORTED_R;
     if (algo == LBI_ALGO_CHAIN_RING && (dt != LBI_BF16 || math == LBI_MATH_BF16_SINGLE))
         return LBI_ERR_DTYPE;
-    if (algo == LBI_ALGO_CHAIN_RING && !ring_plan(widths, K, r).ok)
-        return LBI_ERR_SHAPE;
+    RingPlan rp{false, 0, 0};
+    if (algo == LBI_ALGO_CHAIN_RING) {
+        rp = ring_plan(widths, K, r);
+        if (!rp.ok)
+            return LBI_ERR_SHAPE;
+    }
     if (B == 0)
         return LBI_OK;
     if (!A || !lamK || !lam)
@@ -524,25 +533,31 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
     const size_t nl = (size_t)B * r * esz, nout = (size_t)B * K * r * sizeof(float);
     if (overlaps(lam, nout, A, nA) || overlaps(lam, nout, b, nb) || overlaps(lam, nout, lamK, nl))
         return LBI_ERR_ALIAS;
-    const bool ring = dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r == 128 &&
-                      ring_plan(widths, K, r).ok;
-    lbi_algo use = resolve_algo(algo, B, K, r, dt, math, b != nullptr);
-    // A two-level scan that the model would not take is an offer: without a
-    // workspace that it can use, the chain scan.  The library's one scratch array is shared by
-    // every call on a GPU and is not offered: calls that need none stay independent.
-    if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_TWO_LEVEL && !two_level_by_model(B, K, r, dt)) {
-        const size_t n = two_level_plan(B, K, r, dt, math).bytes;
-        if (scratch || !ws || ws_bytes < n || overlaps(ws, n, A, nA) || overlaps(ws, n, b, nb) ||
-            overlaps(ws, n, lamK, nl) || overlaps(ws, n, lam, nout))
-            use = resolve_algo(algo, B, K, r, dt, math, b != nullptr, true);
-    }
-    // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes
-    // (the mixed-width case): that kernel, measured 1.45x faster there than
-    // the workgroup kernel (188 against 275 us on 1024 chains of 64 slots of
-    // widths 32/64/128); at width 64 the two tie
-    if (algo == LBI_ALGO_AUTO && use == LBI_ALGO_CHAIN && ring)
-        use = LBI_ALGO_CHAIN_RING;
     TwoLevelPlan p = two_level_plan(B, K, r, dt, math);
+    lbi_algo use = algo;
+    if (algo == LBI_ALGO_AUTO) {
+        // An offer is taken up where the caller's workspace can be used.  The
+        // library's one scratch array is shared by every call on a GPU and is not
+        // offered: calls that need none stay independent.
+        const TwoLevel two =
+            auto_tree(B, K, r, dt, math) ? TwoLevel::no : two_level_choice(B, K, r, dt, math, b != nullptr);
+        const bool usable = !scratch && ws && ws_bytes >= p.bytes &&
+                            !overlaps(ws, p.bytes, A, nA) && !overlaps(ws, p.bytes, b, nb) &&
+                            !overlaps(ws, p.bytes, lamK, nl) && !overlaps(ws, p.bytes, lam, nout);
+        use = auto_tree(B, K, r, dt, math) ? LBI_ALGO_TREE
+              : two == TwoLevel::yes || (two == TwoLevel::offer && usable)
+                  ? LBI_ALGO_TWO_LEVEL
+                  : auto_chain(B, r, dt, math);
+        // bf16 chains stored at width 128 whose widths the LDS-ring kernel takes
+        // (the mixed-width case): that kernel, measured 1.45x faster there than
+        // the workgroup kernel (188 against 275 us on 1024 chains of 64 slots of
+        // widths 32/64/128); at width 64 the two tie
+        if (use == LBI_ALGO_CHAIN && dt == LBI_BF16 && math != LBI_MATH_BF16_SINGLE && r == 128) {
+            rp = ring_plan(widths, K, r);
+            if (rp.ok)
+                use = LBI_ALGO_CHAIN_RING;
+        }
+    }
     size_t need = use == LBI_ALGO_TWO_LEVEL
                       ? p.bytes
                       : lbi_scan_backward_workspace_bytes_ex(B, K, r, dt, use);
@@ -586,7 +601,6 @@ lbi_status scan_impl(const void *A, const void *b, const void *lamK, float *lam,
         return run_tree(A, b, lamK, lam, B, K, r, dt, ws, c.stream) == hipSuccess ? LBI_OK
                                                                                   : LBI_ERR_HIP;
     if (use == LBI_ALGO_CHAIN_RING) {
-        const RingPlan rp = ring_plan(widths, K, r);
         c.args.lam = lam;
         c.args.L = K;
         c.args.S = 1;
@@ -878,7 +892,8 @@ size_t lbi_scan_backward_workspace_bytes_ex(int64_t B, int64_t K, int32_t r, lbi
         return 0;
     // AUTO: enough for the choice in every arithmetic
     if (algo == LBI_ALGO_AUTO)
-        return two_level_by_size(B, K, r, dt, true) || two_level_by_size(B, K, r, dt, false) ||
+        return two_level_choice(B, K, r, dt, LBI_MATH_DEFAULT, true) != TwoLevel::no ||
+                       two_level_choice(B, K, r, dt, LBI_MATH_DEFAULT, false) != TwoLevel::no ||
                        two_level_by_model(B, K, r, dt)
                    ? two_level_bytes(B, K, r, dt)
                    : 0;

@@ -177,6 +177,20 @@ template <int N> __device__ __forceinline__ void dma_barrier()
     __builtin_amdgcn_s_barrier();
 }
 
+// this wave's loads done, and no memory operation moved over the wait
+__device__ __forceinline__ void dma_wait()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((15) << 8 | (7 << 4));
+    asm volatile("" ::: "memory");
+}
+// this wave's LDS operations done; then the workgroup barrier
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
+    __builtin_amdgcn_s_barrier();
+}
+
 // acc += A_tile(128 x 64) B_tile(128 x 64)^T for this wave's 64 x 64 quarter
 // (waves 2 x 2; acc[i][j] is the 16 x 16 block (i, j); lane l holds rows
 // 4 (l / 16) + v, column l % 16 of it)
@@ -1151,7 +1165,7 @@ __global__ __launch_bounds__(kT) void ssm_s_kernel(RegionArgs q, int64_t p0)
 // lds_off, and each lane loads the global chunk that its LDS slot holds.
 //
 // A workgroup per CU takes one tile after another, and a tile's first stage
-// loads while the tile before it is weighted and stored: with a workgroup per
+// loads beside the last products of the tile before it: with a workgroup per
 // tile, its start, the latency of that first stage and of the weights, and the
 // end of its stores came on top of every tile.  The weights of a tile (the rows
 // of a [tokens][columns] fp32 array, 16 KB at most) load into LDS beside the
@@ -1170,11 +1184,9 @@ constexpr int kDLds = 2 * kDStage + kDWeights;
 // A tile: resources of its operands' rows (ending at the last valid row, so no
 // load leaves them; the epilogues do not rely on what the products of rows past
 // it hold) and of its weights (from the tile's first token and column, rows ldw
-// bytes apart), and whether its epilogue issues at least AFTER memory operations
-// in this wave (the wait for the next tile's first stage then counts past them).
+// bytes apart).
 struct DTile {
     i4 rsA, rsB, rsW;
-    bool many;
 };
 
 // x, as a value that the compiler does not know to be the same in every tile: an
@@ -1188,7 +1200,7 @@ __device__ __forceinline__ int fresh(int x)
 
 // The tiles i = blockIdx.x, + gridDim.x, ... below n: setup(i) gives the tile,
 // epilogue(i, acc) weights and stores it.
-template <int AFTER, typename Setup, typename Epi>
+template <typename Setup, typename Epi>
 __device__ __forceinline__ void dtile_loop(int64_t n, int K, int tokens, int ldw, int w, int lane,
                                            uint32_t lbase, Setup &&setup, Epi &&epilogue)
 {
@@ -1224,8 +1236,8 @@ __device__ __forceinline__ void dtile_loop(int64_t n, int K, int tokens, int ldw
         return;
     DTile cur = setup(i);
     issue(cur, 0, 0);
-    int buf = 0;          // of the tile's next stage
-    bool counted = false; // AFTER operations follow the stage of the loop's first wait
+    int buf = 0;  // of the tile's next stage
+    bool landed = false;  // this wave's share of it has arrived
     for (;;) {
         const int64_t inext = i + gridDim.x;
         f4 acc[8][4];
@@ -1237,8 +1249,8 @@ __device__ __forceinline__ void dtile_loop(int64_t n, int K, int tokens, int ldw
         DTile next = cur;
         for (int t = 0; t < nk; ++t) {
             // stage t complete; stage t - 1 (or the last tile's) read by every wave
-            if (t == 0 && counted)
-                dma_barrier<AFTER>();
+            if (t == 0 && landed)
+                lds_barrier();
             else
                 dma_barrier<0>();
             if (t == 0)
@@ -1278,12 +1290,17 @@ __device__ __forceinline__ void dtile_loop(int64_t n, int K, int tokens, int ldw
             __builtin_amdgcn_sched_group_barrier(0x100, 24, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 64, 0);
         }
+        // The next tile's first stage (and, with one stage, the weights) before the
+        // epilogue's own memory operations: it was issued a stage of products ago, and
+        // a wait behind the stores would have to know how many the compiler made.
         if (nk == 1)
-            dma_barrier<0>();  // the weights
+            dma_barrier<0>();
+        else
+            dma_wait();
+        landed = true;
         epilogue(i, acc);
         if (inext >= n)
             return;
-        counted = cur.many && nk > 1;
         cur = next;
         i = inext;
     }
@@ -1316,8 +1333,7 @@ __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         return DTile{dma_rsrc(a.S + (t.z * Lr + t.row0) * D, (uint32_t)vA * D * 2),
                      dma_rsrc(a.W1 + (k * a.X + t.col0) * D, (uint32_t)vB * D * 2),
                      dma_rsrc(a.g32 + (t.z * a.L + l0) * a.X + t.col0,
-                              (uint32_t)((((vA - 1) >> a.rs) * a.X + vB) * 4)),
-                     vA == 256 && vB == 256};
+                              (uint32_t)((((vA - 1) >> a.rs) * a.X + vB) * 4))};
     };
     // (a 16-row block is one token: r is a multiple of 16)
     const int wm = w >> 2, wn = w & 3;
@@ -1370,7 +1386,7 @@ __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         }
     };
-    dtile_loop<32>(a.ntiles, D, 256 >> a.rs, a.X * 4, w, lane, lbase, setup, epilogue);
+    dtile_loop(a.ntiles, D, 256 >> a.rs, a.X * 4, w, lane, lbase, setup, epilogue);
 }
 
 // ---- tok_dma: the second tangent product (TokArgs above) -------------------------
@@ -1410,8 +1426,7 @@ __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         return DTile{dma_rsrc(a.Vt + (t.z * Lr + t.row0) * a.X, (uint32_t)vA * a.X * 2),
                      dma_rsrc(a.W2 + (k * a.D + t.col0) * a.X, (uint32_t)vB * a.X * 2),
                      dma_rsrc(a.s32 + (t.z * a.L + l0) * a.D + t.col0,
-                              (uint32_t)((((vA - 1) >> RS) * a.D + vB) * 4)),
-                     RS >= 6 && vA == 256 && vB == 256 && wm == 0};
+                              (uint32_t)((((vA - 1) >> RS) * a.D + vB) * 4))};
     };
     const int nk = a.X / BK;
     int done = 0;  // tiles finished: the last stage of tile t was in buffer (t + 1) nk - 1 mod 2
@@ -1477,7 +1492,7 @@ __global__ __launch_bounds__(kDT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         }
     };
-    dtile_loop<63>(a.ntiles, a.X, 256 >> RS, a.D * 4, w, lane, lbase, setup, epilogue);
+    dtile_loop(a.ntiles, a.X, 256 >> RS, a.D * 4, w, lane, lbase, setup, epilogue);
 }
 
 // ---- tfin: dp^T[pair][j][d] = Jdec^T (1 + w[d]) + (1/L) sum_c Tpart[z][c][j][d] ----

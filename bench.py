@@ -165,9 +165,7 @@ def mfma_flops_executed(wl, math: str) -> int:
 def mode_of(wl, math: str) -> str:
     if wl.dtype == "bf16":
         return "bf16-single" if math == "bf16single" else "bf16"
-    if math == "split" and wl.r <= 64:
-        return "f32-split"
-    return "f32-mfma"
+    return "f32-split" if math == "split" else "f32-mfma"
 
 
 def scan_payload_bytes(K: int, r: int, elem: int) -> int:
@@ -257,15 +255,39 @@ def load_traffic(workload: str):
     return rec.get("hbm_bytes_per_launch")
 
 
-def norms_record(wl, args, total_ms, avg_launch_s, per_launch_ms, ncopy) -> dict:
+def norm_products(singular_values) -> int:
+    """Matrix products that the norms kernel forms for a matrix with these
+    singular values: the Gram product, and normalised squarings H <- (H / tr H)^2
+    until the trace of the new H is at least 1 - 2^-8, at most 24."""
+    u = [float(s) ** 2 for s in singular_values]
+    count = 1
+    for t in range(24):
+        tr = sum(u)
+        if (t > 0 and tr >= 1.0 - 2.0 ** -8) or not tr > 0.0:
+            break
+        u = [(x / tr) ** 2 for x in u]
+        count += 1
+    return count
+
+
+def norms_record(wl, args, total_ms, avg_launch_s, per_launch_ms, ncopy, sample) -> dict:
     """JSON line of the --op norms run: spectral + Frobenius norms of every
-    r x r tile of A.  Bytes: the A stack read twice (norms, then the Rayleigh
-    quotient's matrix-vector product) and two floats written per matrix.  The
-    matrix-core work depends on the spectrum (the squarings end when the
-    leading vector stands out), so the roofline is the traffic's."""
+    r x r tile of A.  Executed matrix-core work: each product is six bf16 partial
+    products (k in blocks of 32); their number depends on the spectrum and is
+    averaged over ``sample``, some of the matrices.  Bytes: the A stack read twice
+    (norms, then the Rayleigh quotient's matrix-vector product) and two floats
+    written per matrix."""
+    import torch
+
     n = wl.B * wl.K
+    sv = torch.linalg.svdvals(sample.double().cpu().reshape(-1, wl.r, wl.r)).tolist()
+    products = sum(norm_products(s) for s in sv) / len(sv)
+    f_exec = n * products * 6 * 2.0 * wl.r * wl.r * max(wl.r, 32)
     b_alg = 2.0 * n * wl.r * wl.r * ELEM[wl.dtype] + 8.0 * n
-    ach = b_alg / avg_launch_s / 1e9
+    peak = PEAK["mfma_bf16_tflops"]
+    t_mfma, t_hbm = f_exec / (peak * 1e12), b_alg / (PEAK["hbm_gbs"] * 1e9)
+    ach, hbm = f_exec / avg_launch_s / 1e12, b_alg / avg_launch_s / 1e9
+    mfma = t_mfma >= t_hbm
     return {
         "metric": "interface-Jacobian norms/sec (spectral + Frobenius, appendix statistics)",
         "value": n * args.steps / (total_ms / 1e3),
@@ -283,11 +305,14 @@ def norms_record(wl, args, total_ms, avg_launch_s, per_launch_ms, ncopy) -> dict
         "config": {"workload": wl.name, "B": wl.B, "K": wl.K, "r": wl.r, "storage": wl.dtype,
                    "op": "norms", "parallelism": "1 GPU, one wavefront per matrix"
                    if wl.r <= 64 else "1 GPU, one workgroup per matrix"},
-        "roofline": {"bound": "hbm", "achieved": ach, "peak": PEAK["hbm_gbs"], "unit": "GB/s",
-                     "frac": ach / PEAK["hbm_gbs"], "traffic": None},
+        "roofline": {"bound": "mfma" if mfma else "hbm", "achieved": ach if mfma else hbm,
+                     "peak": peak if mfma else PEAK["hbm_gbs"],
+                     "unit": "TFLOP/s" if mfma else "GB/s",
+                     "frac": ach / peak if mfma else hbm / PEAK["hbm_gbs"], "traffic": None},
         "extra": {"avg_launch_ms": avg_launch_s * 1e3, "min_launch_ms": min(per_launch_ms),
-                  "ideal_ms_hbm": b_alg / (PEAK["hbm_gbs"] * 1e9) * 1e3,
-                  "input_copies_rotated": ncopy},
+                  "products_per_matrix": products, "matrices_sampled": len(sv),
+                  "executed_mfma_tflops": ach, "ideal_ms_mfma": t_mfma * 1e3,
+                  "hbm_gbs": hbm, "ideal_ms_hbm": t_hbm * 1e3, "input_copies_rotated": ncopy},
     }
 
 
@@ -769,7 +794,8 @@ def measure(wl, op, layout, math_name, algo_name, steps, warmup, chunk, torch, b
             pass
         na = _A()
         na.steps, na.warmup = steps, nwarm
-        return norms_record(wl, na, total_ms, avg_launch_s, per_launch_ms, ncopy), x
+        sample = x.A.reshape(-1, wl.r, wl.r)[::max(1, wl.B * wl.K // 256)][:256]
+        return norms_record(wl, na, total_ms, avg_launch_s, per_launch_ms, ncopy, sample), x
     value = combines(wl) * steps / (total_ms / 1e3)
     f_alg = flops_combines(wl) if op == "suffix_products" else flops_alg(wl)
     mapping = chain_mapping(wl, op, layout, math_name, algo_name, need)

@@ -59,9 +59,37 @@ def test_mode_names():
     bf = synth.WORKLOADS["bf16_tokens"]
     assert bench.mode_of(f32, "split") == "f32-split"
     assert bench.mode_of(f32, "mfma") == "f32-mfma"
-    assert bench.mode_of(f32.with_(r=128), "split") == "f32-mfma"
+    assert bench.mode_of(f32.with_(r=128), "split") == "f32-split"
+    assert bench.mode_of(f32.with_(r=128), "mfma") == "f32-mfma"
     assert bench.mode_of(bf, "split") == "bf16"
     assert bench.mode_of(bf, "bf16single") == "bf16-single"
+
+
+def test_norm_products():
+    # one leading value: the Gram product, one squaring (its trace is 1)
+    assert bench.norm_products([1.0, 0.0, 0.0, 0.0]) == 2
+    # r equal values never stand out: all 24 squarings
+    assert bench.norm_products([0.7] * 16) == 25
+    assert bench.norm_products([0.0] * 16) == 1  # nothing to square
+    # 2 : 1, weights 4 : 1 in the Gram matrix: the traces are 0.68, 0.889, 0.9922 and,
+    # after the fourth squaring, past 1 - 2^-8
+    assert bench.norm_products([2.0, 1.0]) == 1 + 4
+
+
+def test_norms_record_is_bound_by_the_matrix_cores():
+    import argparse
+
+    import torch
+
+    wl = synth.WORKLOADS["long_chain"].with_(B=2, K=4)
+    args = argparse.Namespace(steps=1, warmup=0)
+    sample = torch.eye(64).expand(3, 64, 64)
+    rec = bench.norms_record(wl, args, 1.0, 1e-3, [1.0], 1, sample)
+    assert rec["roofline"]["bound"] == "mfma" and rec["roofline"]["unit"] == "TFLOP/s"
+    assert rec["extra"]["products_per_matrix"] == 25
+    work = 8 * 25 * 6 * 2 * 64 ** 3 / 1e-3 / 1e12
+    assert rec["roofline"]["achieved"] == pytest.approx(work)
+    assert rec["roofline"]["frac"] == pytest.approx(work / bench.PEAK["mfma_bf16_tflops"])
 
 
 def test_more_than_one_gpu_is_refused(capsys):

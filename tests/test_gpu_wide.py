@@ -70,6 +70,38 @@ def test_wide_segments_and_products(B, K):
     assert oracle.rel_frobenius(c.cpu().numpy().astype(np.float64), cr) <= TOL
 
 
+@pytest.mark.parametrize("affine", [True, False])
+@pytest.mark.parametrize("cycle", CYCLES, ids=["-".join(map(str, c)) for c in CYCLES])
+def test_wide_hinted_products(cycle, affine):
+    """The exported composites with narrow widths: slots of one to four panels and row
+    blocks of every number, bit for bit the unhinted ones."""
+    K = 14
+    widths = synth.cyclic_widths(K, cycle)
+    x = synth.random_chain(3, K, 128, seed=83, widths=widths, affine=affine)
+    g = x.to(DEV)
+    P, c = binding.lbi_scan_suffix_products(g.A, g.b)
+    Ph, ch = binding.lbi_scan_suffix_products(g.A, g.b, widths=list(widths))
+    assert torch.equal(P, Ph) and torch.equal(c, ch)
+    Pr, cr = oracle.suffix_composites(x.A, x.b)
+    assert oracle.rel_frobenius(Ph.cpu().numpy().astype(np.float64), Pr) <= TOL
+    if affine:
+        assert oracle.rel_frobenius(ch.cpu().numpy().astype(np.float64), cr) <= TOL
+
+
+@pytest.mark.parametrize("cycle", [(32, 64, 128), (112, 48, 16, 80)])
+def test_wide_hinted_segments(cycle):
+    """Segments that are scanned again from their carries (70 x 128: past 256 MiB of
+    composites), with segment ends of every width of the cycle."""
+    B, K = 70, 128
+    widths = synth.cyclic_widths(K, cycle)
+    x = synth.random_chain(B, K, 128, seed=84, widths=widths)
+    g = x.to(DEV)
+    two = binding.LBI_ALGO_TWO_LEVEL
+    lam = binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, list(widths), algo=two)
+    assert _err(lam, x) <= TOL
+    assert torch.equal(lam, binding.lbi_scan_backward_ex(g.A, g.b, g.lamK, algo=two))
+
+
 # A chain's tiles times 2^-e (per slot), and a value planted at row 5, column 7 of a
 # tile: what the three-part split cannot hold (infinities, NaN, magnitudes that round
 # to an infinity in bf16, values that keep bits below 2^-133).  The finite results

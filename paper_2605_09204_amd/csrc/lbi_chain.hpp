@@ -527,7 +527,12 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
     };
     // b_j at the row this lane owns after the staging reduce (raw bits: a bf16
     // value is moved into the upper half where it is used; beside the load that
-    // shift waited for memory in every slot)
+    // shift waits for memory in every slot).  Composites written at R = 32 are the
+    // exception: loads and stores complete in order, and the wait keeps two waves'
+    // stores from piling up (export of 200 slots, shift at use / at the load, us:
+    // 200 chains 114 / 109, 444 226 / 196, 600 232 / 206, 2000 x 75 207 / 207; R = 64 248
+    // / 249, R = 128 198 / 197).
+    constexpr bool kShiftAtLoad = OUT == kOutComposite && R == 32;
     auto load_b = [&](int64_t j, bool valid, int wr) -> uint32_t {
         if constexpr (AFF) {
             int nrow = R, soff = 0;
@@ -547,7 +552,8 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
             if constexpr (G::ESZ == 4)
                 return __builtin_amdgcn_raw_buffer_load_b32(rs, off, soff, 0);
             else
-                return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, soff, 0);
+                return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, soff, 0)
+                       << (kShiftAtLoad ? 16 : 0);
         } else {
             return 0u;
         }
@@ -619,7 +625,7 @@ __global__ __launch_bounds__(64 * waves_for(R)) void scan_chain_kernel(const Sca
         if constexpr (AFF) {
             group_reduce<LPR, CPT>(st_part, sgi);
             if (oown)
-                sC[ring(j)][orow] = st_part[0] + bitsf(G::ESZ == 4 ? braw : braw << 16);
+                sC[ring(j)][orow] = st_part[0] + bitsf(G::ESZ == 4 || kShiftAtLoad ? braw : braw << 16);
         }
     };
     auto stage = [&](const u4 (&src)[CPT], int buf, uint32_t braw, int64_t j, bool first,

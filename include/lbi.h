@@ -84,7 +84,12 @@ typedef enum {
     LBI_MATH_F32_SPLIT = 2, /* fp32 products from exact three-part bf16 splits
                              * of both operands on the bf16 matrix cores (the
                              * six partial products down to 2^-16 of the leading
-                             * one), fp32 accumulation                           */
+                             * one), fp32 accumulation.  At r = 128 over the
+                             * whole float32 range: what the splits cannot hold
+                             * is done again as LBI_MATH_F32_MFMA does it.  At
+                             * r <= 64 an infinity, or a magnitude from 3.396e38
+                             * on, gives NaN, and values below 2^-110 keep only
+                             * their bits from 2^-133 up                         */
     LBI_MATH_BF16_SINGLE = 3 /* bf16 inputs only (else LBI_ERR_DTYPE) and
                              * K <= LBI_BF16_SINGLE_MAX_K (else
                              * LBI_ERR_SHAPE): the running composite is fed
@@ -266,7 +271,10 @@ size_t lbi_scan_backward_workspace_bytes_ex(int64_t B, int64_t K, int32_t r, lbi
  * LBI_BF16 multiplies bf16 operands on the matrix cores with float32
  * accumulation; the running float32 composite is fed back as a two-term bf16
  * split (hi + lo), so only the inputs are bf16-rounded.  Results are bitwise
- * reproducible run to run for a given (B, K, r, dt, math).
+ * reproducible run to run for the same call: (B, K, r, dt, math), with or
+ * without b, the same widths hint, and the same answer to whether there is a
+ * workspace of the size that the query names (without one, LBI_ALGO_AUTO may
+ * run another scan, whose sums are rounded in another order).
  */
 lbi_status lbi_scan_backward(const void *A, const void *b, const void *lambda_K,
                              float *lambda, int64_t B, int64_t K, int32_t r, lbi_dtype dt,
@@ -278,8 +286,10 @@ lbi_status lbi_scan_backward(const void *A, const void *b, const void *lambda_K,
  * Backpropagation").  widths_host is a HOST array of K+1 entries in [1, r],
  * or NULL (then this is lbi_scan_backward).  The caller zero-pads A, b and
  * lambda_K to r; the hint only lets the kernels skip all-zero tiles, so the
- * results equal the unhinted call's.  For K > LBI_MAX_HINT_K the hint is
- * ignored.  Padded output lanes (rows >= r_j of lambda_j) are exactly 0.
+ * results equal the unhinted call's: bit for bit, except where the hint is one
+ * that LBI_ALGO_CHAIN_RING takes and the call runs that kernel, whose sums are
+ * rounded in another order.  For K > LBI_MAX_HINT_K the hint is ignored.
+ * Padded output lanes (rows >= r_j of lambda_j) are exactly 0.
  */
 lbi_status lbi_scan_backward_widths(const void *A, const void *b, const void *lambda_K,
                                     float *lambda, int64_t B, int64_t K, int32_t r,

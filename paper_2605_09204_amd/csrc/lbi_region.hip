@@ -1170,10 +1170,11 @@ __global__ __launch_bounds__(kT) void ssm_s_kernel(RegionArgs q, int64_t p0)
 // end of its stores came on top of every tile.  The weights of a tile (the rows
 // of a [tokens][columns] fp32 array, 16 KB at most) load into LDS beside the
 // second stage.  2 sequences x 4 regions, L 1024, D 768, X 1536, r 64: gen_dma
-// 1448 -> 1391 us, tok_dma 1250 -> 1140, the call 3074 -> 2890.  Both are held
-// by the operands' way from L2 to LDS: 64 KB per stage and CU are 9.6 TB/s of L2
-// reads, the matrix cores 43% and 52% busy; reading half a stage ahead of the
-// products, or other row pitches of S and Vt, changed nothing.
+// 1448 -> 1391 us, tok_dma 1250 -> 1140, the call 3074 -> 2890.  The
+// matrix cores are 44% and 56% busy, and 64 KB per stage and CU come from L2 at 7.1
+// and 8.0-8.7 TB/s, which is not its limit (region_dma reads 13.8): a stage takes
+// 2.0-2.4 us with one in flight.  Reading half a stage ahead of the products, other
+// row pitches of S and Vt, and four stages of half the depth did not help.
 constexpr int kDT = 512;                  // threads
 constexpr int kDOp = 256 * BK * 2;        // bytes of one operand's stage (32 KB)
 constexpr int kDStage = 2 * kDOp;         // A and B

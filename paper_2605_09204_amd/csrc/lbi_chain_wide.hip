@@ -29,18 +29,21 @@
 //   * Range.  Three bf16 parts hold an fp32 value to its last bit from 2^-110 up
 //     to where it rounds to an infinity in bf16 (about 3.396e38); an infinity, or
 //     a value past that, leaves NaN parts, and a smaller one keeps only its bits
-//     from 2^-133 up.  A segment in which that can show is done again from its
-//     end on the fp32 matrix cores (exact_pass), so the kernel's results are those
-//     of float32 products over float32's whole range.  What shows it, with lambda:
-//     a row of P_s lambda_K that is not finite, or not zero and below 2^-96 of
-//     the largest entry of lambda_K or of the same row at s + 1 (what was lost is
-//     otherwise below 2^-29 of every row).  With composites, the largest magnitude
-//     of a quarter column of P_s (a lane's): 2^126 or more, or not zero and below
-//     2^-96, or below 2^-96 of the quarter's at s + 1; and a NaN in the segment's
-//     last composite.  The checks cost up to 2% of a lambda pass and 5% of a hinted composite pass; a
-//     segment done again takes about 11 us a slot (scan_chain_kernel on the fp32
-//     matrix cores 9), on top of the slots up to what showed the loss: 64 chains of
-//     200 slots that halve at each one 2.67 ms against 1.78.
+//     from 2^-133 up.  A P that fades is scaled by 2^64 long before that (but for
+//     lambda with a hint).  A segment in which a loss can show is done again from
+//     its end on the fp32 matrix cores (exact_pass), so the kernel's results are
+//     those of float32 products over float32's whole range.  What shows it, with
+//     lambda: a row of lambda_s that is not finite, or not zero and below 2^-96 of
+//     the largest entry of lambda_K (until P is scaled) or of the same row at s + 1
+//     (what was lost is otherwise below 2^-29 of every row; a P_s that fades beside
+//     affine terms needs neither).  With composites, the largest magnitude of a
+//     quarter column of P_s (a lane's): 2^126 or more, or not zero and below 2^-96
+//     (until P is scaled) or below 2^-96 of the quarter's at s + 1; and a NaN in the
+//     segment's last composite.  The checks cost up to 3% of a lambda pass and 5% of
+//     a hinted composite pass.  64 chains of 200 slots that halve at each take what
+//     others take (0.94 ms; on the fp32 matrix cores 1.78).  A segment done again
+//     takes 11-12 us a slot (scan_chain_kernel on the fp32 matrix cores 9; widths
+//     32/64/128 without b, 512 x 400, which fade past 2^-96, 5.0 ms against 2.0).
 //
 // What bounds it: a slot is 384 MFMAs of 16 cycles per SIMD (2.6 us at the top
 // clock), with about 500 VALU instructions of the matrix wave beside them; with
@@ -75,6 +78,10 @@ __device__ __forceinline__ int panel_pos(int r, int q)
 
 // The range checks' bounds (see Range above).
 constexpr float kShow = 0x1p-96f, kFull = 0x1p126f;
+// Below kFade P is multiplied by kUp, once a segment, and what is formed from it by
+// kDown: a P that fades then stays in the split's range (float32 itself ends before
+// the scaled values leave it again).
+constexpr float kFade = 0x1p-64f, kUp = 0x1p64f, kDown = 0x1p-64f;
 
 // The three parts of a lane's B operand: 4 rows of two row blocks of P.
 struct Parts {
@@ -311,22 +318,30 @@ __device__ __forceinline__ void exact_pass(int32_t worst, int64_t npub, float (*
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     Q[I][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            // (with a hint, only A_{s-1}'s column blocks and halves of its row blocks)
             u4 a[2][8];
             load(a[0], 0);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
+                if (HINT && k >= wc)
+                    break;
                 if (k < 7)
                     load(a[(k + 1) & 1], k + 1);
                 // (here, a step of products ahead, and not later)
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
+                for (int h = 0; h < 8; h += 4) {
+                    if (HINT && h >= nr)
+                        break;
 #pragma unroll
-                    for (int I = 0; I < 8; ++I)
+                    for (int v = 0; v < 4; ++v)
 #pragma unroll
-                        for (int t = 0; t < NT; ++t)
-                            Q[I][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                bitsf(a[k & 1][I][v]), P[k][t][v], Q[I][t], 0, 0, 0);
+                        for (int I = h; I < h + 4; ++I)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+                                Q[I][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    bitsf(a[k & 1][I][v]), P[k][t][v], Q[I][t], 0, 0, 0);
+                }
             }
             // (with a hint, rows and columns that are not there stay zero: no zero
             // times an infinity)
@@ -353,11 +368,12 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     // entry s & 1
     __shared__ __attribute__((aligned(16))) float sC[4][kR];
     __shared__ __attribute__((aligned(16))) float sPart[OUT == kOutLambda ? 2 : 1][4][kR];
-    // range: the latest slot whose results show a loss (-1: none).  Entry j & 1 holds
-    // j when that was found in the loop's slot j; all waves read it in the next slot
-    // and end the loop with that one (with a hint they go on to the last slot: another
-    // way out of those loops costs them registers that they do not have)
-    __shared__ int32_t sWorst, sLost[2];
+    // range: the latest slot whose results show a loss (-1: none).  Entry j & 1 holds j
+    // when that was found in the loop's slot j, or ~j for a lambda below kFade of
+    // lambda_K; all waves read it in the next slot, and end the loop with that one, or
+    // scale P (with a hint they go on to the last slot: another way out of those loops
+    // costs them registers that they do not have)
+    __shared__ int32_t sWorst, sFound[2];
     __shared__ int64_t sNpub;  // (streaming) publications made
     __shared__ float sTop[2];  // the largest entry of lambda_K in each half
 
@@ -391,6 +407,9 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     // (writing composites, every row block is formed: the shapes of the product
     // do not fit the registers beside the stores)
     constexpr bool kShapes = HINT && OUT == kOutLambda;
+    // whether a fading P is scaled (kFade).  With a hint a lambda pass does such a
+    // segment again instead: reading the flag costs its short slots 8%.
+    constexpr bool kScales = OUT == kOutComposite || !HINT;
     // panels of a tile with wc column blocks; its row pitch in storage
     auto panels = [](int wc) { return HINT ? (wc + 1) >> 1 : kNP; };
     auto pitch = [](int wc) { return compact ? 16 * wc : kR; };
@@ -403,7 +422,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                              : ((const float *)args.lamK)[beta * rK + idx];
     };
     if (tid < 2)
-        sLost[tid] = -1;
+        sFound[tid] = -1;
     if (tid == 2)
         sWorst = -1;
     if (tid == 3)
@@ -419,6 +438,8 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 lk[t] = lambda_end(16 * (w + 4 * t) + li);
         }
         float *Pout = OUT == kOutComposite ? args.Pout + cslot * (int64_t)(kR * kR) : nullptr;
+        bool faded = false;  // P is scaled, and what is formed from it is taken times down
+        float down = 1.0f;
         // P_s, row blocks i0 .. i1 - 1, to global memory
         auto store_rows = [&](const f4(&P)[8][NT], int64_t s, int i0, int i1) {
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -430,7 +451,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         __builtin_amdgcn_raw_buffer_store_b32(
-                            fbits(P[I][t][v]), rs,
+                            fbits(P[I][t][v] * down), rs,
                             ((16 * I + 4 * g + v) * kR + 16 * (w + 4 * t) + li) * 4, 0, 0);
         };
         // P_s lambda over this wave's columns, rows 64 h .. 64 h + 63
@@ -443,7 +464,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     q[4 * I + v] = column_sum<NT>(P[4 * h + I], v, lk);
             group_reduce<16, 16>(q, li);
             // lane li holds value li (= 4 I + v)
-            sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0];
+            sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0] * down;
         };
         f4 P[8][NT];
         {
@@ -470,35 +491,49 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         int buf = 0;  // the panel's LDS buffer
         // (composites) the largest magnitudes in this lane's rows of P's two columns, of
         // the row blocks split so far, and of a slot later
-        float top[NT], before[NT];
+        float top[NT], before[NT], hard = kShow;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             top[t] = column_top(0.0f, P[0][t], P[1][t]);
             before[t] = 0.0f;
         }
         __syncthreads();
+        auto scale_up = [&](f4(&X)[8][NT]) {
+            faded = true;
+            down = kDown;
+#pragma unroll
+            for (int I = 0; I < 8; ++I)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    X[I][t] *= kUp;
+        };
         // the range check of the P whose row blocks are all in top, in the loop's slot j
-        // (-1: past it).  A NaN, which top leaves out, is in every row of every composite
-        // after it: the last slot's check finds it.
+        // (-1: past it); true if it fades.  A NaN, which top leaves out, is in every row
+        // of every composite after it: the last slot's check finds it.
         auto check_columns = [&](int64_t j, bool bad) {
+            bool fades = false;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const float c = top[t];
-                bad |= c >= kFull || (c > 0.0f && c < fmaxf(kShow, before[t] * kShow));
+                bad |= c >= kFull || (c > 0.0f && c < fmaxf(hard, before[t] * kShow));
+                fades |= c > 0.0f && c < kFade;
                 before[t] = c;
             }
             if (__builtin_expect(bad, 0)) {
                 sWorst = 0;
                 if (!HINT && j >= 0)
-                    sLost[j & 1] = (int32_t)j;
+                    sFound[j & 1] = (int32_t)j;
             }
+            if (faded)
+                hard = 0.0f;
+            return !faded && __any(fades);
         };
         // P_j (Pn) from P_{j+1} (P); b holds the split of P's first two row
         // blocks on entry, of Pn's on return
         int wr = blocks(K - 1), wnext = blocks(K - 2);
         // (true: the segment is to be done again)
         auto slot = [&](const f4(&P)[8][NT], f4(&Pn)[8][NT], int64_t j) {
-            int32_t lost = 0;
+            int32_t found = -1;
             const int wc = wr;
             [[maybe_unused]] const int np = panels(wc), nr = wnext;
             wr = wnext;
@@ -516,7 +551,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 const __bf16 *pan = sA[HINT ? buf : p & 1] + apos;
                 buf ^= 1;
                 if (!HINT && p == 0)
-                    lost = sLost[(j + 1) & 1];
+                    found = sFound[(j + 1) & 1];
                 Parts bn[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
@@ -564,15 +599,26 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 for (int t = 0; t < NT; ++t)
                     b[t] = bn[t];
             }
-            if constexpr (OUT == kOutComposite)
-                check_columns(j, false);
+            if constexpr (OUT == kOutComposite) {
+                if (__builtin_expect(check_columns(j, false), 0)) {
+                    scale_up(Pn);
+                    hard = kShow * kUp;  // of P_j, formed before it was scaled
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        before[t] *= kUp;
+                }
+            } else if (kScales &&
+                       __builtin_expect(
+                           !faded && __builtin_amdgcn_readfirstlane(found) == ~(int32_t)(j + 1), 0)) {
+                scale_up(Pn);
+            }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 b[t] = split_rows(Pn[0][t], Pn[1][t]);
                 if constexpr (OUT == kOutComposite)
                     top[t] = column_top(0.0f, Pn[0][t], Pn[1][t]);
             }
-            return !HINT && __builtin_amdgcn_readfirstlane(lost) == (int32_t)(j + 1);
+            return !HINT && __builtin_amdgcn_readfirstlane(found) == (int32_t)(j + 1);
         };
         auto last = [&](const f4(&X)[8][NT]) {
             __syncthreads();
@@ -732,7 +778,10 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         int32_t pub_left = args.pchunk;
         int64_t pub = -1;  // slots final once the next barrier is passed, or -1
         int64_t npub = 0;  // publications so far
-        float show = 0.0f, row = 0.0f;  // of the range check: from lambda_K, from slot s + 1
+        // of the range check: bounds from lambda_K (kFade of it, until P is scaled; kShow,
+        // for slots from `scaled` on) and from slot s + 1
+        float fade = 0.0f, show = 0.0f, row = 0.0f;
+        int32_t scaled = 0;
         // (j: the loop's slot, or -1 past it)
         auto finish = [&](int64_t s, int wr, int64_t j) {
             const int nrow = compact ? 16 * wr : kR;
@@ -748,11 +797,17 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     const float p = HINT && st >= 16 * wr ? 0.0f : sum;
                     if (st < nrow)
                         lam[st] = p + c;
-                    const float a = fabsf(p);
-                    if (__builtin_expect(!(a < kFull) || (a > 0.0f && a < fmaxf(show, row)), 0)) {
-                        atomicMax(&sWorst, (int32_t)s);
-                        if (!HINT && j >= 0)
-                            sLost[j & 1] = (int32_t)j;
+                    const float a = fabsf(p + c);
+                    const bool below = a > 0.0f && (a < row || (a < show && s >= scaled));
+                    if (__builtin_expect(!(a < kFull) || below || (kScales && a > 0.0f && a < fade),
+                                         0)) {
+                        if (!(a < kFull) || below) {
+                            atomicMax(&sWorst, (int32_t)s);
+                            if (!HINT && j >= 0)
+                                sFound[j & 1] = (int32_t)j;
+                        } else if (j >= 0) {
+                            sFound[j & 1] = ~(int32_t)j;
+                        }
                     }
                     row = a * kShow;
                 } else if (args.cout && (!args.agg_only || s == 0)) {
@@ -817,8 +872,10 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
             }
         }
         __syncthreads();
-        if constexpr (OUT == kOutLambda)
+        if constexpr (OUT == kOutLambda) {
+            fade = fmaxf(sTop[0], sTop[1]) * kFade;
             show = fmaxf(sTop[0], sTop[1]) * kShow;
+        }
         // wq[d]: blocks of slot j + 2 - d in the slot loop below
         int wq[NPF + 4];
 #pragma unroll
@@ -832,7 +889,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         auto slot = [&](u4(&cur)[kNP][4], u4(&next)[kNP][4], int64_t j) {
             const int np = panels(wq[1]);
             const int wnext = blocks(j - 2 - NPF);
-            int32_t lost = 0;
+            int32_t found = -1;
 #pragma unroll
             for (int p = 0; p < kNP; ++p) {
                 if (HINT && p >= np)
@@ -840,7 +897,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                 __syncthreads();
                 publish();
                 if (!HINT && p == 0)
-                    lost = sLost[(j + 1) & 1];
+                    found = sFound[(j + 1) & 1];
                 if (p + 1 < kNP && p + 1 < np)
                     stage(cur, p + 1 < kNP ? p + 1 : 0, j, wq + 1);
                 else
@@ -852,7 +909,12 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
             for (int d = 0; d < NPF + 3; ++d)
                 wq[d] = wq[d + 1];
             wq[NPF + 3] = wnext;
-            return !HINT && __builtin_amdgcn_readfirstlane(lost) == (int32_t)(j + 1);
+            // (the matrix waves scale P_j: from P_{j-1} on its products are in range)
+            if (kScales && OUT == kOutLambda && fade > 0.0f && found == ~(int32_t)(j + 1)) {
+                fade = 0.0f;
+                scaled = (int32_t)j;
+            }
+            return !HINT && __builtin_amdgcn_readfirstlane(found) == (int32_t)(j + 1);
         };
         for (int64_t j = K - 2; j >= 0 && !again; j -= NPF) {
             again = slot(pf[0], pf[NPF - 1], j);

@@ -110,7 +110,9 @@ RANGE = {"inf": (0, {3: float("inf")}), "inf at the end": (0, {10: float("inf")}
          "both infinities": (0, {2: float("-inf"), 4: float("inf")}), "nan": (0, {3: float("nan")}),
          "huge": (5, {3: 3.4e38}), "huge at the end": (5, {10: -3.4e38}), "decaying": (10, {}),
          "small at the start": ([112] + [0] * 10, {}), "small at the end": ([0] * 10 + [112], {}),
-         "grown, then small": ([112] + [-10] * 10, {})}
+         "grown, then small": ([112] + [-10] * 10, {}), "fading": ([2] * 38, {}),
+         "fading, then grown": ([-4] * 20 + [3] * 28, {}),
+         "fading, then grown past the scale": ([-8] * 20 + [3] * 28, {})}
 
 
 @pytest.mark.parametrize("cycle", [None, (32, 64, 128), (128, 16)], ids=["full", "mixed", "thin"])
@@ -127,9 +129,9 @@ def test_wide_whole_float32_range(what, affine, cycle):
     A finite planted value makes a row of its slot out of one entry of the adjoint
     after it, so that row's relative error is that entry's: the bar times the norm of
     the slot after it over that entry."""
-    K = 11
     shift, planted = RANGE[what]
-    shift = torch.tensor([shift] * K if isinstance(shift, int) else shift)
+    shift = torch.tensor([shift] * 11 if isinstance(shift, int) else shift)
+    K = len(shift)
     widths = synth.cyclic_widths(K, cycle or (128,))
     x = synth.random_chain(2, K, 128, seed=97, widths=widths, affine=affine)
     x.A[0] = torch.ldexp(x.A[0], -shift[:, None, None])
@@ -190,3 +192,39 @@ def test_wide_whole_float32_range(what, affine, cycle):
                                              p.lamK.to(DEV), list(widths)).cpu()
         r = synth.unpack_ragged(r, widths, 128)
         assert torch.equal(r[:, live].view(torch.int32), lam.cpu()[:, live].view(torch.int32))
+
+
+@pytest.mark.parametrize("cycle", [None, (32, 64, 128)], ids=["full", "mixed"])
+def test_wide_range_in_rescanned_segments(cycle):
+    """What the split cannot hold, in chains whose segments are folded to their
+    aggregates only and scanned again from their carries (past 256 MiB of composites):
+    as the fp32 matrix cores give it, the other chains at the parity bar."""
+    B, K = 70, 128
+    widths = synth.cyclic_widths(K, cycle or (128,))
+    x = synth.random_chain(B, K, 128, seed=85, widths=widths, affine=False)
+    x.A[0, 40, 5, 7] = float("inf")
+    x.A[1, 107, 5, 7] = 3.4e38
+    x.A[1, 108:] *= 2.0 ** -3
+    x.A[2, 120] = torch.ldexp(x.A[2, 120], torch.tensor(-112))
+    x.A[2, :120] = torch.ldexp(x.A[2, :120], torch.tensor(1))
+    x.A[3, 16:27] = torch.ldexp(x.A[3, 16:27], torch.tensor(-10))  # within a segment or two
+    x.A[3, 27:] = torch.ldexp(x.A[3, 27:], torch.tensor(1))
+    g = x.to(DEV)
+    hint = None if cycle is None else list(widths)
+    lam, want = (binding.lbi_scan_backward_ex(g.A, None, g.lamK, hint, math,
+                                              binding.LBI_ALGO_TWO_LEVEL).cpu()
+                 for math in (binding.LBI_MATH_DEFAULT, binding.LBI_MATH_F32_MFMA))
+    live = torch.arange(128) < torch.tensor(widths[:K])[:, None]
+    assert torch.equal(lam[:, live].isnan(), want[:, live].isnan())
+    assert torch.equal(lam[:, live].isinf(), want[:, live].isinf())
+    ref = oracle.recurrence(x.A[2:], None, x.lamK[2:])
+    got = lam[2:].numpy().astype(np.float64)
+    for j in range(K):  # slot by slot: a slot's norm may be 1e-30 of another's
+        err = np.linalg.norm(got[:, j] - ref[:, j], axis=1) / np.linalg.norm(ref[:, j], axis=1)
+        assert err.max() <= 4 * TOL, (j, err.argmax(), err.max())
+    ok = want[1][live].isfinite()
+    assert bool(ok.all())
+    a, b = lam[1][live].double(), want[1][live].double()
+    after = want[1, 108]
+    factor = float(after.double().norm() / after[7].abs())
+    assert float((a - b).norm() / b.norm()) <= factor * TOL

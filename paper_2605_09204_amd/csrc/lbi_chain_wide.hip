@@ -50,8 +50,8 @@
 // every CU busy the MFMAs run at 1.0-1.2 PFLOP/s of bf16 products, where a
 // large library matrix product reaches 1.4 on the same card.  192 chains of 24
 // slots: 119 us against 218 with the workgroup kernel on the fp32 matrix cores;
-// 256 x 128: 757 against 1163; widths cycling 32/64/128, 1024 x 64: 681 against
-// 807 (compact storage 701 against 790).
+// 256 x 128: 757 against 1163; widths cycling 32/64/128, 1024 x 64: 690 against
+// 807 (compact storage 704 against 790).
 //
 // All HIP code here is built with packed fp32 math disabled.
 

@@ -29,29 +29,27 @@
 //   * Range.  Three bf16 parts hold an fp32 value to its last bit from 2^-110 up
 //     to where it rounds to an infinity in bf16 (about 3.396e38); an infinity, or
 //     a value past that, leaves NaN parts, and a smaller one keeps only its bits
-//     from 2^-133 up.  A P that fades is scaled by 2^64 long before that (but for
-//     lambda with a hint).  A segment in which a loss can show is done again from
-//     its end on the fp32 matrix cores (exact_pass), so the kernel's results are
-//     those of float32 products over float32's whole range.  What shows it, with
-//     lambda: a row of lambda_s that is not finite, or not zero and below 2^-96 of
-//     the largest entry of lambda_K (until P is scaled) or of the same row at s + 1
-//     (what was lost is otherwise below 2^-29 of every row; a P_s that fades beside
-//     affine terms needs neither).  With composites, the largest magnitude of a
-//     quarter column of P_s (a lane's): 2^126 or more, or not zero and below 2^-96
-//     (until P is scaled) or below 2^-96 of the quarter's at s + 1; and a NaN in the
-//     segment's last composite.  The checks cost up to 3% of a lambda pass and 5% of
-//     a hinted composite pass.  64 chains of 200 slots that halve at each take what
-//     others take (0.94 ms; on the fp32 matrix cores 1.78).  A segment done again
-//     takes 11-12 us a slot (scan_chain_kernel on the fp32 matrix cores 9; widths
-//     32/64/128 without b, 512 x 400, which fade past 2^-96, 5.0 ms against 2.0).
+//     from 2^-133 up.  A P that fades is therefore scaled by 2^64, once, long before
+//     that: with lambda by each matrix wave for its columns, where a sum over them
+//     falls below 2^-64 of lambda_K's largest entry there.  A segment in which a loss
+//     can show all the same is done again from its end on the fp32 matrix cores
+//     (exact_pass), so the results are those of float32 products.  What shows it,
+//     with lambda: such a sum below 2^-96 before P is scaled, and a row of lambda_s
+//     that is not finite, or not zero and below 2^-96 of itself at s + 1 (what was
+//     lost is otherwise below 2^-29 of a row).  With composites, the largest magnitude
+//     of a quarter column of P_s (a lane's): 2^126 or more, or not zero and below
+//     2^-96 (until P is scaled) or below 2^-96 of the quarter's at s + 1; and a NaN in
+//     the segment's last composite.  The checks cost up to 4% of a lambda pass without
+//     affine terms, 1% of others, and 5% of a hinted composite pass.  A segment done
+//     again takes 11-12 us a slot (scan_chain_kernel on the fp32 matrix cores 9).
 //
 // What bounds it: a slot is 384 MFMAs of 16 cycles per SIMD (2.6 us at the top
 // clock), with about 500 VALU instructions of the matrix wave beside them; with
 // every CU busy the MFMAs run at 1.0-1.2 PFLOP/s of bf16 products, where a
 // large library matrix product reaches 1.4 on the same card.  192 chains of 24
 // slots: 119 us against 218 with the workgroup kernel on the fp32 matrix cores;
-// 256 x 128: 757 against 1163; widths cycling 32/64/128, 1024 x 64: 690 against
-// 807 (compact storage 704 against 790).
+// 256 x 128: 757 against 1163; widths cycling 32/64/128, 1024 x 64: 675 against
+// 807 (compact storage 698 against 790).
 //
 // All HIP code here is built with packed fp32 math disabled.
 
@@ -368,14 +366,12 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     // entry s & 1
     __shared__ __attribute__((aligned(16))) float sC[4][kR];
     __shared__ __attribute__((aligned(16))) float sPart[OUT == kOutLambda ? 2 : 1][4][kR];
-    // range: the latest slot whose results show a loss (-1: none).  Entry j & 1 holds j
-    // when that was found in the loop's slot j, or ~j for a lambda below kFade of
-    // lambda_K; all waves read it in the next slot, and end the loop with that one, or
-    // scale P (with a hint they go on to the last slot: another way out of those loops
-    // costs them registers that they do not have)
+    // range: the latest slot whose results show a loss (-1: none).  Entry j & 1 holds
+    // j when that was found in the loop's slot j; all waves read it in the next slot
+    // and end the loop with that one (with a hint they go on to the last slot: another
+    // way out of those loops costs them registers that they do not have)
     __shared__ int32_t sWorst, sFound[2];
     __shared__ int64_t sNpub;  // (streaming) publications made
-    __shared__ float sTop[2];  // the largest entry of lambda_K in each half
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -407,9 +403,6 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     // (writing composites, every row block is formed: the shapes of the product
     // do not fit the registers beside the stores)
     constexpr bool kShapes = HINT && OUT == kOutLambda;
-    // whether a fading P is scaled (kFade).  With a hint a lambda pass does such a
-    // segment again instead: reading the flag costs its short slots 8%.
-    constexpr bool kScales = OUT == kOutComposite || !HINT;
     // panels of a tile with wc column blocks; its row pitch in storage
     auto panels = [](int wc) { return HINT ? (wc + 1) >> 1 : kNP; };
     auto pitch = [](int wc) { return compact ? 16 * wc : kR; };
@@ -432,10 +425,32 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
     if (w < 4) {
         // ---- matrix waves ---------------------------------------------------
         float lk[NT] = {};
+        int up = 0;
+        // (lambda) sums below fade show that P fades: it is then scaled, once
+        float fade = 0.0f;
+        bool fades = false;
         if constexpr (OUT == kOutLambda) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 lk[t] = lambda_end(16 * (w + 4 * t) + li);
+            // The wave's part of lambda_K is taken times 2^up, so that its largest entry
+            // is at least 1 and no sum vanishes before the check below has seen it
+            // (the sums are taken times 2^-up).
+            float end = fabsf(lk[0]);
+            if (NT == 2)
+                end = fmaxf(end, fabsf(lk[NT - 1]));
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1)
+                end = fmaxf(end, __shfl_xor(end, o));
+            end = bitsf(__builtin_amdgcn_readfirstlane(fbits(end)));
+            if (end > 0.0f && end < 1.0f) {
+                up = 1 - __builtin_amdgcn_frexp_expf(end);
+                end = 1.0f;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    lk[t] = ldexpf(lk[t], up);
+            }
+            fade = end * kFade;
         }
         float *Pout = OUT == kOutComposite ? args.Pout + cslot * (int64_t)(kR * kR) : nullptr;
         bool faded = false;  // P is scaled, and what is formed from it is taken times down
@@ -464,7 +479,17 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     q[4 * I + v] = column_sum<NT>(P[4 * h + I], v, lk);
             group_reduce<16, 16>(q, li);
             // lane li holds value li (= 4 I + v)
-            sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = q[0] * down;
+            sPart[s & 1][w][64 * h + 16 * (li >> 2) + 4 * g + (li & 3)] = ldexpf(q[0], -up);
+            const float a = fabsf(q[0]);
+            const bool low = a > 0.0f && a < fade;
+            if (__builtin_expect(__any(low), 0)) {
+                fades = true;
+                if (low && a < fade * (kShow * kUp)) {
+                    atomicMax(&sWorst, (int32_t)s);
+                    if (!HINT)
+                        sFound[(s - 1) & 1] = (int32_t)(s - 1);
+                }
+            }
         };
         f4 P[8][NT];
         {
@@ -501,6 +526,9 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         auto scale_up = [&](f4(&X)[8][NT]) {
             faded = true;
             down = kDown;
+            up += 64;
+            fade = 0.0f;
+            fades = false;
 #pragma unroll
             for (int I = 0; I < 8; ++I)
 #pragma unroll
@@ -607,9 +635,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     for (int t = 0; t < NT; ++t)
                         before[t] *= kUp;
                 }
-            } else if (kScales &&
-                       __builtin_expect(
-                           !faded && __builtin_amdgcn_readfirstlane(found) == ~(int32_t)(j + 1), 0)) {
+            } else if (__builtin_expect(fades, 0)) {
                 scale_up(Pn);
             }
 #pragma unroll
@@ -778,10 +804,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         int32_t pub_left = args.pchunk;
         int64_t pub = -1;  // slots final once the next barrier is passed, or -1
         int64_t npub = 0;  // publications so far
-        // of the range check: bounds from lambda_K (kFade of it, until P is scaled; kShow,
-        // for slots from `scaled` on) and from slot s + 1
-        float fade = 0.0f, show = 0.0f, row = 0.0f;
-        int32_t scaled = 0;
+        float row = 0.0f;  // the range check's bound, from slot s + 1
         // (j: the loop's slot, or -1 past it)
         auto finish = [&](int64_t s, int wr, int64_t j) {
             const int nrow = compact ? 16 * wr : kR;
@@ -798,16 +821,10 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
                     if (st < nrow)
                         lam[st] = p + c;
                     const float a = fabsf(p + c);
-                    const bool below = a > 0.0f && (a < row || (a < show && s >= scaled));
-                    if (__builtin_expect(!(a < kFull) || below || (kScales && a > 0.0f && a < fade),
-                                         0)) {
-                        if (!(a < kFull) || below) {
-                            atomicMax(&sWorst, (int32_t)s);
-                            if (!HINT && j >= 0)
-                                sFound[j & 1] = (int32_t)j;
-                        } else if (j >= 0) {
-                            sFound[j & 1] = ~(int32_t)j;
-                        }
+                    if (__builtin_expect(!(a < kFull) || (a > 0.0f && a < row), 0)) {
+                        atomicMax(&sWorst, (int32_t)s);
+                        if (!HINT && j >= 0)
+                            sFound[j & 1] = (int32_t)j;
                     }
                     row = a * kShow;
                 } else if (args.cout && (!args.agg_only || s == 0)) {
@@ -861,21 +878,7 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
         if (compact)
             curB -= 16 * blocks(K - 1);
         load_b(K - 2, blocks(K - 2));
-        if constexpr (OUT == kOutLambda) {
-            if (st < kR) {
-                float top = fabsf(lambda_end(st));
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1)
-                    top = fmaxf(top, __shfl_xor(top, o));
-                if (lane == 0)
-                    sTop[st >> 6] = top;
-            }
-        }
         __syncthreads();
-        if constexpr (OUT == kOutLambda) {
-            fade = fmaxf(sTop[0], sTop[1]) * kFade;
-            show = fmaxf(sTop[0], sTop[1]) * kShow;
-        }
         // wq[d]: blocks of slot j + 2 - d in the slot loop below
         int wq[NPF + 4];
 #pragma unroll
@@ -909,11 +912,6 @@ __global__ __launch_bounds__(512) void scan_wide_kernel(const ScanArgs args)
             for (int d = 0; d < NPF + 3; ++d)
                 wq[d] = wq[d + 1];
             wq[NPF + 3] = wnext;
-            // (the matrix waves scale P_j: from P_{j-1} on its products are in range)
-            if (kScales && OUT == kOutLambda && fade > 0.0f && found == ~(int32_t)(j + 1)) {
-                fade = 0.0f;
-                scaled = (int32_t)j;
-            }
             return !HINT && __builtin_amdgcn_readfirstlane(found) == (int32_t)(j + 1);
         };
         for (int64_t j = K - 2; j >= 0 && !again; j -= NPF) {

@@ -112,7 +112,8 @@ RANGE = {"inf": (0, {3: float("inf")}), "inf at the end": (0, {10: float("inf")}
          "small at the start": ([112] + [0] * 10, {}), "small at the end": ([0] * 10 + [112], {}),
          "grown, then small": ([112] + [-10] * 10, {}), "fading": ([2] * 38, {}),
          "fading, then grown": ([-4] * 20 + [3] * 28, {}),
-         "fading, then grown past the scale": ([-8] * 20 + [3] * 28, {})}
+         "fading, then grown past the scale": ([-8] * 20 + [3] * 28, {}),
+         "vanishing beside a small lambda_K": ([0] * 4 + [-100, 60, 60] + [0] * 4, {})}
 
 
 @pytest.mark.parametrize("cycle", [None, (32, 64, 128), (128, 16)], ids=["full", "mixed", "thin"])
@@ -126,6 +127,8 @@ def test_wide_whole_float32_range(what, affine, cycle):
     another's), in every form of the launch.  A second, ordinary chain beside the
     planted one keeps its results.
 
+    Entries below float32's normal range are held to its spacing there, 2^-149.
+
     A finite planted value makes a row of its slot out of one entry of the adjoint
     after it, so that row's relative error is that entry's: the bar times the norm of
     the slot after it over that entry."""
@@ -135,8 +138,11 @@ def test_wide_whole_float32_range(what, affine, cycle):
     widths = synth.cyclic_widths(K, cycle or (128,))
     x = synth.random_chain(2, K, 128, seed=97, widths=widths, affine=affine)
     x.A[0] = torch.ldexp(x.A[0], -shift[:, None, None])
-    if affine:  # as large as the adjoint beside it
-        x.b[0] = torch.ldexp(x.b[0], -shift.flip(0).cumsum(0).flip(0)[:, None])
+    end = -60 if "small lambda_K" in what else 0
+    x.lamK[0] = torch.ldexp(x.lamK[0], torch.tensor(end))
+    if affine:  # as large as the adjoint beside it (that float32 holds)
+        scale = (end - shift.flip(0).cumsum(0).flip(0)).clamp(min=-120)
+        x.b[0] = torch.ldexp(x.b[0], scale[:, None])
     tol = TOL
     finite = [j for j, v in planted.items() if np.isfinite(v)]
     if finite:
@@ -160,7 +166,8 @@ def test_wide_whole_float32_range(what, affine, cycle):
         slot = torch.arange(K).repeat_interleave(torch.tensor(widths[:K]))
         for j in range(K):
             a, e = ((t * ok)[:, slot == j].nan_to_num(0, 0, 0).double() for t in (got, exact))
-            err = (a - e).flatten(1).norm(dim=1) / e.flatten(1).norm(dim=1).clamp(min=1e-45)
+            err = ((a - e).flatten(1).norm(dim=1) - a[0].numel() ** 0.5 * 2.0 ** -149).clamp(min=0)
+            err /= e.flatten(1).norm(dim=1).clamp(min=1e-45)
             assert float(err[0]) <= tol and float(err[1]) <= TOL, (what, j, err)
 
     fp32 = binding.LBI_MATH_F32_MFMA

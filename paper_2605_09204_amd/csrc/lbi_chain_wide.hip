@@ -947,8 +947,8 @@ hipError_t launch_chain_wide_f32x(const ChainLaunch &c)
     // r_K <= 64: P's columns from 64 on are zero, and a matrix wave that holds one column
     // block instead of two has half of the splits, copies and sums beside its products,
     // which is what bounds a slot of few row blocks (the same results: the rest adds
-    // exact zeros).  Two blocks / one, us: widths 32/64/128, 1024 x 64, with b 715 / 681,
-    // compact without b 693 / 641; width 32, 600 x 64 268 / 235; width 64 652 / 611.  The
+    // exact zeros).  Two blocks / one, us: widths 32/64/128, 1024 x 64, with b 715 / 675,
+    // compact without b 693 / 643; width 32, 600 x 64 268 / 235; width 64 652 / 587.  The
     // fp32 matrix cores take 807, 663, 392 and 542 there: chains of no width above 64
     // belong in r = 64 storage.  (Segments end in widths of their own.)
     const bool narrow = c.ncol <= 4 && c.args.S == 1;
